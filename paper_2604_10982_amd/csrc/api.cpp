@@ -88,22 +88,6 @@ struct psm_ctx {
   std::vector<TuneKey> tuned;
 };
 
-namespace psm {
-
-// Persistent grids: as many blocks as fit on the device at once.
-int tile_grid(const Layout& L, int sched, const void* kernel, size_t dyn_lds) {
-  if (sched != kSchedPersistent) return xcd_grid(L.tiles);
-  int dev = 0, cus = 0, per_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    cus = 256;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, dyn_lds) != hipSuccess || per_cu < 1)
-    per_cu = 1;
-  const int64_t g = (int64_t)cus * per_cu;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(g, L.tiles));
-}
-
-}  // namespace psm
-
 // ----------------------------------------------------- static workspace
 // For callers that cannot allocate device memory: a file-scope device array
 // used as the workspace of psm_forward_static.  Each device holds its own
@@ -258,6 +242,7 @@ CamTable cam_table(const psm_camera* cams, int32_t n_cams, int64_t n, const psm_
   t.th = kTilePix / t.tw;
   t.tsh = 0;
   while ((1 << t.tsh) < t.tw) ++t.tsh;
+  t.ssh = t.tw == 64 ? 4 : 3;
   int tile = 0;
   int64_t pix = 0;
   for (int b = 0; b < n_cams; ++b) {
@@ -359,7 +344,7 @@ void enqueue_forward(const SurfelArgs& sa, const CamTable& ct, const psm_config*
   launch_scan_counts(L, ws, st);
   prof.end(kStageScan, st);
   prof.begin(kStageEmit, st);
-  launch_emit(ct, cfg->tile_mode, L, ws, st);
+  launch_emit(ct, cfg->tile_mode, lp, L, ws, st);
   prof.end(kStageEmit, st);
   prof.begin(kStagePairSort, st);
   radix_sort_pairs((uint32_t*)(ws + L.ptile0), (uint32_t*)(ws + L.eid0), (uint32_t*)(ws + L.ptile1),
@@ -459,13 +444,12 @@ psm_status read_stats_impl(psm_ctx* ctx, const void* workspace, int64_t n, const
   r = check_signature(L, h);
   if (r != PSM_OK) return r;
   const bool topk = cfg->blend == PSM_BLEND_TOPK;
-  if (topk) {
-    launch_count_selected(L, (char*)workspace, st);
-    r = check_hip("psm_read_stats selection count");
-    if (r != PSM_OK) return r;
-    r = read_status(L, workspace, h, st);
-    if (r != PSM_OK) return r;
-  }
+  launch_sum_stats(L, (char*)workspace, st);
+  if (topk) launch_count_selected(L, (char*)workspace, st);
+  r = check_hip("psm_read_stats counters");
+  if (r != PSM_OK) return r;
+  r = read_status(L, workspace, h, st);
+  if (r != PSM_OK) return r;
   std::memset(out, 0, sizeof(*out));
   out->n = n;
   out->visible = h[kStVisible];

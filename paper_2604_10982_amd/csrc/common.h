@@ -24,9 +24,10 @@ constexpr float kAlphaMax = 0.99f;
 constexpr float kTMin = 1e-4f;
 
 // A tile has kTilePix = 256 pixels, one per thread of a 4-wave block: tw x th
-// pixels with tw in {8, 16, 32, 64} (a launch choice, 16 x 16 by default),
-// row-major inside the tile, so wave w owns the tile rows
-// [w * 64 / tw, (w + 1) * 64 / tw).
+// pixels with tw in {8, 16, 32, 64} (a launch choice, 16 x 16 by default).
+// Wave w owns a sub-tile of 8 x 8 pixels (16 x 4 in a 64 x 4 tile), the
+// sub-tiles row-major in the tile and the pixels row-major in the sub-tile: a
+// compact sub-tile meets fewer of the tile's surfels than 16 x 4 rows do.
 constexpr int kTilePix = 256;
 constexpr int kTileDefault = 16;
 constexpr int kMaxK = 32;
@@ -46,13 +47,13 @@ enum : int {
   kStTiles = 9,    // number of tiles (length of the tile work order)
   kStReqLo = 10,   // required pairs, 64-bit
   kStReqHi = 11,
-  kStWalked = 12,  // 64-bit: pixel x list-entry evaluations of the forward walk
-  kStBlended = 14, // 64-bit: blended (pixel, surfel) pairs
-  kStQueue = 16,   // 16 .. 19: work-queue heads of the persistent tile kernels
+  // walk counters, 64-bit, written by the stats read-back from the walk's slots
+  kStWalked = 12,  // pixel x list-entry evaluations of the forward walk
+  kStBlended = 14, // blended (pixel, surfel) pairs
   kStWide = 20,    // tiles the Top-K blend left to its windowed pass
   kStSigCap = 21,  // layout the forward ran with: pair capacity, tiles, total bytes (64-bit)
   kStSigTiles = 22,
-  kStBwdEntries = 24,  // 64-bit: sum over pixels of n_last (list entries the backward walk must evaluate)
+  kStBwdEntries = 24,  // sum over pixels of n_last (list entries the backward walk must evaluate)
   kStSigLo = 26,
   kStSigHi = 27,
   kStUnique = 28,  // 64-bit, written by the stats read-back: distinct selected virtual surfels
@@ -66,7 +67,6 @@ enum : int {
 static_assert(kStReqLo % 2 == 0 && kStWalked % 2 == 0 && kStBlended % 2 == 0 && kStBwdEntries % 2 == 0 &&
                   kStUnique % 2 == 0 && kStSelected % 2 == 0 && kStSelPairs % 2 == 0 && kStSigLo % 2 == 0,
               "64-bit status words sit at even word indices");
-enum : int { kQWalk = 0, kQBlend = 1, kQFeatBwd = 2, kQWalkBwd = 3 };
 // Radix sort tiling.
 // Surfels with more flagged feature-gradient rows than this (over all
 // cameras) have them summed by a block of their own rather than a lane group.
@@ -99,6 +99,7 @@ struct CamTable {
   int n;
   int64_t nsurf;
   int tw, th, tsh;  // tile width and height in pixels (tw * th = 256), log2(tw)
+  int ssh;          // log2 of the sub-tile width
   CamArgs cam[kMaxCams];
   int ntx[kMaxCams], nty[kMaxCams];
   int tile0[kMaxCams + 1];
@@ -106,8 +107,12 @@ struct CamTable {
 };
 
 // Tile-local column and row of pixel p (0..255) of a tile.
-__host__ __device__ inline int tile_lx(const CamTable& ct, int p) { return p & (ct.tw - 1); }
-__host__ __device__ inline int tile_ly(const CamTable& ct, int p) { return p >> ct.tsh; }
+__host__ __device__ inline int tile_lx(const CamTable& ct, int p) {
+  return (p & ((1 << ct.ssh) - 1)) + (((p >> 6) & ((1 << (ct.tsh - ct.ssh)) - 1)) << ct.ssh);
+}
+__host__ __device__ inline int tile_ly(const CamTable& ct, int p) {
+  return ((p & 63) >> ct.ssh) + (((p >> 6) >> (ct.tsh - ct.ssh)) << (6 - ct.ssh));
+}
 
 // Where global tile g lies: its camera, tile coordinates and image.
 struct TileLoc {
@@ -164,8 +169,8 @@ inline Layout make_layout(const CamTable& ct, int k, int c, int64_t cap) {
   auto take = [&](size_t bytes) { size_t at = o; o = align256(o + bytes); return at; };
   L.status = take(kStWords * 4);  // first, so a read-back can check the layout before any other access
   L.rec = take(n1 * 16 * kRecWords);  // walk record
-  L.fp = take(n1 * 48);           // footprint floats, 12
-  L.ext = take(n1 * 16);          // ellipse centre and half-extents (x, y), for band culling
+  L.fp = take(n1 * 32);           // footprint of the tile lists, 8 floats
+  L.ext = take(n1 * 32);          // sub-tile culling record of the walks, 8 floats
   L.key0 = take(n1 * 4);          // depth keys (sort ping-pong)
   L.key1 = take(n1 * 4);
   L.id0 = take(n1 * 4);           // virtual surfel ids (sort ping-pong)
@@ -206,6 +211,18 @@ inline Layout make_layout(const CamTable& ct, int k, int c, int64_t cap) {
   return L;
 }
 
+// Walk counters: every wave of the forward walk adds its three sums (entries
+// walked, contributors, entries up to the last contributor) to one of
+// stat_slots 128-byte lines, and the stats read-back adds up the lines.  One
+// shared line took 9 ns per addition whatever the walk did: 0.88 of 0.90 ms
+// for the 98k additions of a 1080p frame.  The lines are the sort's histogram
+// area, which is free once the pairs are sorted (16 lines at least).
+constexpr int kStatLine = 16;  // 64-bit words per line
+__host__ __device__ inline int stat_slots(const Layout& L) {
+  const int64_t lines = (int64_t)((L.bsum - L.hist) / (8 * kStatLine));
+  return lines >= 256 ? 256 : (lines >= 64 ? 64 : 16);
+}
+
 // ------------------------------------------------------------ walk record
 // Per surfel (global, 6 x 16 bytes), computed in FP64 from the FP32 inputs:
 //   d0 = (Ai00, Ai01), d1 = (Ai10, Ai11)   FP64: inverse of A, the centred,
@@ -227,26 +244,54 @@ struct __align__(16) WalkRec {
 };
 static_assert(sizeof(WalkRec) == 16 * kRecWords, "walk record layout");
 
-// Tile-local copy staged in LDS: the tile origin's offset (ox, oy) from the
-// centre, so a pixel's offset is d = (lx + ox, ly + oy) for its tile-local
-// centre (lx, ly).
+// The record as the per-pixel evaluation takes it.
 struct LRec {
-  double a00, a01, a10, a11, e0, e1, ox, oy;
+  double a00, a01, a10, a11, e0, e1, xc, yc;
   float mz, o, r, g, b, n0, n1, n2;
 };
 
-// LDS staging of a batch of tile-local records (structure of arrays, so a
-// batch is written with consecutive addresses and read by broadcast).
+// Walk record by a wave-uniform surfel id through the scalar cache: 24 words
+// in scalar registers, which the per-pixel arithmetic takes as operands, so an
+// entry costs no LDS traffic and no vector registers.  (The records are
+// written by an earlier kernel: nothing in a walk writes them.)
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+struct SRec {
+  u32x16 a;
+  u32x8 b;
+  __device__ __forceinline__ LRec get() const {
+    LRec s;
+    auto d = [](uint32_t lo, uint32_t hi) { return __hiloint2double((int)hi, (int)lo); };
+    s.a00 = d(a[0], a[1]); s.a01 = d(a[2], a[3]); s.a10 = d(a[4], a[5]); s.a11 = d(a[6], a[7]);
+    s.e0 = d(a[8], a[9]); s.e1 = d(a[10], a[11]); s.xc = d(a[12], a[13]); s.yc = d(a[14], a[15]);
+    s.mz = __uint_as_float(b[0]); s.o = __uint_as_float(b[1]); s.r = __uint_as_float(b[2]); s.g = __uint_as_float(b[3]);
+    s.b = __uint_as_float(b[4]); s.n0 = __uint_as_float(b[5]); s.n1 = __uint_as_float(b[6]); s.n2 = __uint_as_float(b[7]);
+    return s;
+  }
+};
+__device__ __forceinline__ SRec load_rec(const WalkRec* rec, uint32_t id) {
+  const uint64_t p = (uint64_t)rec + (uint64_t)id * sizeof(WalkRec);
+  SRec r;
+  r.a = *(const __attribute__((address_space(4))) u32x16*)p;
+  r.b = *(const __attribute__((address_space(4))) u32x8*)(p + 64);
+  return r;
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
+}
+
+// LDS staging of a batch of records (structure of arrays, so a batch is
+// written with consecutive addresses and read by broadcast).
 template <int B>
 struct Staged {
   double2 a0[B], a1[B], e[B], o[B];
   float4 f0[B], f1[B];
 
-  __device__ __forceinline__ void put(int slot, const WalkRec& r, float tx0, float ty0) {
+  __device__ __forceinline__ void put(int slot, const WalkRec& r) {
     a0[slot] = r.d0;
     a1[slot] = r.d1;
     e[slot] = r.d2;
-    o[slot] = make_double2((double)tx0 - r.d3.x, (double)ty0 - r.d3.y);
+    o[slot] = r.d3;
     f0[slot] = r.f0;
     f1[slot] = r.f1;
   }
@@ -255,7 +300,7 @@ struct Staged {
     const double2 x0 = a0[k], x1 = a1[k], x2 = e[k], x3 = o[k];
     const float4 y0 = f0[k], y1 = f1[k];
     s.a00 = x0.x; s.a01 = x0.y; s.a10 = x1.x; s.a11 = x1.y;
-    s.e0 = x2.x; s.e1 = x2.y; s.ox = x3.x; s.oy = x3.y;
+    s.e0 = x2.x; s.e1 = x2.y; s.xc = x3.x; s.yc = x3.y;
     s.mz = y0.x; s.o = y0.y; s.r = y0.z; s.g = y0.w;
     s.b = y1.x; s.n0 = y1.y; s.n1 = y1.z; s.n2 = y1.w;
     return s;
@@ -278,60 +323,85 @@ struct PixEval {
   bool clamped, filt;
 };
 
+// Evaluated without branches: a wave reaches it with entries that meet its
+// sub-tile, of which nearly every one has a pixel that hits.  A pixel that
+// has stopped passes x = NaN, which fails the hit test.
 template <bool LP = false>
-__device__ __forceinline__ bool eval_pixel(const LRec& s, float lx, float ly, PixEval& e) {
-  const double dx = (double)lx + s.ox, dy = (double)ly + s.oy;
+__device__ __forceinline__ bool eval_pixel(const LRec& s, double x, double y, PixEval& e) {
+  const double dx = x - s.xc, dy = y - s.yc;
   const double u1 = fma(s.a00, dx, s.a01 * dy);
   const double v1 = fma(s.a10, dx, s.a11 * dy);
   const double w1 = 1.0 - fma(s.e0, dx, s.e1 * dy);
-  const double num = fma(u1, u1, v1 * v1);
-  float rho;
+  const double num = fma(u1, u1, v1 * v1), w2 = w1 * w1;
+  bool hit = (w1 > 0.0) & (num <= 9.0 * w2);
+  e.filt = false;
+  e.dx = (float)dx;
+  e.dy = (float)dy;
+  e.iw = __builtin_amdgcn_rcpf((float)w1);
+  e.u = (float)u1 * e.iw;
+  e.v = (float)v1 * e.iw;
+  float rho = fmaf(e.u, e.u, e.v * e.v);
   if constexpr (LP) {
     const double rf = 2.0 * fma(dx, dx, dy * dy);
-    const bool splat = w1 > 0.0 && num <= rf * (w1 * w1);
-    if (splat ? !(num <= 9.0 * (w1 * w1)) : !(rf <= 9.0)) return false;
+    const bool splat = (w1 > 0.0) & (num <= rf * w2);
+    hit = splat ? num <= 9.0 * w2 : rf <= 9.0;
     e.filt = !splat;
-    e.dx = (float)dx;
-    e.dy = (float)dy;
-    if (splat) {
-      const float wf = (float)w1;
-      e.iw = __builtin_amdgcn_rcpf(wf);
-      e.u = (float)u1 * e.iw;
-      e.v = (float)v1 * e.iw;
-      rho = fmaf(e.u, e.u, e.v * e.v);
-    } else {
-      e.iw = 1.0f;
-      e.u = 0.0f;
-      e.v = 0.0f;
-      rho = 2.0f * fmaf(e.dx, e.dx, e.dy * e.dy);
-    }
-  } else {
-    if (!(w1 > 0.0) || !(num <= 9.0 * (w1 * w1))) return false;
-    e.filt = false;
-    e.dx = (float)dx;
-    e.dy = (float)dy;
-    const float wf = (float)w1;
-    e.iw = __builtin_amdgcn_rcpf(wf);
-    e.u = (float)u1 * e.iw;
-    e.v = (float)v1 * e.iw;
-    rho = fmaf(e.u, e.u, e.v * e.v);
+    e.iw = splat ? e.iw : 1.0f;
+    e.u = splat ? e.u : 0.0f;
+    e.v = splat ? e.v : 0.0f;
+    rho = splat ? rho : 2.0f * fmaf(e.dx, e.dx, e.dy * e.dy);
   }
   e.G = __builtin_amdgcn_exp2f(rho * -0.72134752044448170f);  // exp(-rho/2)
   const float oG = s.o * e.G;
   e.clamped = oG > kAlphaMax;
   e.alpha = e.clamped ? kAlphaMax : oG;
-  return e.alpha >= kAlphaMin;
+  return hit & (e.alpha >= kAlphaMin);
 }
 
-// Band culling of the walks: a wave owns 64 / tw rows of its tile and skips
-// a surfel whose footprint ellipse's y-extent (centre ecy, half-extent ey,
-// the key stage's FP32 values) misses the rows' pixel centres.  The footprint
-// contains every pixel the per-pixel test can hit; the slack covers the FP32
-// rounding of the band edges (ulp(16384) = 2^-9 px).
-constexpr float kBandSlack = 0.015625f;
+// Sub-tile culling of the walks: a wave skips a surfel no pixel centre of its
+// sub-tile can blend.  Per surfel the key stage keeps the ellipse of
+// rho <= min(9, 2 ln(255 o)) (beyond it alpha < 1/255), widened like the
+// footprint, as centre (ecx, ecy), half-extents (ex, ey), the y offset of the
+// rightmost point yr, the slope of the chord midpoints and the half-chord
+// factor, so its x-extent over the rows [y0, y1] of the sub-tile is two
+// clamps and two square roots.  One lane tests one list entry, so a test
+// costs each pixel 1/64 of that.  The slack covers the FP32 rounding of the
+// record and the test (relative 2^-16 of the extents: a thin ellipse's chord is a
+// difference of terms of the size of its extents).  With the low-pass filter
+// the record is the box of the ellipse and the filter's disk.
+struct CullRec {
+  float4 e0;  // ecx, ecy, ex, ey
+  float4 e1;  // yr, slope, half-chord factor, slack (low-pass: xc, yc, rf2, slack)
+};
 
-__device__ __forceinline__ bool band_meets(float ecy, float ey, float yb0, float yb1) {
-  return (ecy + ey) + kBandSlack >= yb0 && (ecy - ey) - kBandSlack <= yb1;
+template <bool LP>
+__device__ __forceinline__ bool rect_meets(const CullRec& c, float x0, float x1, float y0, float y1) {
+  const float sl = c.e1.w, ey = c.e0.w;
+  const float lo = fmaxf((y0 - c.e0.y) - sl, -ey), hi = fminf((y1 - c.e0.y) + sl, ey);
+  float xl, xr;
+  if constexpr (LP) {
+    xl = c.e0.x - c.e0.z;
+    xr = c.e0.x + c.e0.z;
+  } else {
+    const float dr = fminf(fmaxf(c.e1.x, lo), hi), dl = fminf(fmaxf(-c.e1.x, lo), hi);
+    const float s2 = ey * ey;
+    xr = c.e0.x + (c.e1.y * dr + c.e1.z * __builtin_amdgcn_sqrtf(fmaxf(0.0f, s2 - dr * dr)));
+    xl = c.e0.x + (c.e1.y * dl - c.e1.z * __builtin_amdgcn_sqrtf(fmaxf(0.0f, s2 - dl * dl)));
+  }
+  return !(lo > hi) && !(xr + sl < x0) && !(xl - sl > x1);
+}
+
+// Pixel centres of a wave's sub-tile (pixels past the image included).
+struct SubRect {
+  float x0, x1, y0, y1;
+};
+__device__ __forceinline__ SubRect sub_rect(const CamTable& ct, const TileLoc& tl, int wave) {
+  SubRect r;
+  r.x0 = (float)(tl.tx * ct.tw + tile_lx(ct, 64 * wave)) + 0.5f;
+  r.y0 = (float)(tl.ty * ct.th + tile_ly(ct, 64 * wave)) + 0.5f;
+  r.x1 = r.x0 + (float)((1 << ct.ssh) - 1);
+  r.y1 = r.y0 + (float)((64 >> ct.ssh) - 1);
+  return r;
 }
 
 // Tile index of a block: consecutive block ids are dispatched round-robin
@@ -343,32 +413,23 @@ __device__ inline int xcd_tile(int bid, int tiles) {
 }
 inline int xcd_grid(int64_t tiles) { return (int)(((tiles + 7) >> 3) << 3); }
 
-// Tile scheduling of the per-tile kernels.  Grid mode (order == null): one
-// block per tile, XCD-aware.  Persistent mode: a grid that fills the device
-// once takes tiles from a work queue ordered longest list first, so long
-// tiles start early and blocks that finish keep taking work.  Every block
-// leaves the loop once the queue is drained.
-struct TileQueue {
-  const uint32_t* order;  // tile ids, longest list first; null: grid mode
-  uint32_t* head;         // queue head, zero before the launch
+// Tile scheduling of the per-tile kernels, one block per tile.  order == null:
+// neighbouring tiles on one XCD.  Otherwise block i takes tile order[i], the
+// tiles of the longest lists first: blocks are dispatched in index order as
+// others finish, so long tiles start early and short ones fill the gaps, with
+// no queue and no loop over tiles in the kernel (a resident grid taking tiles
+// from an atomic queue kept its arguments live across that loop: 80 spilled
+// scalar registers in the forward walk, and two barriers per tile).
+struct TileOrder {
+  const uint32_t* order;
   int tiles;
 };
 
-template <bool PERSIST, class F>
-__device__ __forceinline__ void for_tiles(const TileQueue& q, int* s_item, F&& body) {
-  if constexpr (!PERSIST) {
-    const int tile = xcd_tile(blockIdx.x, q.tiles);
-    if (tile < q.tiles) body(tile);
-  } else {
-    for (;;) {
-      __syncthreads();  // the previous tile is finished by every thread
-      if (threadIdx.x == 0) *s_item = (int)atomicAdd(q.head, 1u);
-      __syncthreads();
-      const int it = *s_item;
-      if (it >= q.tiles) break;
-      body((int)q.order[it]);
-    }
-  }
+template <class F>
+__device__ __forceinline__ void with_tile(const TileOrder& q, F&& body) {
+  const int b = (int)blockIdx.x;
+  const int tile = q.order ? b : xcd_tile(b, q.tiles);
+  if (tile < q.tiles) body(q.order ? (int)q.order[tile] : tile);
 }
 
 // ------------------------------------------------------------ wave helpers

@@ -68,7 +68,7 @@ void launch_preprocess(const SurfelArgs& s, const CamTable& ct, int mode, bool o
                        const Layout& L,
                        char* ws, hipStream_t st);
 void launch_scan_counts(const Layout& L, char* ws, hipStream_t st);
-void launch_emit(const CamTable& ct, int mode, const Layout& L, char* ws, hipStream_t st);
+void launch_emit(const CamTable& ct, int mode, bool lowpass, const Layout& L, char* ws, hipStream_t st);
 void launch_ranges(const Layout& L, char* ws, hipStream_t st);
 void launch_tile_order(const Layout& L, char* ws, hipStream_t st);
 void launch_export_keys(const Layout& L, char* ws, int32_t* cull, uint32_t* depth, int32_t* count, hipStream_t st);
@@ -79,18 +79,9 @@ void launch_export_keys(const Layout& L, char* ws, int32_t* cull, uint32_t* dept
 void radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, const uint32_t* n_dev,
                       int64_t cap_n, int bits, uint32_t* hist, int64_t nb_max, hipStream_t st);
 
-// Grid of a per-tile kernel: one block per tile, or (persistent) enough
-// blocks to fill the device once.
-int tile_grid(const Layout& L, int sched, const void* kernel, size_t dyn_lds);
-
-// Work queue of a per-tile kernel (work order sorted by the forward; queue
-// heads zeroed before each use).
-inline TileQueue tile_queue(const Layout& L, int sched, char* ws, int q) {
-  TileQueue t;
-  t.tiles = (int)L.tiles;
-  t.order = sched == kSchedPersistent ? (const uint32_t*)(ws + L.torder0) : nullptr;
-  t.head = (uint32_t*)(ws + L.status) + kStQueue + q;
-  return t;
+// Tile order of a per-tile kernel (sorted by the forward).
+inline TileOrder tile_order(const Layout& L, int sched, const char* ws) {
+  return TileOrder{sched == kSchedPersistent ? (const uint32_t*)(ws + L.torder0) : nullptr, (int)L.tiles};
 }
 
 // raster_fwd.hip
@@ -100,6 +91,8 @@ void launch_feature_blend(const SurfelArgs& s, const Layout& L, const CamTable& 
                           float* out_feat, bool renorm, bool lowpass, char* ws, hipStream_t st);
 void launch_export_selection(const Layout& L, const CamTable& ct, char* ws, int32_t* sel_id, float* sel_w,
                              int32_t* n_last, float* t_final, hipStream_t st);
+// Adds up the walk's counters into the status words.
+void launch_sum_stats(const Layout& L, char* ws, hipStream_t st);
 // Counts the distinct selected virtual surfels and the (pixel, slot)
 // selections of the last Top-K forward into the status words.
 void launch_count_selected(const Layout& L, char* ws, hipStream_t st);

@@ -20,7 +20,8 @@ using Cam = CamArgs;
 // Projected cutoff ellipse of a visible surfel; with the low-pass filter also
 // the projected centre and the filter disk's radius^2 (rf2 = 0: no filter).
 struct Foot {
-  float ecx, ecy, S00, S01, S11, ex, ey, gam, kk;
+  float ecx, ecy, S01, S11, ex, ey, gam;
+  float kk;  // chord factor |c detA|; half-size of the isotropic square in its mode
   float xc, yc, rf2;
 };
 
@@ -31,6 +32,7 @@ struct Key {
   float mc2, p, q, xc, yc, A00, A01, A10, A11, dA;
   float nc[3];
   Foot f;
+  CullRec cr;
 };
 
 // Opacity-aware footprint radius^2 (an exact work reduction): a pixel is
@@ -46,11 +48,19 @@ __device__ __forceinline__ float opacity_foot2(float o) {
   return (float)fmin((double)kFoot2, fmax(r, 1.0 / 4096.0));
 }
 
+// Radius^2 beyond which alpha < 1/255 for the walks' sub-tile culling: the
+// same bound with a plain FP32 logarithm and a margin of 2^-8 (absolute) and
+// 2^-9 (relative), far above its rounding.
+__device__ __forceinline__ float cull_foot2(float o) {
+  return fmaxf(2.0f * __logf(255.0f * o) * (1.0f + 0x1p-9f) + 0x1p-8f, 0x1p-12f);
+}
+
 // foot2: footprint radius^2 (kFoot2, or the opacity-aware bound).  The cull
 // decisions always use kFoot2, so both footprints keep the same visible set.
 // lowpass: the footprint also takes the low-pass filter's disk.
+// cull2: radius^2 of the walks' culling ellipse (at most foot2).
 __device__ __forceinline__ Key key_stage(const float* mu, const float* sc, const float* qq, const Cam& k, float foot2,
-                                      int lowpass) {
+                                      float cull2, int mode, int lowpass) {
   Key r;
   r.cull = 0;
   r.flip = 0;
@@ -113,7 +123,7 @@ __device__ __forceinline__ Key key_stage(const float* mu, const float* sc, const
   r.A00 = A00; r.A01 = A01; r.A10 = A10; r.A11 = A11; r.dA = dA;
   r.f.ecx = xc - cc * w0;
   r.f.ecy = yc - cc * w1;
-  r.f.S00 = S00; r.f.S01 = S01; r.f.S11 = S11;
+  r.f.S01 = S01; r.f.S11 = S11;
   r.f.ex = sqrtf(S00);
   r.f.ey = sqrtf(S11);
   r.f.gam = gf;
@@ -121,6 +131,29 @@ __device__ __forceinline__ Key key_stage(const float* mu, const float* sc, const
   r.f.xc = xc;
   r.f.yc = yc;
   r.f.rf2 = lowpass ? 0.5f * foot2 + kLpPad : 0.0f;
+  if (lowpass) {
+    const float rf = sqrtf(r.f.rf2);
+    const float x0 = fminf(r.f.ecx - r.f.ex, xc - rf), x1 = fmaxf(r.f.ecx + r.f.ex, xc + rf);
+    const float y0 = fminf(r.f.ecy - r.f.ey, yc - rf), y1 = fmaxf(r.f.ecy + r.f.ey, yc + rf);
+    r.cr.e0 = make_float4(0.5f * (x0 + x1), 0.5f * (y0 + y1), 0.5f * (x1 - x0), 0.5f * (y1 - y0));
+    r.cr.e1 = make_float4(xc, yc, r.f.rf2, 0.0f);
+  } else {  // the same ellipse formulas at cull2 (not part of a decision)
+    const float gc = 1.0f - cull2 * g2, c2 = cull2 / gc;
+    const float T00 = c2 * ((A00 * A00 + A01 * A01) + c2 * (w0 * w0));
+    const float T01 = c2 * ((A00 * A10 + A01 * A11) + c2 * (w0 * w1));
+    const float T11 = c2 * ((A10 * A10 + A11 * A11) + c2 * (w1 * w1));
+    const float tx = __builtin_amdgcn_sqrtf(T00), it = __builtin_amdgcn_rcpf(T11);
+    r.cr.e0 = make_float4(xc - c2 * w0, yc - c2 * w1, tx, __builtin_amdgcn_sqrtf(T11));
+    r.cr.e1 = make_float4(T01 * __builtin_amdgcn_rcpf(tx), T01 * it,
+                          fabsf(c2 * dA) * it * __builtin_amdgcn_rsqf(gc), 0.0f);
+  }
+  r.cr.e1.w = 0x1p-6f + 0x1p-16f * (r.cr.e0.z + r.cr.e0.w) + 0x1p-20f * (fabsf(r.cr.e0.x) + fabsf(r.cr.e0.y));
+  if (mode == kSphere) {
+    const float hs = 0.5f * (S00 + S11);
+    const float hd = 0.5f * (S00 - S11);
+    const float lmax = hs + sqrtf(hd * hd + S01 * S01);
+    r.f.kk = fmaxf(sqrtf(lmax), fmaxf(r.f.ex, r.f.ey));
+  }
   return r;
 }
 
@@ -185,10 +218,7 @@ __device__ __forceinline__ void for_each_row(const Foot& f, int mode, int W, int
   int ax0, ax1, ay0, ay1;
   float bx0, bx1, by0, by1;
   if (mode == kSphere) {
-    const float hs = 0.5f * (f.S00 + f.S11);
-    const float hd = 0.5f * (f.S00 - f.S11);
-    const float lmax = hs + sqrtf(hd * hd + f.S01 * f.S01);
-    const float rr = fmaxf(sqrtf(lmax), fmaxf(f.ex, f.ey));
+    const float rr = f.kk;
     bx0 = f.ecx - rr;
     bx1 = f.ecx + rr;
     by0 = f.ecy - rr;
@@ -276,7 +306,7 @@ __global__ __launch_bounds__(256) void k_preprocess(
     int64_t nv, const float* __restrict__ means, const float* __restrict__ scales,
     const float* __restrict__ quats, const float* __restrict__ opacity, const float* __restrict__ rgb,
     CamTable ct, int mode, int opacity_foot, int lowpass, WalkRec* __restrict__ rec, float4* __restrict__ fp,
-    float4* __restrict__ ext,
+    CullRec* __restrict__ ext,
     uint32_t* __restrict__ key, uint32_t* __restrict__ ids, uint32_t* __restrict__ count,
     int32_t* __restrict__ cull, uint32_t* __restrict__ status) {
   __shared__ uint32_t s_cnt[5];
@@ -292,7 +322,8 @@ __global__ __launch_bounds__(256) void k_preprocess(
     const int64_t i = v - (int64_t)b * ct.nsurf;
     const Cam& cam = s_cam[b];
     const float foot2 = opacity_foot ? opacity_foot2(opacity[i]) : kFoot2;
-    const Key kk = key_stage(means + 3 * i, scales + 2 * i, quats + 4 * i, cam, foot2, lowpass);
+    const Key kk = key_stage(means + 3 * i, scales + 2 * i, quats + 4 * i, cam, foot2,
+                             fminf(foot2, cull_foot2(opacity[i])), mode, lowpass);
     ids[v] = (uint32_t)v;
     cull[v] = kk.cull | (kk.flip << 8);  // bit 8: normal flipped toward the camera
     atomicAdd(&s_cnt[kk.cull], 1u);
@@ -305,17 +336,9 @@ __global__ __launch_bounds__(256) void k_preprocess(
       for_each_row(kk.f, mode, cam.W, cam.H, ct.tw, ct.th, ct.ntx[b], ct.nty[b],
                    [&](int, int x0, int x1) { c += (uint32_t)(x1 - x0 + 1); });
       count[v] = c;
-      fp[3 * v + 0] = make_float4(kk.f.ecx, kk.f.ecy, kk.f.S00, kk.f.S01);
-      fp[3 * v + 1] = make_float4(kk.f.S11, kk.f.ex, kk.f.ey, kk.f.gam);
-      fp[3 * v + 2] = make_float4(kk.f.kk, kk.f.xc, kk.f.yc, kk.f.rf2);
-      if (lowpass) {  // the walks' band culling sees the union's extent
-        const float rf = sqrtf(kk.f.rf2);
-        const float x0 = fminf(kk.f.ecx - kk.f.ex, kk.f.xc - rf), x1 = fmaxf(kk.f.ecx + kk.f.ex, kk.f.xc + rf);
-        const float y0 = fminf(kk.f.ecy - kk.f.ey, kk.f.yc - rf), y1 = fmaxf(kk.f.ecy + kk.f.ey, kk.f.yc + rf);
-        ext[v] = make_float4(0.5f * (x0 + x1), 0.5f * (y0 + y1), 0.5f * (x1 - x0), 0.5f * (y1 - y0));
-      } else {
-        ext[v] = make_float4(kk.f.ecx, kk.f.ecy, kk.f.ex, kk.f.ey);
-      }
+      fp[2 * v] = make_float4(kk.f.ecx, kk.f.ecy, kk.f.ex, kk.f.ey);
+      fp[2 * v + 1] = make_float4(kk.f.S01, kk.f.S11, kk.f.gam, kk.f.kk);
+      ext[v] = kk.cr;
       walk_record(means + 3 * i, scales + 2 * i, quats + 4 * i, opacity[i], rgb + 3 * i, kk.nc, cam,
                   rec + v);
     }
@@ -415,7 +438,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(int64_t n, const uin
 __global__ __launch_bounds__(256) void k_emit(int64_t nv, const uint32_t* __restrict__ order,
                                               const uint32_t* __restrict__ count,
                                               const uint32_t* __restrict__ offs, const float4* __restrict__ fp,
-                                              CamTable ct, int mode, int64_t cap, uint32_t* __restrict__ vbase,
+                                              const CullRec* __restrict__ ext, int lowpass, CamTable ct, int mode, int64_t cap, uint32_t* __restrict__ vbase,
                                               uint32_t* __restrict__ ptile, uint32_t* __restrict__ eid,
                                               uint32_t* __restrict__ sid_emit) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -425,8 +448,10 @@ __global__ __launch_bounds__(256) void k_emit(int64_t nv, const uint32_t* __rest
   if (count[v] == 0) return;
   const int b = camera_of(ct, v);
   const int ntx = ct.ntx[b], t0 = ct.tile0[b];
-  const float4 f0 = fp[3 * (size_t)v], f1 = fp[3 * (size_t)v + 1], f2 = fp[3 * (size_t)v + 2];
-  const Foot f{f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w, f2.x, f2.y, f2.z, f2.w};
+  const float4 f0 = fp[2 * (size_t)v], f1 = fp[2 * (size_t)v + 1];
+  float4 f2 = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (lowpass) f2 = ext[v].e1;
+  const Foot f{f0.x, f0.y, f1.x, f1.y, f0.z, f0.w, f1.z, f1.w, f2.x, f2.y, f2.z};
   int64_t o = offs[r];
   for_each_row(f, mode, ct.cam[b].W, ct.cam[b].H, ct.tw, ct.th, ntx, ct.nty[b], [&](int ty, int x0, int x1) {
     for (int tx = x0; tx <= x1; ++tx, ++o) {
@@ -462,9 +487,14 @@ __global__ __launch_bounds__(256) void k_finalize_pairs(const uint32_t* __restri
                                                         const uint32_t* __restrict__ eid,
                                                         const uint32_t* __restrict__ sid_emit,
                                                         const uint32_t* __restrict__ status, uint32_t* __restrict__ pid,
-                                                        uint2* __restrict__ ranges) {
+                                                        uint2* __restrict__ ranges, uint64_t* __restrict__ stat,
+                                                        uint32_t slots) {
   const uint32_t P = status[kStP];
   const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j < slots) {  // slots <= 256: the first block clears the walk's counters
+#pragma unroll
+    for (int i = 0; i < 3; ++i) stat[j * kStatLine + i] = 0ull;
+  }
   if (j >= P) return;
   pid[j] = sid_emit[eid[j]];
   const uint32_t t = ptile[j];
@@ -522,7 +552,7 @@ void launch_preprocess(const SurfelArgs& s, const CamTable& ct, int mode, bool o
   hipLaunchKernelGGL(k_preprocess, dim3((unsigned)cdiv(L.n, 256)), dim3(256), 0, st, L.n, s.means, s.scales,
                      s.quats, s.opacity, s.rgb, ct, mode, opacity_foot ? 1 : 0, lowpass ? 1 : 0, (WalkRec*)(ws + L.rec),
                      (float4*)(ws + L.fp),
-                     (float4*)(ws + L.ext),
+                     (CullRec*)(ws + L.ext),
                      (uint32_t*)(ws + L.key0), (uint32_t*)(ws + L.id0), (uint32_t*)(ws + L.count),
                      (int32_t*)(ws + L.cull), (uint32_t*)(ws + L.status));
 }
@@ -538,11 +568,12 @@ void launch_scan_counts(const Layout& L, char* ws, hipStream_t st) {
                      (const uint64_t*)bsum, (uint32_t*)(ws + L.offs));
 }
 
-void launch_emit(const CamTable& ct, int mode, const Layout& L, char* ws, hipStream_t st) {
+void launch_emit(const CamTable& ct, int mode, bool lowpass, const Layout& L, char* ws, hipStream_t st) {
   if (L.n == 0) return;
   hipLaunchKernelGGL(k_emit, dim3((unsigned)cdiv(L.n, 256)), dim3(256), 0, st, L.n,
                      (const uint32_t*)(ws + L.id0), (const uint32_t*)(ws + L.count),
-                     (const uint32_t*)(ws + L.offs), (const float4*)(ws + L.fp), ct, mode, L.cap,
+                     (const uint32_t*)(ws + L.offs), (const float4*)(ws + L.fp), (const CullRec*)(ws + L.ext), lowpass ? 1 : 0,
+                     ct, mode, L.cap,
                      (uint32_t*)(ws + L.vbase), (uint32_t*)(ws + L.ptile0), (uint32_t*)(ws + L.eid0),
                      (uint32_t*)(ws + L.sid_emit));
 }
@@ -555,11 +586,15 @@ void launch_export_keys(const Layout& L, char* ws, int32_t* cull, uint32_t* dept
 }
 
 void launch_ranges(const Layout& L, char* ws, hipStream_t st) {
-  if (L.cap == 0) return;
+  const int slots = stat_slots(L);
+  if (L.cap == 0) {
+    launch_fill_u32(ws + L.hist, 0u, (int64_t)slots * kStatLine * 2, st);
+    return;
+  }
   hipLaunchKernelGGL(k_finalize_pairs, dim3((unsigned)cdiv(L.cap, 256)), dim3(256), 0, st,
                      (const uint32_t*)(ws + L.ptile0), (const uint32_t*)(ws + L.eid0),
                      (const uint32_t*)(ws + L.sid_emit), (const uint32_t*)(ws + L.status), (uint32_t*)(ws + L.pid),
-                     (uint2*)(ws + L.ranges));
+                     (uint2*)(ws + L.ranges), (uint64_t*)(ws + L.hist), (uint32_t)slots);
 }
 
 void launch_tile_order(const Layout& L, char* ws, hipStream_t st) {

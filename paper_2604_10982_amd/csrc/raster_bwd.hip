@@ -58,11 +58,11 @@ constexpr int kQStride = 72;   // bytes per pixel row of the selection map
 // dword, so a lane reads its 4 slot blocks at once.
 __device__ __forceinline__ int qmap_off(int p, int s) { return p * kQStride + (s & 15) * 4 + (s >> 4); }
 
-template <typename FT, int KMAX, int GC, bool PERSIST>
+template <typename FT, int KMAX, int GC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 16 ? 2 : 1))) void k_feat_bwd_topk(
     const uint32_t* __restrict__ pid, const uint32_t* __restrict__ eid, const uint2* __restrict__ ranges,
     const int32_t* __restrict__ selpos, const float* __restrict__ selw, const FeatSrc<FT> feat,
-    const float* __restrict__ gfeat, int C, int K, CamTable ct, TileQueue tq, float* __restrict__ seldot,
+    const float* __restrict__ gfeat, int C, int K, CamTable ct, TileOrder tq, float* __restrict__ seldot,
     float* __restrict__ fpart, uint8_t* __restrict__ fflag, int renorm) {
   static_assert(GC % 16 == 0, "pass width is a multiple of the MFMA tile");
   // Row stride of the staged G and F: = 2 mod 4, so a 16-row x 2-column read
@@ -77,9 +77,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 16 
   __shared__ __align__(16) uint8_t s_q[kTilePix * kQStride];
   __shared__ uint32_t s_fe[kFbSlots];  // emitted pair index per slot
   extern __shared__ float s_w[];       // selection weights, replaced by dots
-  __shared__ int s_item;
 
-  for_tiles<PERSIST>(tq, &s_item, [&](const int tile) {
+  with_tile(tq, [&](const int tile) {
   const TileLoc tl = locate(ct, tile);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
@@ -299,10 +298,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 16 
 // DM (dense mode only): the batch's feature contractions on the matrix cores
 // (true) or in vector FMAs (false); a launch choice, whichever is faster for
 // the workload (the autotuner times both).
-template <int MODE, typename FT, bool PERSIST, bool LP, bool DM>
+template <int MODE, typename FT, bool LP, bool DM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTopK ? 4 : 1))) void k_walk_bwd(
-    const WalkRec* __restrict__ rec, const float4* __restrict__ ext, const uint32_t* __restrict__ pid, const uint32_t* __restrict__ eid,
-    const uint2* __restrict__ ranges, CamTable ct, TileQueue tq, int K, const uint32_t* __restrict__ nlast,
+    const WalkRec* __restrict__ rec, const CullRec* __restrict__ ext, const uint32_t* __restrict__ pid, const uint32_t* __restrict__ eid,
+    const uint2* __restrict__ ranges, CamTable ct, TileOrder tq, int K, const uint32_t* __restrict__ nlast,
     const float* __restrict__ tfinal,
     const int32_t* __restrict__ selpos, const float* __restrict__ seldot, const float* __restrict__ g_rgb,
     const float* __restrict__ g_depth, const float* __restrict__ g_normal, const float* __restrict__ g_alpha,
@@ -314,7 +313,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
   // weights come from eval_pixel, written outside this scope and evaluated
   // exactly as in the forward)
   __shared__ Staged<kBB> s_r;
-  __shared__ float2 s_band[kBB];  // (ecy, ey) of the batch, for band culling
+  __shared__ CullRec s_cull[kBB];  // culling records of the batch
   __shared__ uint32_t s_id[kBB];
   constexpr int kNV = nv_of(LP);
   __shared__ float s_part[4][kBB][kNV];
@@ -333,18 +332,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
   // for K = 16 lets four blocks share a CU, with the kernel's registers held
   // to 128 for four waves per SIMD)
   extern __shared__ int s_sel[];
-  __shared__ int s_item;
 
-  for_tiles<PERSIST>(tq, &s_item, [&](const int tile) {
+  with_tile(tq, [&](const int tile) {
   const TileLoc tl = locate(ct, tile);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tx = tl.tx, ty = tl.ty, W = tl.W, H = tl.H;
-  const int qx0 = tile_lx(ct, tid), qy0 = tile_ly(ct, tid), rpw = 64 >> ct.tsh;  // rows per wave
-  const int px = tx * ct.tw + qx0, py = ty * ct.th + qy0;
+  const int px = tx * ct.tw + tile_lx(ct, tid), py = ty * ct.th + tile_ly(ct, tid);
   const bool inside = px < W && py < H;
-  const float lx = (float)qx0 + 0.5f, ly = (float)qy0 + 0.5f;
-  const float tx0 = (float)(tx * ct.tw), ty0 = (float)(ty * ct.th);
-  const float yb0 = ty0 + (float)(rpw * wave) + 0.5f, yb1 = yb0 + (float)(rpw - 1);  // this wave's rows
+  const double X = (double)px + 0.5, Y = (double)py + 0.5;
+  const SubRect sr = sub_rect(ct, tl, wave);
   const uint32_t start = ranges[tile].x;
   const int sp = tile * kTilePix + tid;
   const int my_last = (int)nlast[sp];
@@ -397,9 +393,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
     if (tid < nb) {
       const uint32_t id = pid[start + lo + tid];
       s_id[tid] = id;  // virtual surfel id
-      s_r.put(tid, rec[id], tx0, ty0);
-      const float4 x = ext[id];
-      s_band[tid] = make_float2(x.y, x.w);
+      s_r.put(tid, rec[id]);
+      s_cull[tid] = ext[id];
     }
     __syncthreads();
 
@@ -490,9 +485,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
       }
     }
 
-    // surfels of the batch whose footprint meets this wave's 4 rows
-    const uint64_t band = __ballot(lane < nb && band_meets(s_band[lane < kBB ? lane : 0].x,
-                                                           s_band[lane < kBB ? lane : 0].y, yb0, yb1));
+    // surfels of the batch that meet this wave's sub-tile
+    const uint64_t band = __ballot(lane < nb && rect_meets<LP>(s_cull[lane < kBB ? lane : 0], sr.x0, sr.x1, sr.y0, sr.y1));
     const int ktop = min(nb - 1, wmax - 1 - lo);
     if (lane > ktop && lane < nb) s_has[wave][lane] = 0u;  // skipped entries: nothing to add
     if constexpr (MODE == kFull)
@@ -508,7 +502,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
       if (pos < my_last && ((band >> k) & 1u)) {
         const LRec s = s_r.get(k);
         PixEval e;
-        if (eval_pixel<LP>(s, lx, ly, e)) {
+        if (eval_pixel<LP>(s, X, Y, e)) {
           contrib = true;
           // 1 / (1 - alpha) once for both quotients: alpha <= 0.99, so the
           // reciprocal's relative error (about 1 ulp) stays that small
@@ -678,9 +672,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
           f4v racc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
           const float* wrow = s_om[16 * eb + li];
           // G of the lane's first pixel (tile column lk, row 0); step t covers
-          // pixels 4 t + lk (row-major in the tile, tw a multiple of 4), whose
-          // offsets from it are the same for all lanes and below 2^29 (W, C
-          // and the tile height are bounded)
+          // pixels 4 t + lk (four neighbours of a sub-tile row), whose offsets
+          // from it are the same for all lanes and below 2^29 (W, C and the
+          // tile height are bounded)
           const float* gt = g_feat + (tl.pix0 + (int64_t)(ty * ct.th) * W + tx * ct.tw + lk) * C + c;
           // 128 pixels (32 steps) at a time: their 32 G values are loaded
           // together, so enough of them are in flight to cover the memory
@@ -689,12 +683,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
             // the shape values go through an empty asm statement so that the
             // step offsets and bounds are formed here and not kept live
             // across units (64 of them would not fit in the registers)
-            int wc = W * C, cs = C, tm = ct.tw - 1, sh = ct.tsh, wlim = wl - lk, hlim = hl;
-            asm volatile("" : "+s"(wc), "+s"(cs), "+s"(tm), "+s"(sh), "+v"(wlim), "+s"(hlim));
+            int wc = W * C, cs = C, sw = ct.ssh, sn = ct.tsh - ct.ssh, wlim = wl - lk, hlim = hl;
+            asm volatile("" : "+s"(wc), "+s"(cs), "+s"(sw), "+s"(sn), "+v"(wlim), "+s"(hlim));
             float b[32];
 #pragma unroll
             for (int t = 0; t < 32; ++t) {
-              const int q4 = 4 * (t0 + t), lx = q4 & tm, ly = q4 >> sh;
+              const int q4 = 4 * (t0 + t), sub = q4 >> 6;  // the sub-tile and the pixel in it
+              const int lx = (q4 & ((1 << sw) - 1)) + ((sub & ((1 << sn) - 1)) << sw);
+              const int ly = ((q4 & 63) >> sw) + ((sub >> sn) << (6 - sw));
               b[t] = lx < wlim && ly < hlim && c < C ? gt[ly * wc + lx * cs] : 0.0f;
             }
 #pragma unroll
@@ -1127,37 +1123,33 @@ __global__ __launch_bounds__(256) void k_reduce_feat_heavy(int64_t n, int ncam, 
 }
 
 // ------------------------------------------------------------- host wrappers
-template <typename FT, int KMAX, int GC, bool PERSIST>
+template <typename FT, int KMAX, int GC>
 static void feat_bwd_launch(const SurfelArgs& s, const Layout& L, const CamTable& ct, const Tuning& tu,
                             const ImageGradArgs& g, bool renorm, char* ws, hipStream_t st) {
   const size_t shm = (size_t)kWRow * L.k * sizeof(float);  // weights, then dots
-  const void* k = reinterpret_cast<const void*>(&k_feat_bwd_topk<FT, KMAX, GC, PERSIST>);
-  hipLaunchKernelGGL((k_feat_bwd_topk<FT, KMAX, GC, PERSIST>), dim3(tile_grid(L, tu.sched_bwd, k, shm)), dim3(256), shm, st,
+  hipLaunchKernelGGL((k_feat_bwd_topk<FT, KMAX, GC>), dim3(xcd_grid(L.tiles)), dim3(256), shm, st,
                      (const uint32_t*)(ws + L.pid), (const uint32_t*)(ws + L.eid0), (const uint2*)(ws + L.ranges),
                      (const int32_t*)(ws + L.selpos), (const float*)(ws + L.selw), feat_src<FT>(s), g.feat, s.c, L.k,
-                     ct, tile_queue(L, tu.sched_bwd, ws, kQFeatBwd), (float*)(ws + L.seldot), (float*)(ws + L.fpart),
+                     ct, tile_order(L, tu.sched_bwd, ws), (float*)(ws + L.seldot), (float*)(ws + L.fpart),
                      (uint8_t*)(ws + L.fflag), renorm ? 1 : 0);
 }
 
 template <typename FT, int GC>
 static void feat_bwd_k(const SurfelArgs& s, const Layout& L, const CamTable& ct, const Tuning& tu,
                        const ImageGradArgs& g, bool rn, char* ws, hipStream_t st) {
-  const bool p = tu.sched_bwd == kSchedPersistent;
-  if (L.k <= 8) (p ? feat_bwd_launch<FT, 8, GC, true> : feat_bwd_launch<FT, 8, GC, false>)(s, L, ct, tu, g, rn, ws, st);
-  else if (L.k <= 16)
-    (p ? feat_bwd_launch<FT, 16, GC, true> : feat_bwd_launch<FT, 16, GC, false>)(s, L, ct, tu, g, rn, ws, st);
-  else (p ? feat_bwd_launch<FT, 32, GC, true> : feat_bwd_launch<FT, 32, GC, false>)(s, L, ct, tu, g, rn, ws, st);
+  if (L.k <= 8) feat_bwd_launch<FT, 8, GC>(s, L, ct, tu, g, rn, ws, st);
+  else if (L.k <= 16) feat_bwd_launch<FT, 16, GC>(s, L, ct, tu, g, rn, ws, st);
+  else feat_bwd_launch<FT, 32, GC>(s, L, ct, tu, g, rn, ws, st);
 }
 
-template <int MODE, typename FT, bool PERSIST, bool LP, bool DM>
+template <int MODE, typename FT, bool LP, bool DM>
 static void walk_bwd_launch_d(const SurfelArgs& s, const Layout& L, const CamTable& ct, const Tuning& tu,
                               const ImageGradArgs& g, bool want_f, char* ws, hipStream_t st) {
-  const void* k = reinterpret_cast<const void*>(&k_walk_bwd<MODE, FT, PERSIST, LP, DM>);
   const size_t shm = MODE == kTopK ? (size_t)L.k * kTilePix * 4 : 0;  // selection positions
-  hipLaunchKernelGGL((k_walk_bwd<MODE, FT, PERSIST, LP, DM>), dim3(tile_grid(L, tu.sched_bwd, k, shm)), dim3(256), shm,
-                     st, (const WalkRec*)(ws + L.rec), (const float4*)(ws + L.ext), (const uint32_t*)(ws + L.pid),
+  hipLaunchKernelGGL((k_walk_bwd<MODE, FT, LP, DM>), dim3(xcd_grid(L.tiles)), dim3(256), shm,
+                     st, (const WalkRec*)(ws + L.rec), (const CullRec*)(ws + L.ext), (const uint32_t*)(ws + L.pid),
                      (const uint32_t*)(ws + L.eid0), (const uint2*)(ws + L.ranges), ct,
-                     tile_queue(L, tu.sched_bwd, ws, kQWalkBwd), L.k,
+                     tile_order(L, tu.sched_bwd, ws), L.k,
                      (const uint32_t*)(ws + L.nlast), (const float*)(ws + L.tfinal), (const int32_t*)(ws + L.selpos),
                      (const float*)(ws + L.seldot), g.rgb, g.depth, g.normal, g.alpha, want_f ? g.feat : nullptr,
                      feat_src<FT>(s), s.c, (float*)(ws + L.gpart), (uint8_t*)(ws + L.gflag), (float*)(ws + L.fpart),
@@ -1166,23 +1158,17 @@ static void walk_bwd_launch_d(const SurfelArgs& s, const Layout& L, const CamTab
 
 // dense mode: the feature-backward pass width selects the contraction unit
 // (16: vector FMAs, 32: matrix cores)
-template <int MODE, typename FT, bool PERSIST, bool LP>
+template <int MODE, typename FT, bool LP>
 static void walk_bwd_launch_t(const SurfelArgs& s, const Layout& L, const CamTable& ct, const Tuning& tu,
                               const ImageGradArgs& g, bool want_f, char* ws, hipStream_t st) {
-  if (MODE == kFull && tu.bwd_pass == 32) walk_bwd_launch_d<MODE, FT, PERSIST, LP, true>(s, L, ct, tu, g, want_f, ws, st);
-  else walk_bwd_launch_d<MODE, FT, PERSIST, LP, false>(s, L, ct, tu, g, want_f, ws, st);
+  if (MODE == kFull && tu.bwd_pass == 32) walk_bwd_launch_d<MODE, FT, LP, true>(s, L, ct, tu, g, want_f, ws, st);
+  else walk_bwd_launch_d<MODE, FT, LP, false>(s, L, ct, tu, g, want_f, ws, st);
 }
 
 template <int MODE, typename FT>
 static void walk_bwd_launch(const SurfelArgs& s, const Layout& L, const CamTable& ct, const Tuning& tu,
                             const ImageGradArgs& g, bool want_f, bool lp, char* ws, hipStream_t st) {
-  const bool p = tu.sched_bwd == kSchedPersistent;
-  if (lp)
-    (p ? walk_bwd_launch_t<MODE, FT, true, true> : walk_bwd_launch_t<MODE, FT, false, true>)(s, L, ct, tu, g, want_f,
-                                                                                           ws, st);
-  else
-    (p ? walk_bwd_launch_t<MODE, FT, true, false> : walk_bwd_launch_t<MODE, FT, false, false>)(s, L, ct, tu, g,
-                                                                                             want_f, ws, st);
+  (lp ? walk_bwd_launch_t<MODE, FT, true> : walk_bwd_launch_t<MODE, FT, false>)(s, L, ct, tu, g, want_f, ws, st);
 }
 
 template <typename FT>
@@ -1245,7 +1231,6 @@ void launch_backward(const SurfelArgs& s, const CamTable& ct, int blend, const T
   prof.begin(kStageFill, st);
   launch_fill_u32(ws + L.gflag, 0u, cdiv(std::max<int64_t>(L.cap, 1), 4), st);
   launch_fill_u32(ws + L.fflag, 0u, cdiv(std::max<int64_t>(L.cap, 1), 4), st);
-  launch_fill_u32((uint32_t*)(ws + L.status) + kStQueue + kQFeatBwd, 0u, 2, st);
   prof.end(kStageFill, st);
   if (s.dtype == kF32) backward_typed<float>(s, ct, blend, tu, L, g, grads, renorm, lowpass, ws, st, prof);
   else if (s.dtype == kF16) backward_typed<__half>(s, ct, blend, tu, L, g, grads, renorm, lowpass, ws, st, prof);

@@ -1,12 +1,12 @@
 // Forward compositing (Sec. 3.1 eq. (1); Sec. 5 eq. (18)).
 //
-// k_walk: one 16x16 tile per 256-thread block (4 wave64), one pixel per lane.
-//   Surfel records of the tile's depth-sorted list are staged in LDS in
-//   batches of 256 and read by broadcast.  Each lane walks front to back:
-//   ray/surfel intersection, alpha, transmittance, dense RGB/depth/normal/
-//   alpha blend, stop before T would fall below 1e-4, and (Top-K mode) a
-//   per-pixel register heap of the K largest weights with their list
-//   positions.  A block stops when all of its pixels are done.
+// k_walk: one tile per 256-thread block (4 wave64), one pixel per lane, each
+//   wave on its own over the entries of the tile's depth-sorted list that meet
+//   its sub-tile, their records read through the scalar cache.  Each lane
+//   walks front to back: ray/surfel intersection, alpha, transmittance, dense
+//   RGB/depth/normal/alpha blend, stop before T would fall below 1e-4, and
+//   (Top-K mode) a sorted register list of the K largest weights with their
+//   positions.  A wave stops when all of its pixels are done.
 // k_blend_topk: eq. (18) blend of the selected feature rows, thread per pixel.
 //   The tile's distinct selected rows are staged in LDS per pass of 16 or 32
 //   channels and read by slot; each pixel accumulates in ascending list
@@ -18,8 +18,6 @@
 #include "select.h"
 
 namespace psm {
-
-constexpr int kWalkBatch = 256;
 
 template <int N>
 __device__ __forceinline__ void sort_by_position(int (&p)[N], float (&w)[N]) {
@@ -47,126 +45,120 @@ __device__ __forceinline__ void sort_by_position(int (&p)[N], float (&w)[N]) {
 
 constexpr int kWalkChunk = 64;  // list entries a wave examines at once
 
-// Each wave walks its 64 pixels (a 16x4 band of the tile) on its own, with no
-// block barriers: per chunk of 64 list entries every lane tests one entry's
-// footprint against the band (one vector gather of the extent records and a
-// ballot), the kept entries' records are staged, compacted, in the wave's LDS
-// slice by parallel vector loads, and the wave then evaluates them in list
-// order with broadcast reads.
-// KFULL: K == KMAX, known at compile time, so no per-entry "q < K" masks are
-// held across the tile loop (they cost the persistent form 60 registers).
-template <int KMAX, bool TOPK, bool PERSIST, bool LP, bool KFULL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_walk(const WalkRec* __restrict__ rec, const float4* __restrict__ ext,
+// Each wave walks its sub-tile's 64 pixels on its own, with no block
+// barriers and no LDS: per chunk of 64 list entries every lane tests one
+// entry's culling record against the sub-tile (a ballot gives the kept
+// entries, the next chunk's records are loaded meanwhile), and the wave then
+// evaluates the kept entries in list order, each record read through the
+// scalar cache one entry ahead of its use.
+// Top-K: the KMAX largest weights, sorted descending, so an insertion is a
+// median and two selects per held entry with no chain between the entries
+// (64 vector instructions for K = 16; a heap of 64-bit keys with a search for
+// the new minimum took 123, in sequence).
+template <int KMAX, bool TOPK, bool LP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_walk(const WalkRec* __restrict__ rec, const CullRec* __restrict__ ext,
                                               const uint32_t* __restrict__ pid,
-                                              const uint2* __restrict__ ranges, CamTable ct, TileQueue tq,
-                                              int K_, float* __restrict__ o_rgb, float* __restrict__ o_depth,
+                                              const uint2* __restrict__ ranges, CamTable ct, TileOrder tq,
+                                              int K, float* __restrict__ o_rgb, float* __restrict__ o_depth,
                                               float* __restrict__ o_normal, float* __restrict__ o_alpha,
                                               uint32_t* __restrict__ nlast, float* __restrict__ tfinal,
                                               int32_t* __restrict__ selpos, float* __restrict__ selw,
-                                              uint32_t* __restrict__ status, int feat_only) {
-  const int K = KFULL ? KMAX : K_;
-  __shared__ Staged<kWalkChunk> s_rec[4];
-  __shared__ int s_pos[4][kWalkChunk];
-  __shared__ int s_item;
-  for_tiles<PERSIST>(tq, &s_item, [&](const int tile) {
+                                              unsigned long long* __restrict__ stat, int slots, int feat_only) {
+  with_tile(tq, [&](const int tile) {
   const TileLoc tl = locate(ct, tile);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int tx = tl.tx, ty = tl.ty, W = tl.W, H = tl.H;
-  const int qx = tile_lx(ct, tid), qy = tile_ly(ct, tid), rpw = 64 >> ct.tsh;  // rows per wave
-  const int px = tx * ct.tw + qx, py = ty * ct.th + qy;
+  const int px = tx * ct.tw + tile_lx(ct, tid), py = ty * ct.th + tile_ly(ct, tid);
   const bool inside = px < W && py < H;
-  const float lx = (float)qx + 0.5f, ly = (float)qy + 0.5f;
-  const float tx0 = (float)(tx * ct.tw), ty0 = (float)(ty * ct.th);
-  const float yb0 = ty0 + (float)(rpw * wave) + 0.5f, yb1 = yb0 + (float)(rpw - 1);  // this wave's rows
+  const double Y = (double)py + 0.5;
+  double X = inside ? (double)px + 0.5 : __builtin_nan("");  // NaN: the pixel has stopped
+  const SubRect sr = sub_rect(ct, tl, __builtin_amdgcn_readfirstlane(tid >> 6));
   const uint2 rg = ranges[tile];
-  const int L = (int)(rg.y - rg.x);
+  const int L = __builtin_amdgcn_readfirstlane((int)(rg.y - rg.x));
   const uint32_t* ids = pid + rg.x;
-  Staged<kWalkChunk>& S = s_rec[wave];
-  int* spos = s_pos[wave];
 
   float T = 1.0f, cr = 0.f, cg = 0.f, cb = 0.f, dep = 0.f, nx = 0.f, ny = 0.f, nz = 0.f;
   int last = 0, blended = 0, stop = -1;
-  bool done = !inside;
-  // Top-K heap: one 64-bit key per entry, weight bits above the complemented
-  // list position.  Weights are positive, so unsigned key order is the order
-  // (weight, then earlier position) of eq. (18); an empty entry is key 0 and
-  // entries beyond K can never be the minimum.
-  uint64_t hk[KMAX];
+  // held weights, largest first, and their list positions; an empty entry has
+  // weight 0.  Weights are positive and a later position loses ties, so an
+  // entry goes in behind every weight that is at least its own: the order
+  // (weight, then earlier position) of eq. (18).  With K < KMAX the first
+  // KMAX - K entries are held by infinite weights, so the last one is always
+  // the smallest of the K.
+  float hw[KMAX];
+  int hp[KMAX];
 #pragma unroll
-  for (int q = 0; q < KMAX; ++q) hk[q] = q < K ? 0ull : ~0ull;
-  uint64_t kmin = 0ull;
-  int imin = 0;
+  for (int q = 0; q < KMAX; ++q) {
+    hw[q] = q < KMAX - K ? INFINITY : 0.0f;
+    hp[q] = -1;
+  }
 
+  // the chunk's ids and culling records; ids are read two chunks ahead,
+  // records one
+  const auto id_at = [&](int j) { return j < L ? ids[j] : 0u; };
+  uint32_t id = id_at(lane), nid = id_at(kWalkChunk + lane);
+  CullRec c = ext[id];
   for (int base = 0; base < L; base += kWalkChunk) {
-    if (__all(done)) break;
-    const int j = base + lane;
-    uint32_t id = 0;
-    bool keep = false;
-    if (j < L) {
-      id = ids[j];
-      const float4 x = ext[id];
-      keep = band_meets(x.y, x.w, yb0, yb1);
-    }
-    const uint64_t mask = __ballot(keep);
-    const int nk = __popcll(mask);
-    wave_lds_sync();  // the previous chunk's reads are done
-    if (keep) {
-      const int slot = __popcll(mask & ((1ull << lane) - 1ull));
-      S.put(slot, rec[id], tx0, ty0);
-      spos[slot] = j;
-    }
-    wave_lds_sync();
-    for (int k = 0; k < nk; ++k) {
-      if (__all(done)) break;
-      if (done) continue;
-      const int pos = spos[k];
-      const LRec s = S.get(k);
-      PixEval e;
-      if (!eval_pixel<LP>(s, lx, ly, e)) continue;
-      const float Tn = T * (1.0f - e.alpha);
-      if (Tn < kTMin) {
-        done = true;
-        stop = pos;
-        continue;
+    uint64_t mask = __ballot(base + lane < L && rect_meets<LP>(c, sr.x0, sr.x1, sr.y0, sr.y1));
+    const uint32_t cid = id;
+    id = nid;
+    nid = id_at(base + 2 * kWalkChunk + lane);
+    c = ext[id];
+    if (mask == 0) continue;
+    int k = __builtin_ctzll(mask);
+    SRec next = load_rec(rec, lane_value(cid, k));
+    do {
+      const int pos = base + k;
+      const LRec s = next.get();
+      mask &= mask - 1;
+      if (mask) {
+        k = __builtin_ctzll(mask);
+        next = load_rec(rec, lane_value(cid, k));
       }
-      const float w = e.alpha * T;
-      cr = fmaf(w, s.r, cr);
-      cg = fmaf(w, s.g, cg);
-      cb = fmaf(w, s.b, cb);
-      dep = fmaf(w, s.mz * e.iw, dep);
-      nx = fmaf(w, s.n0, nx);
-      ny = fmaf(w, s.n1, ny);
-      nz = fmaf(w, s.n2, nz);
-      T = Tn;
-      ++blended;
-      last = pos + 1;
-      if (TOPK) {
-        // a later position loses ties, so the new entry enters iff its key
-        // exceeds the minimum key; it replaces the minimum, then the new
-        // minimum is found (branch-free selects)
-        const uint64_t key = ((uint64_t)__float_as_uint(w) << 32) | (uint32_t)~(uint32_t)pos;
-        if (key > kmin) {
+      PixEval e;
+      bool stops = false;
+      if (eval_pixel<LP>(s, X, Y, e)) {
+        const float Tn = T * (1.0f - e.alpha);
+        const float w = e.alpha * T;
+        stops = Tn < kTMin;
+        if (!stops) {
+          cr = fmaf(w, s.r, cr);
+          cg = fmaf(w, s.g, cg);
+          cb = fmaf(w, s.b, cb);
+          dep = fmaf(w, s.mz * e.iw, dep);
+          nx = fmaf(w, s.n0, nx);
+          ny = fmaf(w, s.n1, ny);
+          nz = fmaf(w, s.n2, nz);
+          T = Tn;
+          ++blended;
+          last = pos + 1;
+          if (TOPK) {
+            if (w > hw[KMAX - 1]) {
+              // from the smallest up: every entry below the new weight moves down one
 #pragma unroll
-          for (int q = 0; q < KMAX; ++q) hk[q] = q == imin ? key : hk[q];
-          kmin = hk[0];
-          imin = 0;
-#pragma unroll
-          for (int q = 1; q < KMAX; ++q) {
-            const bool lt = hk[q] < kmin;
-            kmin = lt ? hk[q] : kmin;
-            imin = lt ? q : imin;
+              for (int q = KMAX - 1; q > 0; --q) {
+                const bool above = w > hw[q], over = w > hw[q - 1];
+                hp[q] = over ? hp[q - 1] : (above ? pos : hp[q]);
+                hw[q] = __builtin_amdgcn_fmed3f(w, hw[q], hw[q - 1]);
+              }
+              hp[0] = w > hw[0] ? pos : hp[0];
+              hw[0] = fmaxf(w, hw[0]);
+            }
+            // feature-only rendering: with K weights held, a later weight is
+            // alpha T' <= fl(0.99 T) (alpha <= 0.99, T' <= T, rounding is
+            // monotone) and loses a tie, so once fl(0.99 T) <= the smallest
+            // held weight the selection is final and the pixel stops
+            stops = feat_only && hw[KMAX - 1] > 0.0f && kAlphaMax * T <= hw[KMAX - 1];
           }
         }
-        // feature-only rendering: with K weights held, a later weight is
-        // alpha T' <= fl(0.99 T) (alpha <= 0.99, T' <= T, rounding is
-        // monotone) and loses a tie, so once fl(0.99 T) <= the smallest held
-        // weight the selection is final and the pixel stops
-        if (feat_only && kmin != 0ull && kAlphaMax * T <= __uint_as_float((uint32_t)(kmin >> 32))) {
-          done = true;
+        if (stops) {
+          X = __builtin_nan("");
           stop = pos;
         }
       }
-    }
+      if (__any(stops) && __all(X != X)) break;
+    } while (mask);
+    if (__all(X != X)) break;
   }
   // list entries this pixel walked: up to and including its stop, or all
   const int walked = !inside ? 0 : (stop >= 0 ? stop + 1 : L);
@@ -182,10 +174,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       bsum += __shfl_xor(bsum, o, 64);
       lsum += __shfl_xor(lsum, o, 64);
     }
-    if ((tid & 63) == 0) {
-      atomicAdd(reinterpret_cast<unsigned long long*>(status + kStWalked), (unsigned long long)wsum);
-      atomicAdd(reinterpret_cast<unsigned long long*>(status + kStBlended), (unsigned long long)bsum);
-      atomicAdd(reinterpret_cast<unsigned long long*>(status + kStBwdEntries), (unsigned long long)lsum);
+    if (lane == 0 && L > 0) {
+      unsigned long long* line = stat + (size_t)((tile * 4 + (tid >> 6)) & (slots - 1)) * kStatLine;
+      atomicAdd(line, (unsigned long long)wsum);
+      atomicAdd(line + 1, (unsigned long long)bsum);
+      atomicAdd(line + 2, (unsigned long long)lsum);
     }
   }
   if (inside) {
@@ -204,14 +197,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     if (o_alpha) o_alpha[pix] = 1.0f - T;
   }
   if (TOPK) {
-    float hw[KMAX];
-    int hp[KMAX];
 #pragma unroll
-    for (int q = 0; q < KMAX; ++q) {
-      const bool used = q < K && hk[q] != 0ull;
-      hw[q] = __uint_as_float((uint32_t)(hk[q] >> 32));
-      hp[q] = used ? (int)~(uint32_t)hk[q] : 0x7FFFFFFF;
-    }
+    for (int q = 0; q < KMAX; ++q) hp[q] = hw[q] > 0.0f && hw[q] < INFINITY ? hp[q] : 0x7FFFFFFF;
     sort_by_position<KMAX>(hp, hw);
 #pragma unroll
     for (int q = 0; q < KMAX; ++q) {
@@ -270,17 +257,16 @@ __device__ __forceinline__ void blend_chunk(const float* s_F, const int (&sl)[KM
 //   WIDE = true: the listed tiles, window by window and chunk by chunk.
 // Both take a pixel's selections in ascending list position, so a tile's
 // result does not depend on the pass that blends it.
-template <typename FT, int KMAX, int BC, bool PERSIST, bool WIDE>
+template <typename FT, int KMAX, int BC, bool WIDE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE || KMAX > 16 ? 1 : 4))) void k_blend_topk(const uint32_t* __restrict__ pid, const uint2* __restrict__ ranges,
                                                     const int32_t* __restrict__ selpos,
                                                     const float* __restrict__ selw, const FeatSrc<FT> feat,
-                                                    int C, int K, CamTable ct, TileQueue tq,
+                                                    int C, int K, CamTable ct, TileOrder tq,
                                                     float* __restrict__ o_feat, int renorm,
                                                     uint32_t* __restrict__ wide, uint32_t* __restrict__ status) {
   __shared__ SelShared S;
   constexpr int kBRow = BC + 4;
   __shared__ __align__(16) float s_F[kSlotChunk * kBRow];
-  __shared__ int s_item;
   auto body = [&](const int tile) {
   const TileLoc tl = locate(ct, tile);
   const int tid = threadIdx.x;
@@ -423,30 +409,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE || KMA
       body((int)wide[i]);
     }
   } else {
-    for_tiles<PERSIST>(tq, &s_item, body);
+    with_tile(tq, body);
   }
 }
 
 constexpr int kFullBatch = 64;
 
-template <typename FT, int CH, bool PERSIST, bool LP>
+template <typename FT, int CH, bool LP>
 __global__ __launch_bounds__(256) void k_full_feat(const WalkRec* __restrict__ rec, const uint32_t* __restrict__ pid,
                                                    const uint2* __restrict__ ranges, const FeatSrc<FT> feat,
-                                                   int C, CamTable ct, TileQueue tq,
+                                                   int C, CamTable ct, TileOrder tq,
                                                    const uint32_t* __restrict__ nlast, float* __restrict__ o_feat) {
   __shared__ Staged<kFullBatch> s_r;
   __shared__ float s_f[kFullBatch][CH];
   __shared__ uint32_t s_id[kFullBatch];
   __shared__ int s_lmax;
-  __shared__ int s_item;
-  for_tiles<PERSIST>(tq, &s_item, [&](const int tile) {
+  with_tile(tq, [&](const int tile) {
   const TileLoc tl = locate(ct, tile);
   const int tid = threadIdx.x;
   const int tx = tl.tx, ty = tl.ty;
   const int qx = tile_lx(ct, tid), qy = tile_ly(ct, tid);
   const int px = tx * ct.tw + qx, py = ty * ct.th + qy;
   const bool inside = px < tl.W && py < tl.H;
-  const float lx = (float)qx + 0.5f, ly = (float)qy + 0.5f;
+  const double X = (double)px + 0.5, Y = (double)py + 0.5;
   const uint32_t start = ranges[tile].x;
   const int my_last = (int)nlast[tile * kTilePix + tid];
   __syncthreads();
@@ -466,7 +451,7 @@ __global__ __launch_bounds__(256) void k_full_feat(const WalkRec* __restrict__ r
       if (tid < nb) {
         const uint32_t id = pid[start + base + tid];
         s_id[tid] = (uint32_t)(id - tl.v0);
-        s_r.put(tid, rec[id], (float)(tx * ct.tw), (float)(ty * ct.th));
+        s_r.put(tid, rec[id]);
       }
       __syncthreads();
       for (int e = tid; e < nb * CH; e += 256) {
@@ -482,7 +467,7 @@ __global__ __launch_bounds__(256) void k_full_feat(const WalkRec* __restrict__ r
         if (base + k >= my_last) break;
         const LRec s = s_r.get(k);
         PixEval ev;
-        if (!eval_pixel<LP>(s, lx, ly, ev)) continue;
+        if (!eval_pixel<LP>(s, X, Y, ev)) continue;
         const float w = ev.alpha * T;
 #pragma unroll
         for (int c = 0; c < CH; ++c) acc[c] = fmaf(w, s_f[k][c], acc[c]);
@@ -575,41 +560,42 @@ __global__ __launch_bounds__(256) void k_count_bits(const uint32_t* __restrict__
     atomicAdd(reinterpret_cast<unsigned long long*>(status + kStUnique), (unsigned long long)cnt);
 }
 
-// ------------------------------------------------------------- host wrappers
-template <int KMAX, bool TOPK, bool PERSIST, bool LP, bool KFULL>
-static void walk_launch_k(const Layout& L, const CamTable& ct, const Tuning& tu, const ImageArgs& out,
-                          bool feat_only, char* ws, hipStream_t st) {
-  const void* k = reinterpret_cast<const void*>(&k_walk<KMAX, TOPK, PERSIST, LP, KFULL>);
-  hipLaunchKernelGGL((k_walk<KMAX, TOPK, PERSIST, LP, KFULL>), dim3(tile_grid(L, tu.sched, k, 0)), dim3(256), 0, st,
-                     (const WalkRec*)(ws + L.rec), (const float4*)(ws + L.ext), (const uint32_t*)(ws + L.pid),
-                     (const uint2*)(ws + L.ranges), ct, tile_queue(L, tu.sched, ws, kQWalk), L.k, out.rgb, out.depth,
-                     out.normal, out.alpha,
-                     (uint32_t*)(ws + L.nlast), (float*)(ws + L.tfinal), (int32_t*)(ws + L.selpos),
-                     (float*)(ws + L.selw), (uint32_t*)(ws + L.status), feat_only ? 1 : 0);
+// Walk counters: the lines' sums into the status words (stats read-back).
+__global__ __launch_bounds__(256) void k_sum_stats(const uint64_t* __restrict__ stat, int slots,
+                                                   uint32_t* __restrict__ status) {
+  __shared__ uint64_t s[256];
+  for (int i = 0; i < 3; ++i) {
+    s[threadIdx.x] = (int)threadIdx.x < slots ? stat[threadIdx.x * kStatLine + i] : 0ull;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+      if ((int)threadIdx.x < o) s[threadIdx.x] += s[threadIdx.x + o];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+      const int w = i == 0 ? kStWalked : (i == 1 ? kStBlended : kStBwdEntries);
+      status[w] = (uint32_t)s[0];
+      status[w + 1] = (uint32_t)(s[0] >> 32);
+    }
+    __syncthreads();
+  }
 }
 
-template <int KMAX, bool TOPK, bool PERSIST, bool LP>
+// ------------------------------------------------------------- host wrappers
+template <int KMAX, bool TOPK, bool LP>
 static void walk_launch_t(const Layout& L, const CamTable& ct, const Tuning& tu, const ImageArgs& out,
                           bool feat_only, char* ws, hipStream_t st) {
-  if constexpr (TOPK) {
-    if (L.k == KMAX) {
-      walk_launch_k<KMAX, TOPK, PERSIST, LP, true>(L, ct, tu, out, feat_only, ws, st);
-      return;
-    }
-  }
-  walk_launch_k<KMAX, TOPK, PERSIST, LP, false>(L, ct, tu, out, feat_only, ws, st);
+  hipLaunchKernelGGL((k_walk<KMAX, TOPK, LP>), dim3(xcd_grid(L.tiles)), dim3(256), 0, st,
+                     (const WalkRec*)(ws + L.rec), (const CullRec*)(ws + L.ext), (const uint32_t*)(ws + L.pid),
+                     (const uint2*)(ws + L.ranges), ct, tile_order(L, tu.sched, ws), L.k, out.rgb, out.depth,
+                     out.normal, out.alpha,
+                     (uint32_t*)(ws + L.nlast), (float*)(ws + L.tfinal), (int32_t*)(ws + L.selpos),
+                     (float*)(ws + L.selw), (unsigned long long*)(ws + L.hist), stat_slots(L), feat_only ? 1 : 0);
 }
 
 template <int KMAX, bool TOPK>
 static void walk_launch(const Layout& L, const CamTable& ct, const Tuning& tu, const ImageArgs& out, bool feat_only,
                         bool lp, char* ws, hipStream_t st) {
-  const bool p = tu.sched == kSchedPersistent;
-  if (lp)
-    (p ? walk_launch_t<KMAX, TOPK, true, true> : walk_launch_t<KMAX, TOPK, false, true>)(L, ct, tu, out, feat_only, ws,
-                                                                                       st);
-  else
-    (p ? walk_launch_t<KMAX, TOPK, true, false> : walk_launch_t<KMAX, TOPK, false, false>)(L, ct, tu, out, feat_only,
-                                                                                         ws, st);
+  (lp ? walk_launch_t<KMAX, TOPK, true> : walk_launch_t<KMAX, TOPK, false>)(L, ct, tu, out, feat_only, ws, st);
 }
 
 void launch_walk(const Layout& L, const CamTable& ct, int blend, const Tuning& tu, const ImageArgs& out,
@@ -626,59 +612,51 @@ void launch_walk(const Layout& L, const CamTable& ct, int blend, const Tuning& t
   }
 }
 
-template <typename FT, int KMAX, int BC, bool PERSIST>
+template <typename FT, int KMAX, int BC>
 static void blend_topk_launch(const SurfelArgs& s, const Layout& L, const CamTable& ct, const Tuning& tu,
                               float* out_feat, bool renorm, char* ws, hipStream_t st) {
   uint32_t* status = (uint32_t*)(ws + L.status);
   uint32_t* wide = (uint32_t*)(ws + L.wide);
-  launch_fill_u32(status + kStWide, 0u, 1, st);
-  const void* k = reinterpret_cast<const void*>(&k_blend_topk<FT, KMAX, BC, PERSIST, false>);
-  const int sched = PERSIST ? kSchedPersistent : kSchedGrid;
-  hipLaunchKernelGGL((k_blend_topk<FT, KMAX, BC, PERSIST, false>), dim3(tile_grid(L, sched, k, 0)), dim3(256), 0,
+  hipLaunchKernelGGL((k_blend_topk<FT, KMAX, BC, false>), dim3(xcd_grid(L.tiles)), dim3(256), 0,
                      st, (const uint32_t*)(ws + L.pid), (const uint2*)(ws + L.ranges), (const int32_t*)(ws + L.selpos),
-                     (const float*)(ws + L.selw), feat_src<FT>(s), s.c, L.k, ct, tile_queue(L, sched, ws, kQBlend),
+                     (const float*)(ws + L.selw), feat_src<FT>(s), s.c, L.k, ct, TileOrder{nullptr, (int)L.tiles},
                      out_feat, renorm ? 1 : 0, wide, status);
   // the listed tiles (usually none): a fixed grid strides over the list,
   // whose length it reads on the device
   const unsigned gw = (unsigned)std::min<int64_t>(L.tiles, 1024);
-  hipLaunchKernelGGL((k_blend_topk<FT, KMAX, BC, false, true>), dim3(gw), dim3(256), 0, st,
+  hipLaunchKernelGGL((k_blend_topk<FT, KMAX, BC, true>), dim3(gw), dim3(256), 0, st,
                      (const uint32_t*)(ws + L.pid), (const uint2*)(ws + L.ranges), (const int32_t*)(ws + L.selpos),
-                     (const float*)(ws + L.selw), feat_src<FT>(s), s.c, L.k, ct, TileQueue{nullptr, nullptr, 0},
+                     (const float*)(ws + L.selw), feat_src<FT>(s), s.c, L.k, ct, TileOrder{nullptr, 0},
                      out_feat, renorm ? 1 : 0, wide, status);
 }
 
 template <typename FT, int BC>
 static void blend_topk_k(const SurfelArgs& s, const Layout& L, const CamTable& ct, const Tuning& tu, float* out_feat,
                          bool rn, char* ws, hipStream_t st) {
-  // always grid-scheduled: with the long tiles moved to the windowed pass the
-  // common pass's tiles cost about the same, and the grid form keeps fewer
-  // registers live across tiles (more waves per SIMD)
-  if (L.k <= 8) blend_topk_launch<FT, 8, BC, false>(s, L, ct, tu, out_feat, rn, ws, st);
-  else if (L.k <= 16) blend_topk_launch<FT, 16, BC, false>(s, L, ct, tu, out_feat, rn, ws, st);
-  else blend_topk_launch<FT, 32, BC, false>(s, L, ct, tu, out_feat, rn, ws, st);
+  // never longest-first: with the long tiles moved to the windowed pass the
+  // common pass's tiles cost about the same, and neighbouring tiles share rows
+  if (L.k <= 8) blend_topk_launch<FT, 8, BC>(s, L, ct, tu, out_feat, rn, ws, st);
+  else if (L.k <= 16) blend_topk_launch<FT, 16, BC>(s, L, ct, tu, out_feat, rn, ws, st);
+  else blend_topk_launch<FT, 32, BC>(s, L, ct, tu, out_feat, rn, ws, st);
 }
 
-template <typename FT, bool PERSIST, bool LP>
+template <typename FT, bool LP>
 static void full_feat_launch(const SurfelArgs& s, const Layout& L, const CamTable& ct, const Tuning& tu,
                              float* out_feat, char* ws, hipStream_t st) {
-  const void* k = reinterpret_cast<const void*>(&k_full_feat<FT, 64, PERSIST, LP>);
-  hipLaunchKernelGGL((k_full_feat<FT, 64, PERSIST, LP>), dim3(tile_grid(L, tu.sched, k, 0)), dim3(256), 0, st,
+  hipLaunchKernelGGL((k_full_feat<FT, 64, LP>), dim3(xcd_grid(L.tiles)), dim3(256), 0, st,
                      (const WalkRec*)(ws + L.rec), (const uint32_t*)(ws + L.pid), (const uint2*)(ws + L.ranges),
-                     feat_src<FT>(s), s.c, ct, tile_queue(L, tu.sched, ws, kQBlend), (const uint32_t*)(ws + L.nlast),
+                     feat_src<FT>(s), s.c, ct, tile_order(L, tu.sched, ws), (const uint32_t*)(ws + L.nlast),
                      out_feat);
 }
 
 template <typename FT>
 static void blend_launch(const SurfelArgs& s, const Layout& L, const CamTable& ct, int blend, const Tuning& tu,
                          float* out_feat, bool renorm, bool lp, char* ws, hipStream_t st) {
-  const bool p = tu.sched == kSchedPersistent;
   if (blend == kTopK) {
     if (tu.blend_pass == 16) blend_topk_k<FT, 16>(s, L, ct, tu, out_feat, renorm, ws, st);
     else blend_topk_k<FT, 32>(s, L, ct, tu, out_feat, renorm, ws, st);
-  } else if (lp) {
-    (p ? full_feat_launch<FT, true, true> : full_feat_launch<FT, false, true>)(s, L, ct, tu, out_feat, ws, st);
   } else {
-    (p ? full_feat_launch<FT, true, false> : full_feat_launch<FT, false, false>)(s, L, ct, tu, out_feat, ws, st);
+    (lp ? full_feat_launch<FT, true> : full_feat_launch<FT, false>)(s, L, ct, tu, out_feat, ws, st);
   }
 }
 
@@ -702,6 +680,11 @@ void launch_count_selected(const Layout& L, char* ws, hipStream_t st) {
   const int64_t blocks = std::min<int64_t>(1024, cdiv(words, 256));
   hipLaunchKernelGGL(k_count_bits, dim3((unsigned)blocks), dim3(256), 0, st, (const uint32_t*)(ws + L.ubits), words,
                      status);
+}
+
+void launch_sum_stats(const Layout& L, char* ws, hipStream_t st) {
+  hipLaunchKernelGGL(k_sum_stats, dim3(1), dim3(256), 0, st, (const uint64_t*)(ws + L.hist), stat_slots(L),
+                     (uint32_t*)(ws + L.status));
 }
 
 void launch_export_selection(const Layout& L, const CamTable& ct, char* ws, int32_t* sel_id, float* sel_w,
