@@ -329,8 +329,7 @@ void enqueue_forward(const SurfelArgs& sa, const CamTable& ct, const psm_config*
   uint32_t* status = (uint32_t*)(ws + L.status);
   uint32_t* hist = (uint32_t*)(ws + L.hist);
   prof.begin(kStageFill, st);
-  launch_init_status(status, L, st);
-  launch_fill_u32(ws + L.ranges, 0u, L.tiles * 2, st);
+  launch_init_forward(L, ws, st);
   prof.end(kStageFill, st);
   prof.begin(kStagePreprocess, st);
   const bool lp = (cfg->flags & PSM_FLAG_LOWPASS) != 0;
@@ -445,6 +444,7 @@ psm_status read_stats_impl(psm_ctx* ctx, const void* workspace, int64_t n, const
   if (r != PSM_OK) return r;
   const bool topk = cfg->blend == PSM_BLEND_TOPK;
   launch_sum_stats(L, (char*)workspace, st);
+  launch_count_culls(L, (char*)workspace, st);
   if (topk) launch_count_selected(L, (char*)workspace, st);
   r = check_hip("psm_read_stats counters");
   if (r != PSM_OK) return r;

@@ -42,8 +42,8 @@ enum : int {
   kStP = 0,        // pairs emitted (min(required, capacity))
   kStOverflow = 1, // 1 if required > capacity
   kStN = 2,        // number of virtual surfels
-  kStVisible = 3,
-  kStCull = 4,     // 4 .. 8: cull codes 0..4
+  kStVisible = 3,  // written by the stats read-back
+  kStCull = 4,     // 4 .. 8: cull codes 0..4, written by the stats read-back
   kStTiles = 9,    // number of tiles (length of the tile work order)
   kStReqLo = 10,   // required pairs, 64-bit
   kStReqHi = 11,

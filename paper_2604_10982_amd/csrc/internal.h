@@ -63,7 +63,9 @@ enum : int { kSchedGrid = 0, kSchedPersistent = 1 };
 
 // keystage.hip
 void launch_fill_u32(void* p, uint32_t v, int64_t count, hipStream_t st);
-void launch_init_status(uint32_t* status, const Layout& L, hipStream_t st);
+void launch_init_forward(const Layout& L, char* ws, hipStream_t st);
+// Counts the visible and culled virtual surfels into the status words.
+void launch_count_culls(const Layout& L, char* ws, hipStream_t st);
 void launch_preprocess(const SurfelArgs& s, const CamTable& ct, int mode, bool opacity_foot, bool lowpass,
                        const Layout& L,
                        char* ws, hipStream_t st);

@@ -289,8 +289,10 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t v, int64_t count) 
   for (int64_t j = i; j < count; j += stride) p[j] = v;
 }
 
-__global__ void k_init_status(uint32_t* __restrict__ st, uint32_t n, uint32_t tiles, uint64_t total, uint32_t cap) {
-  const int i = threadIdx.x;
+// Status words and empty tile ranges, before a forward.
+__global__ __launch_bounds__(256) void k_init_forward(uint32_t* __restrict__ st, uint32_t n, uint32_t tiles,
+                                                      uint64_t total, uint32_t cap, uint2* __restrict__ ranges) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
   uint32_t v = 0u;
   v = i == kStN ? n : v;
   v = i == kStTiles ? tiles : v;
@@ -299,6 +301,7 @@ __global__ void k_init_status(uint32_t* __restrict__ st, uint32_t n, uint32_t ti
   v = i == kStSigCap ? cap : v;
   v = i == kStSigTiles ? tiles : v;
   if (i < kStWords) st[i] = v;
+  if (i < tiles) ranges[i] = make_uint2(0u, 0u);
 }
 
 // Thread per virtual surfel v = b * N + i (surfel i seen by camera b).
@@ -308,10 +311,8 @@ __global__ __launch_bounds__(256) void k_preprocess(
     CamTable ct, int mode, int opacity_foot, int lowpass, WalkRec* __restrict__ rec, float4* __restrict__ fp,
     CullRec* __restrict__ ext,
     uint32_t* __restrict__ key, uint32_t* __restrict__ ids, uint32_t* __restrict__ count,
-    int32_t* __restrict__ cull, uint32_t* __restrict__ status) {
-  __shared__ uint32_t s_cnt[5];
+    int32_t* __restrict__ cull) {
   __shared__ Cam s_cam[kMaxCams];  // cameras by constant index (no private copy of the table)
-  if (threadIdx.x < 5) s_cnt[threadIdx.x] = 0;
 #pragma unroll
   for (int b = 0; b < kMaxCams; ++b)
     if (threadIdx.x == b && b < ct.n) s_cam[b] = ct.cam[b];
@@ -326,7 +327,6 @@ __global__ __launch_bounds__(256) void k_preprocess(
                              fminf(foot2, cull_foot2(opacity[i])), mode, lowpass);
     ids[v] = (uint32_t)v;
     cull[v] = kk.cull | (kk.flip << 8);  // bit 8: normal flipped toward the camera
-    atomicAdd(&s_cnt[kk.cull], 1u);
     if (kk.cull != 0) {
       key[v] = 0xFFFFFFFFu;
       count[v] = 0;
@@ -343,6 +343,18 @@ __global__ __launch_bounds__(256) void k_preprocess(
                   rec + v);
     }
   }
+}
+
+// Cull codes of all virtual surfels into the status words (stats read-back):
+// counting them in k_preprocess cost it 9 ns per block and code on one shared
+// line, 113 of its us for 1M surfels against the rest of its work.
+__global__ __launch_bounds__(256) void k_count_culls(int64_t nv, const int32_t* __restrict__ cull,
+                                                     uint32_t* __restrict__ status) {
+  __shared__ uint32_t s_cnt[5];
+  if (threadIdx.x < 5) s_cnt[threadIdx.x] = 0;
+  __syncthreads();
+  for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < nv; v += (int64_t)gridDim.x * 256)
+    atomicAdd(&s_cnt[min(cull[v] & 0xFF, 4)], 1u);
   __syncthreads();
   if (threadIdx.x < 5 && s_cnt[threadIdx.x]) atomicAdd(&status[kStCull + threadIdx.x], s_cnt[threadIdx.x]);
   if (threadIdx.x == 0 && s_cnt[0]) atomicAdd(&status[kStVisible], s_cnt[0]);
@@ -540,10 +552,10 @@ void launch_fill_u32(void* p, uint32_t v, int64_t count, hipStream_t st) {
   hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)blocks), dim3(256), 0, st, (uint32_t*)p, v, count);
 }
 
-void launch_init_status(uint32_t* status, const Layout& L, hipStream_t st) {
-  static_assert(kStWords <= 64, "status words are written by one wave");
-  hipLaunchKernelGGL(k_init_status, dim3(1), dim3(64), 0, st, status, (uint32_t)L.n, (uint32_t)L.tiles,
-                     (uint64_t)L.total, (uint32_t)L.cap);
+void launch_init_forward(const Layout& L, char* ws, hipStream_t st) {
+  const int64_t items = std::max<int64_t>(L.tiles, kStWords);
+  hipLaunchKernelGGL(k_init_forward, dim3((unsigned)cdiv(items, 256)), dim3(256), 0, st, (uint32_t*)(ws + L.status),
+                     (uint32_t)L.n, (uint32_t)L.tiles, (uint64_t)L.total, (uint32_t)L.cap, (uint2*)(ws + L.ranges));
 }
 
 void launch_preprocess(const SurfelArgs& s, const CamTable& ct, int mode, bool opacity_foot, bool lowpass,
@@ -554,7 +566,16 @@ void launch_preprocess(const SurfelArgs& s, const CamTable& ct, int mode, bool o
                      (float4*)(ws + L.fp),
                      (CullRec*)(ws + L.ext),
                      (uint32_t*)(ws + L.key0), (uint32_t*)(ws + L.id0), (uint32_t*)(ws + L.count),
-                     (int32_t*)(ws + L.cull), (uint32_t*)(ws + L.status));
+                     (int32_t*)(ws + L.cull));
+}
+
+void launch_count_culls(const Layout& L, char* ws, hipStream_t st) {
+  uint32_t* status = (uint32_t*)(ws + L.status);
+  static_assert(kStCull == kStVisible + 1, "the visible count and the cull codes are cleared together");
+  launch_fill_u32(status + kStVisible, 0u, 6, st);
+  if (L.n == 0) return;
+  hipLaunchKernelGGL(k_count_culls, dim3((unsigned)std::min<int64_t>(256, cdiv(L.n, 256))), dim3(256), 0, st, L.n,
+                     (const int32_t*)(ws + L.cull), status);
 }
 
 void launch_scan_counts(const Layout& L, char* ws, hipStream_t st) {
