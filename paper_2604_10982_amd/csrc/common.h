@@ -31,7 +31,6 @@ constexpr float kTMin = 1e-4f;
 constexpr int kTilePix = 256;
 constexpr int kTileDefault = 16;
 constexpr int kMaxK = 32;
-constexpr int kRecWords = 6;             // 16-byte words per surfel walk record
 
 enum : int { kSphere = 0, kAabb = 1, kEllipse = 2 };
 enum : int { kFull = 0, kTopK = 1 };
@@ -149,7 +148,7 @@ __host__ __device__ inline TileLoc locate(const CamTable& ct, int g) {
 struct Layout {
   int64_t n, nreal, cap, tiles, spix;  // n = virtual surfels; spix = tiles * 256 (tile-major pixels)
   int k, c, ncam;
-  size_t rec, fp, ext, key0, key1, id0, id1, vbase, count, offs, cull, ptile0, ptile1, eid0, eid1, sid_emit, pid, ranges,
+  size_t rec, fp, key0, key1, id0, id1, vbase, count, offs, cull, ptile0, ptile1, eid0, eid1, sid_emit, pid, ranges,
       torder0, wide, nlast, tfinal, selpos, selw, seldot, gflag, fflag, gpart, fpart, hist, bsum, ubits, heavy,
       status, total;
 };
@@ -168,9 +167,8 @@ inline Layout make_layout(const CamTable& ct, int k, int c, int64_t cap) {
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o = align256(o + bytes); return at; };
   L.status = take(kStWords * 4);  // first, so a read-back can check the layout before any other access
-  L.rec = take(n1 * 16 * kRecWords);  // walk record
+  L.rec = take(n1 * 128);         // walk record and the walks' culling record
   L.fp = take(n1 * 32);           // footprint of the tile lists, 8 floats
-  L.ext = take(n1 * 32);          // sub-tile culling record of the walks, 8 floats
   L.key0 = take(n1 * 4);          // depth keys (sort ping-pong)
   L.key1 = take(n1 * 4);
   L.id0 = take(n1 * 4);           // virtual surfel ids (sort ping-pong)
@@ -224,7 +222,23 @@ __host__ __device__ inline int stat_slots(const Layout& L) {
 }
 
 // ------------------------------------------------------------ walk record
-// Per surfel (global, 6 x 16 bytes), computed in FP64 from the FP32 inputs:
+// Sub-tile culling of the walks: a wave skips a surfel no pixel centre of its
+// sub-tile can blend.  Per surfel the key stage keeps the ellipse of
+// rho <= min(9, 2 ln(255 o)) (beyond it alpha < 1/255), widened like the
+// footprint, as centre (ecx, ecy), half-extents (ex, ey), the y offset of the
+// rightmost point yr, the slope of the chord midpoints and the half-chord
+// factor, so its x-extent over the rows [y0, y1] of the sub-tile is two
+// clamps and two square roots.  One lane tests one list entry, so a test
+// costs each pixel 1/64 of that.  The slack covers the FP32 rounding of the
+// record and the test (relative 2^-16 of the extents: a thin ellipse's chord is a
+// difference of terms of the size of its extents).  With the low-pass filter
+// the record is the box of the ellipse and the filter's disk.
+struct CullRec {
+  float4 e0;  // ecx, ecy, ex, ey
+  float4 e1;  // yr, slope, half-chord factor, slack (low-pass: xc, yc, rf2, slack)
+};
+
+// Walk record per surfel, computed in FP64 from the FP32 inputs:
 //   d0 = (Ai00, Ai01), d1 = (Ai10, Ai11)   FP64: inverse of A, the centred,
 //                                          depth-normalised homography [[A,0],[p q 1]]
 //   d2 = (e0, e1)                          FP64: e = (p, q) A^-1
@@ -238,11 +252,17 @@ __host__ __device__ inline int stat_slots(const Layout& L) {
 // rho at cond(A) ~ 100), far beyond the 1e-5 image tolerance; FP32 pixel
 // coordinates near 10^3 would also carry 6e-5 px of rounding.
 
-struct __align__(16) WalkRec {
+// It shares its 128-byte line with the culling record, which a wave reads a
+// chunk of entries ahead: the line is then in the XCD's L2 when the entry's
+// turn comes and its scalar load is one entry ahead.  (Apart, a record's first
+// read by an XCD came from beyond L2, some 2000 cycles, the walks' largest
+// wait.)
+struct __align__(128) WalkRec {
   double2 d0, d1, d2, d3;
   float4 f0, f1;
+  CullRec c;
 };
-static_assert(sizeof(WalkRec) == 16 * kRecWords, "walk record layout");
+static_assert(sizeof(WalkRec) == 128, "a record is a cache line");
 
 // The record as the per-pixel evaluation takes it.
 struct LRec {
@@ -358,22 +378,6 @@ __device__ __forceinline__ bool eval_pixel(const LRec& s, double x, double y, Pi
   return hit & (e.alpha >= kAlphaMin);
 }
 
-// Sub-tile culling of the walks: a wave skips a surfel no pixel centre of its
-// sub-tile can blend.  Per surfel the key stage keeps the ellipse of
-// rho <= min(9, 2 ln(255 o)) (beyond it alpha < 1/255), widened like the
-// footprint, as centre (ecx, ecy), half-extents (ex, ey), the y offset of the
-// rightmost point yr, the slope of the chord midpoints and the half-chord
-// factor, so its x-extent over the rows [y0, y1] of the sub-tile is two
-// clamps and two square roots.  One lane tests one list entry, so a test
-// costs each pixel 1/64 of that.  The slack covers the FP32 rounding of the
-// record and the test (relative 2^-16 of the extents: a thin ellipse's chord is a
-// difference of terms of the size of its extents).  With the low-pass filter
-// the record is the box of the ellipse and the filter's disk.
-struct CullRec {
-  float4 e0;  // ecx, ecy, ex, ey
-  float4 e1;  // yr, slope, half-chord factor, slack (low-pass: xc, yc, rf2, slack)
-};
-
 template <bool LP>
 __device__ __forceinline__ bool rect_meets(const CullRec& c, float x0, float x1, float y0, float y1) {
   const float sl = c.e1.w, ey = c.e0.w;
@@ -441,6 +445,7 @@ __device__ __forceinline__ float dpp_mov(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));
 }
 constexpr int kDppRowRor8 = 0x128;      // lane l <- lane l ^ 8 within a row
+constexpr int kDppRowRor4 = 0x124;      // lane l <- lane l - 4 within a row
 constexpr int kDppRowHalfMirror = 0x141;  // lane l <- lane 7 - l within 8 lanes
 constexpr int kDppXor2 = 0x4E;          // quad_perm [2,3,0,1]
 constexpr int kDppXor1 = 0xB1;          // quad_perm [1,0,3,2]

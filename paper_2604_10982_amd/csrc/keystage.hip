@@ -161,7 +161,8 @@ __device__ __forceinline__ Key key_stage(const float* mu, const float* sc, const
 // depth-normalised homography's A^-1, e = (p, q) A^-1 and the projected centre,
 // evaluated and kept in FP64 (the per-pixel solve is FP64 as well).
 __device__ __forceinline__ void walk_record(const float* mu_f, const float* sc, const float* qf, float o,
-                                         const float* rgb, const float* nc, const Cam& k, WalkRec* out) {
+                                         const float* rgb, const float* nc, const CullRec& cr, const Cam& k,
+                                         WalkRec* out) {
   const double q0 = qf[0], q1 = qf[1], q2 = qf[2], q3 = qf[3];
   const double rn = 1.0 / sqrt(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
   const double w = q0 * rn, x = q1 * rn, y = q2 * rn, z = q3 * rn;
@@ -189,6 +190,7 @@ __device__ __forceinline__ void walk_record(const float* mu_f, const float* sc, 
   r.d3 = make_double2(xc, yc);
   r.f0 = make_float4((float)mc[2], o, rgb[0], rgb[1]);
   r.f1 = make_float4(rgb[2], nc[0], nc[1], nc[2]);
+  r.c = cr;
   *out = r;
 }
 
@@ -309,7 +311,6 @@ __global__ __launch_bounds__(256) void k_preprocess(
     int64_t nv, const float* __restrict__ means, const float* __restrict__ scales,
     const float* __restrict__ quats, const float* __restrict__ opacity, const float* __restrict__ rgb,
     CamTable ct, int mode, int opacity_foot, int lowpass, WalkRec* __restrict__ rec, float4* __restrict__ fp,
-    CullRec* __restrict__ ext,
     uint32_t* __restrict__ key, uint32_t* __restrict__ ids, uint32_t* __restrict__ count,
     int32_t* __restrict__ cull) {
   __shared__ Cam s_cam[kMaxCams];  // cameras by constant index (no private copy of the table)
@@ -338,9 +339,8 @@ __global__ __launch_bounds__(256) void k_preprocess(
       count[v] = c;
       fp[2 * v] = make_float4(kk.f.ecx, kk.f.ecy, kk.f.ex, kk.f.ey);
       fp[2 * v + 1] = make_float4(kk.f.S01, kk.f.S11, kk.f.gam, kk.f.kk);
-      ext[v] = kk.cr;
-      walk_record(means + 3 * i, scales + 2 * i, quats + 4 * i, opacity[i], rgb + 3 * i, kk.nc, cam,
-                  rec + v);
+      walk_record(means + 3 * i, scales + 2 * i, quats + 4 * i, opacity[i], rgb + 3 * i, kk.nc, kk.cr,
+                  cam, rec + v);
     }
   }
 }
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(int64_t n, const uin
 __global__ __launch_bounds__(256) void k_emit(int64_t nv, const uint32_t* __restrict__ order,
                                               const uint32_t* __restrict__ count,
                                               const uint32_t* __restrict__ offs, const float4* __restrict__ fp,
-                                              const CullRec* __restrict__ ext, int lowpass, CamTable ct, int mode, int64_t cap, uint32_t* __restrict__ vbase,
+                                              const WalkRec* __restrict__ rec, int lowpass, CamTable ct, int mode, int64_t cap, uint32_t* __restrict__ vbase,
                                               uint32_t* __restrict__ ptile, uint32_t* __restrict__ eid,
                                               uint32_t* __restrict__ sid_emit) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -462,7 +462,7 @@ __global__ __launch_bounds__(256) void k_emit(int64_t nv, const uint32_t* __rest
   const int ntx = ct.ntx[b], t0 = ct.tile0[b];
   const float4 f0 = fp[2 * (size_t)v], f1 = fp[2 * (size_t)v + 1];
   float4 f2 = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (lowpass) f2 = ext[v].e1;
+  if (lowpass) f2 = rec[v].c.e1;
   const Foot f{f0.x, f0.y, f1.x, f1.y, f0.z, f0.w, f1.z, f1.w, f2.x, f2.y, f2.z};
   int64_t o = offs[r];
   for_each_row(f, mode, ct.cam[b].W, ct.cam[b].H, ct.tw, ct.th, ntx, ct.nty[b], [&](int ty, int x0, int x1) {
@@ -564,7 +564,6 @@ void launch_preprocess(const SurfelArgs& s, const CamTable& ct, int mode, bool o
   hipLaunchKernelGGL(k_preprocess, dim3((unsigned)cdiv(L.n, 256)), dim3(256), 0, st, L.n, s.means, s.scales,
                      s.quats, s.opacity, s.rgb, ct, mode, opacity_foot ? 1 : 0, lowpass ? 1 : 0, (WalkRec*)(ws + L.rec),
                      (float4*)(ws + L.fp),
-                     (CullRec*)(ws + L.ext),
                      (uint32_t*)(ws + L.key0), (uint32_t*)(ws + L.id0), (uint32_t*)(ws + L.count),
                      (int32_t*)(ws + L.cull));
 }
@@ -593,7 +592,7 @@ void launch_emit(const CamTable& ct, int mode, bool lowpass, const Layout& L, ch
   if (L.n == 0) return;
   hipLaunchKernelGGL(k_emit, dim3((unsigned)cdiv(L.n, 256)), dim3(256), 0, st, L.n,
                      (const uint32_t*)(ws + L.id0), (const uint32_t*)(ws + L.count),
-                     (const uint32_t*)(ws + L.offs), (const float4*)(ws + L.fp), (const CullRec*)(ws + L.ext), lowpass ? 1 : 0,
+                     (const uint32_t*)(ws + L.offs), (const float4*)(ws + L.fp), (const WalkRec*)(ws + L.rec), lowpass ? 1 : 0,
                      ct, mode, L.cap,
                      (uint32_t*)(ws + L.vbase), (uint32_t*)(ws + L.ptile0), (uint32_t*)(ws + L.eid0),
                      (uint32_t*)(ws + L.sid_emit));

@@ -14,8 +14,8 @@
 //   order.
 // k_walk_bwd: per tile, back to front from each pixel's last contributor,
 //   recovering T_i = T_{i+1} / (1 - alpha_i).  Per surfel the per-pixel terms
-//   are reduced over the wave, then over the 4 waves through LDS, and written
-//   as the pair's 16 partial sums.  In dense-blend mode each batch also forms
+//   are summed over the wave by small matrix products, then over the 4 waves
+//   through LDS, and written as the pair's 16 partial sums.  In dense-blend mode each batch also forms
 //   the feature dot products and feature-gradient rows tile-wide.
 // k_reduce_geo / k_reduce_feat: per surfel, sum of its pairs' partials, then
 //   the chain rule to mu, s, q (FP64, as the forward's walk record).
@@ -28,9 +28,6 @@
 namespace psm {
 
 constexpr int kBB = 32;          // surfels per backward batch
-// per-pixel values reduced per surfel: 17, and 2 more (the low-pass filter
-// term's centre gradient) with the filter
-constexpr int nv_of(bool lp) { return lp ? 19 : 17; }
 
 // ------------------------------------------------------------ Top-K feature
 // Per tile, the distinct selected surfels of the tile (a few dozen: each is
@@ -295,12 +292,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 16 
 }
 
 // ------------------------------------------------------------- walk backward
+// The per-surfel sums of a wave's sub-tile as small matrix products.  Every
+// term is one of a few per-pixel factors times a column of the pixel: w times
+// the upstream gradients (dC, dn_c), dL/du', dL/dv', dL/dw' times (1, dx, dy)
+// with (dx, dy) the pixel's offset from the surfel's centre, and two plain
+// sums.  The wave puts the factors of its contributing entries in its LDS
+// slice and multiplies them by the columns on v_mfma_f32_4x4x1 (16 blocks,
+// block b holding the pixels 4 b .. 4 b + 3, one per step); for four entries
+// together the 16 blocks are then added across lanes.  Rows of the first
+// product are an entry's four geometric factors (the offset columns are the
+// entry's own; formed every second entry, so that LDS holds two entries'),
+// rows of the others the four entries.  That is 28 matrix and 80 vector instructions for
+// four entries, where forming 17 products per pixel and reducing them over
+// the wave took 65 vector instructions per entry of the 142 the walk issued
+// (it is bound by their issue).  Offsets from a fixed point of the sub-tile
+// instead of the surfel's centre would save 7 more per entry, but the sums
+// about the centre then cancel: 5 times the error in the quaternions.
+constexpr int kGeoFac = 4;   // du', dv', dw', dop
+// Sums per entry and wave, at 4 r + j: row r = 0, 1, 2: (du', dv', dw') times
+// (1, dx, dy); column 3 of these rows: dn_1, dn_2, dz; row 3: dC, dn_0; then
+// dop (and, low-pass, the filter term's centre gradient).
+constexpr int kSums = 20;
+
+// Quad broadcast: every lane of a quad gets the quad's lane S.
+template <int S>
+__device__ __forceinline__ float quad_lane(float v) {
+  return dpp_mov<S | (S << 2) | (S << 4) | (S << 6)>(v);
+}
+
+// Column value of lane (block b = lane >> 2, column j = lane & 3) for the pixel of lane 4 b + S.
+template <int S>
+__device__ __forceinline__ float quad_col(int j, float c0, float c1, float c2, float c3) {
+  const float a = quad_lane<S>(c0), b = quad_lane<S>(c1), c = quad_lane<S>(c2), d = quad_lane<S>(c3);
+  return j == 0 ? a : (j == 1 ? b : (j == 2 ? c : d));
+}
+
+__device__ __forceinline__ f4v mfma_4x4x1(float a, float b, f4v c) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
+}
+
 // DM (dense mode only): the batch's feature contractions on the matrix cores
 // (true) or in vector FMAs (false); a launch choice, whichever is faster for
 // the workload (the autotuner times both).
 template <int MODE, typename FT, bool LP, bool DM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTopK ? 4 : 1))) void k_walk_bwd(
-    const WalkRec* __restrict__ rec, const CullRec* __restrict__ ext, const uint32_t* __restrict__ pid, const uint32_t* __restrict__ eid,
+    const WalkRec* __restrict__ rec, const uint32_t* __restrict__ pid, const uint32_t* __restrict__ eid,
     const uint2* __restrict__ ranges, CamTable ct, TileOrder tq, int K, const uint32_t* __restrict__ nlast,
     const float* __restrict__ tfinal,
     const int32_t* __restrict__ selpos, const float* __restrict__ seldot, const float* __restrict__ g_rgb,
@@ -312,30 +348,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
   // are gradients, which no decision depends on; the hit test, alpha and the
   // weights come from eval_pixel, written outside this scope and evaluated
   // exactly as in the forward)
-  __shared__ Staged<kBB> s_r;
-  __shared__ CullRec s_cull[kBB];  // culling records of the batch
-  __shared__ uint32_t s_id[kBB];
-  constexpr int kNV = nv_of(LP);
-  __shared__ float s_part[4][kBB][kNV];
-  __shared__ uint32_t s_has[4][kBB];
+  constexpr int NC = LP ? 4 : 2;  // w, dz (low-pass: and the filter term's centre gradient)
+  __shared__ __align__(16) float s_geo[4][2][kGeoFac][64];  // [wave][entry of the pair][factor][pixel]
+  __shared__ __align__(16) float s_col[4][NC][4][64];       // [wave][factor][entry of the group][pixel]
+  __shared__ float s_off[4][2][8];  // [wave][entry of the pair]: 0, centre x, y, 0, and what they lack to the FP64 centre
+  __shared__ __align__(16) float s_part[4][kBB][kSums];
+  __shared__ uint32_t s_has[4];
   __shared__ int s_lmax;
-  // dense-blend mode only: each wave's dots tile (16 pixels x the batch) and
-  // the batch weights (rows padded to 260 floats: the matrix-core operand
-  // reads of 16 entries x 4 pixels fall in distinct banks)
-  constexpr int kPhS = kBB + 4, kOmS = kTilePix + 4;
-  __shared__ float s_ph[MODE == kFull && DM ? 4 : 1][16 * kPhS];
+  // dense-blend mode only: the batch's feature dots, replaced by its weights
+  // (rows padded to 260 floats: the matrix-core operand reads of 16 entries x
+  // 4 pixels fall in distinct banks)
+  constexpr int kOmS = kTilePix + 4;
   __shared__ float s_fc[MODE == kFull && !DM ? kBB : 1][64];  // vector form: the batch's feature chunk
   __shared__ __align__(16) float s_om[MODE == kFull ? kBB : 1][kOmS];
-  // Top-K mode: every pixel's selected list positions ([K][256]), read back
-  // to front by the pixel's own lane; the feature dots stay in global memory,
-  // each loaded when the previous one is used (16 KB of LDS instead of 32 KB
-  // for K = 16 lets four blocks share a CU, with the kernel's registers held
-  // to 128 for four waves per SIMD)
-  extern __shared__ int s_sel[];
+  __shared__ uint32_t s_id[MODE == kFull ? kBB : 1];
+  // Top-K mode: every pixel's selected list positions ([K][256], 16 bits: a
+  // tile whose pixels reach further takes them from memory), read back to
+  // front by the pixel's own lane; the feature dots stay in global memory,
+  // each loaded when the previous one is used.  (With K = 16 a block then
+  // takes 35 KB of LDS and four share a CU; at three the walk is 15% slower.)
+  extern __shared__ uint16_t s_sel[];
 
   with_tile(tq, [&](const int tile) {
   const TileLoc tl = locate(ct, tile);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tx = tl.tx, ty = tl.ty, W = tl.W, H = tl.H;
   const int px = tx * ct.tw + tile_lx(ct, tid), py = ty * ct.th + tile_ly(ct, tid);
   const bool inside = px < W && py < H;
@@ -345,7 +381,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
   const int sp = tile * kTilePix + tid;
   const int my_last = (int)nlast[sp];
   float T = tfinal[sp];
-  const float Tfin = T;
   const int64_t pix = tl.pix0 + (int64_t)py * W + px;
   float gC0 = 0.f, gC1 = 0.f, gC2 = 0.f, gD = 0.f, gN0 = 0.f, gN1 = 0.f, gN2 = 0.f, gA = 0.f;
   if (inside) {
@@ -354,60 +389,86 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
     if (g_normal) { gN0 = g_normal[3 * pix]; gN1 = g_normal[3 * pix + 1]; gN2 = g_normal[3 * pix + 2]; }
     if (g_alpha) gA = g_alpha[pix];
   }
-  // Top-K: walk the saved selection from its back end
-  int kp = -1, nextsel = -1;
+  const float gAT = gA * T;
+  // the columns, a step per pixel of the quad: (1, x, y, -) about the
+  // sub-tile's centre, less the entry's centre; (dC, dn_0); (dn_1, dn_2, -, -);
+  // and unit column 2 for the plain sum
+  const int col = lane & 3;
+  const float mx = 0.5f * (sr.x0 + sr.x1), my = 0.5f * (sr.y0 + sr.y1);
+  float bg[4], bc[4], bn[4];
+  {
+    const float xs = (float)px + 0.5f - mx, ys = (float)py + 0.5f - my;
+    bg[0] = quad_col<0>(col, 1.f, xs, ys, 0.f); bc[0] = quad_col<0>(col, gC0, gC1, gC2, gN0); bn[0] = quad_col<0>(col, gN1, gN2, 0.f, 0.f);
+    bg[1] = quad_col<1>(col, 1.f, xs, ys, 0.f); bc[1] = quad_col<1>(col, gC0, gC1, gC2, gN0); bn[1] = quad_col<1>(col, gN1, gN2, 0.f, 0.f);
+    bg[2] = quad_col<2>(col, 1.f, xs, ys, 0.f); bc[2] = quad_col<2>(col, gC0, gC1, gC2, gN0); bn[2] = quad_col<2>(col, gN1, gN2, 0.f, 0.f);
+    bg[3] = quad_col<3>(col, 1.f, xs, ys, 0.f); bc[3] = quad_col<3>(col, gC0, gC1, gC2, gN0); bn[3] = quad_col<3>(col, gN1, gN2, 0.f, 0.f);
+  }
+  const float unit2 = col == 2 ? 1.0f : 0.0f;
+  const double mcol = col == 1 ? (double)mx : (double)my;
+  // Top-K: walk the saved selection from its back end.  kq: the last selection
+  // before the current batch, at position cursel; kp: the next one whose dot is
+  // used (held in nextdot)
+  int kp = -1, kq = -1, cursel = -1;
   float nextdot = 0.0f;
   const size_t tbase = (size_t)tile * K * kTilePix;
-  int* s_sp = s_sel;
+  uint16_t* s_sp = s_sel;
   const float* g_sd = seldot + tbase + tid;  // this pixel's dots, read one ahead of their use
   if (MODE == kTopK) {
     for (int q = 0; q < K; ++q) {
       const int sq = selpos[tbase + (size_t)q * kTilePix + tid];
-      s_sp[q * kTilePix + tid] = sq;
-      if (sq >= 0) kp = q;
+      s_sp[q * kTilePix + tid] = (uint16_t)sq;
+      if (sq >= 0) {
+        kp = q;
+        cursel = sq;
+      }
     }
-    if (kp >= 0) {
-      nextsel = s_sp[kp * kTilePix + tid];
-      nextdot = g_sd[(size_t)kp * kTilePix];
-    }
+    kq = kp;
+    if (kp >= 0) nextdot = g_sd[(size_t)kp * kTilePix];
   }
 
-  __syncthreads();
-  if (tid == 0) s_lmax = 0;
-  __syncthreads();
-  atomicMax(&s_lmax, my_last);
-  __syncthreads();
-  const int Lmax = __builtin_amdgcn_readfirstlane(s_lmax);  // block-uniform: a scalar loop bound
-  float suffix = 0.0f;
-  // the wave starts each batch at its own last contributor: the entries past
-  // it change nothing of its pixels (no selection lies there; in dense mode
-  // their weights are zero)
+  // the wave starts at its own last contributor: the entries past it change
+  // nothing of its pixels
   int wmax = my_last;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) wmax = max(wmax, __shfl_xor(wmax, o, 64));
-  wmax = __builtin_amdgcn_readfirstlane(wmax);  // the same in every lane: keeps the loop bound scalar
+  wmax = __builtin_amdgcn_readfirstlane(wmax);
+  if (tid == 0) s_lmax = 0;
+  __syncthreads();
+  if (lane == 0) atomicMax(&s_lmax, wmax);
+  __syncthreads();
+  const int Lmax = __builtin_amdgcn_readfirstlane(s_lmax);  // block-uniform: a scalar loop bound
+  float suffix = 0.0f;
 
+  // the batch's ids and culling records, a lane per entry (the upper half of
+  // the wave repeats the lower); records are read one batch ahead, ids two
+  const int el = lane & (kBB - 1);
+  const auto id_at = [&](int h) {
+    const int l = max(0, h - kBB);
+    return h > 0 ? pid[start + min(l + el, h - 1)] : 0u;
+  };
+  uint32_t id1 = id_at(Lmax), id2 = id_at(Lmax - kBB);
+  CullRec nc = rec[id1].c;
   for (int hi = Lmax; hi > 0; hi -= kBB) {
     const int lo = max(0, hi - kBB), nb = hi - lo;
-    __syncthreads();
-    if (tid < nb) {
-      const uint32_t id = pid[start + lo + tid];
-      s_id[tid] = id;  // virtual surfel id
-      s_r.put(tid, rec[id]);
-      s_cull[tid] = ext[id];
-    }
-    __syncthreads();
+    const uint32_t id = id1;
+    const bool meets = rect_meets<LP>(nc, sr.x0, sr.x1, sr.y0, sr.y1);
+    id1 = id2;
+    id2 = id_at(hi - 2 * kBB);
+    nc = rec[id1].c;
+    // entries of the batch that meet this wave's sub-tile and lie before its
+    // last contributor
+    const int ktop = min(nb, wmax - lo);
+    uint32_t mask = ktop > 0 ? (uint32_t)__ballot(meets) & (0xFFFFFFFFu >> (kBB - ktop)) : 0u;
 
-    // dense mode: phi[k] = g_F(p) . f_k for the batch, the product
-    // PHI = G F^T on the matrix cores: wave w takes its 4 pixel blocks of 16
-    // x the 2 entry blocks of 16, k = 4 channels per step (lane (li, lk)
-    // loads channels 4 lk .. 4 lk + 3 of a 16-channel group as one vector,
-    // component i feeding step i); the tile goes through the wave's LDS
-    // region to the lanes of its pixels
-    float phi[MODE == kFull ? kBB : 1];
+    // dense mode: phi[k] = g_F(p) . f_k for the batch, left in s_om
+    if constexpr (MODE == kFull) {
+      if (wave == 0 && lane < nb) s_id[lane] = id;
+      __syncthreads();
+    }
     if constexpr (MODE == kFull && !DM) {
       // vector form: feature chunks of 64 channels staged in LDS, each pixel
       // its 32 dots (LDS reads by broadcast)
+      float phi[kBB];
 #pragma unroll
       for (int k = 0; k < kBB; ++k) phi[k] = 0.0f;
       if (g_feat) {
@@ -431,79 +492,171 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
           __syncthreads();
         }
       }
+#pragma unroll
+      for (int k = 0; k < kBB; ++k) s_om[k][tid] = phi[k];
     }
     if constexpr (MODE == kFull && DM) {
+      // the product PHI = G F^T on the matrix cores: wave w takes its 4 pixel
+      // blocks of 16 x the 2 entry blocks of 16, k = 4 channels per step (lane
+      // (li, lk) loads channels 4 lk .. 4 lk + 3 of a 16-channel group as one
+      // vector, component i feeding step i)
+      const int li = lane & 15, lk = lane >> 4;
+      int fr[2];  // feature row of the lane's entry of each block, -1 past the batch
 #pragma unroll
-      for (int k = 0; k < kBB; ++k) phi[k] = 0.0f;
-      if (g_feat) {
-        const int li = lane & 15, lk = lane >> 4;
-        int fr[2];  // feature row of the lane's entry of each block, -1 past the batch
-#pragma unroll
-        for (int eb = 0; eb < 2; ++eb) {
-          const int e = 16 * eb + li;
-          fr[eb] = e < nb ? (int)(s_id[e] - tl.v0) : -1;
-        }
-        float* ph = s_ph[wave];
-        for (int pb = 0; pb < 4; ++pb) {
-          const int q = 64 * wave + 16 * pb + li;  // pixel of lane li
-          const int qx = tx * ct.tw + tile_lx(ct, q), qy = ty * ct.th + tile_ly(ct, q);
-          const float* gq = qx < W && qy < H ? g_feat + (tl.pix0 + (int64_t)qy * W + qx) * C : nullptr;
-          f4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-          // 128 channels at a time: every operand of the segment is loaded
-          // before its products, so the loads are in flight together
-          for (int cs = 0; cs < C; cs += 128) {
-            float4 a[8], b[2][8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const int c = cs + 16 * j + 4 * lk;  // C % 4 == 0: a group of 4 is whole or absent
-              a[j] = gq && c < C ? *reinterpret_cast<const float4*>(gq + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-              for (int eb = 0; eb < 2; ++eb)
-                b[eb][j] = fr[eb] >= 0 && c < C ? feat.load4(fr[eb], c) : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-#pragma unroll
-              for (int eb = 0; eb < 2; ++eb) {
-                acc[eb] = mfma_16x16x4(a[j].x, b[eb][j].x, acc[eb]);
-                acc[eb] = mfma_16x16x4(a[j].y, b[eb][j].y, acc[eb]);
-                acc[eb] = mfma_16x16x4(a[j].z, b[eb][j].z, acc[eb]);
-                acc[eb] = mfma_16x16x4(a[j].w, b[eb][j].w, acc[eb]);
-              }
-          }
-#pragma unroll
-          for (int eb = 0; eb < 2; ++eb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) ph[(4 * lk + r) * kPhS + 16 * eb + li] = acc[eb][r];
-          wave_lds_sync();
-          if (lk == pb) {
-#pragma unroll
-            for (int k = 0; k < kBB; ++k) phi[k] = ph[li * kPhS + k];
-          }
-          wave_lds_sync();
-        }
+      for (int eb = 0; eb < 2; ++eb) {
+        const int e = 16 * eb + li;
+        fr[eb] = e < nb ? (int)(s_id[e] - tl.v0) : -1;
       }
+      for (int pb = 0; pb < 4; ++pb) {
+        const int q = 64 * wave + 16 * pb + li;  // pixel of lane li
+        const int qx = tx * ct.tw + tile_lx(ct, q), qy = ty * ct.th + tile_ly(ct, q);
+        const float* gq = g_feat && qx < W && qy < H ? g_feat + (tl.pix0 + (int64_t)qy * W + qx) * C : nullptr;
+        f4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        // 128 channels at a time: every operand of the segment is loaded
+        // before its products, so the loads are in flight together
+        for (int cs = 0; g_feat && cs < C; cs += 128) {
+          float4 a[8], b[2][8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const int c = cs + 16 * j + 4 * lk;  // C % 4 == 0: a group of 4 is whole or absent
+            a[j] = gq && c < C ? *reinterpret_cast<const float4*>(gq + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int eb = 0; eb < 2; ++eb)
+              b[eb][j] = fr[eb] >= 0 && c < C ? feat.load4(fr[eb], c) : make_float4(0.f, 0.f, 0.f, 0.f);
+          }
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int eb = 0; eb < 2; ++eb) {
+              acc[eb] = mfma_16x16x4(a[j].x, b[eb][j].x, acc[eb]);
+              acc[eb] = mfma_16x16x4(a[j].y, b[eb][j].y, acc[eb]);
+              acc[eb] = mfma_16x16x4(a[j].z, b[eb][j].z, acc[eb]);
+              acc[eb] = mfma_16x16x4(a[j].w, b[eb][j].w, acc[eb]);
+            }
+        }
+#pragma unroll
+        for (int eb = 0; eb < 2; ++eb)
+          *reinterpret_cast<f4v*>(&s_om[16 * eb + li][64 * wave + 16 * pb + 4 * lk]) = acc[eb];
+      }
+      wave_lds_sync();  // a wave reads back its own pixels only
+    }
+    if constexpr (MODE == kFull) {
+      // entries the wave does not evaluate have zero weight
+      for (uint32_t m = ~mask & (0xFFFFFFFFu >> (kBB - nb)); m; m &= m - 1) s_om[__builtin_ctz(m)][tid] = 0.0f;
     }
 
-    // surfels of the batch that meet this wave's sub-tile
-    const uint64_t band = __ballot(lane < nb && rect_meets<LP>(s_cull[lane < kBB ? lane : 0], sr.x0, sr.x1, sr.y0, sr.y1));
-    const int ktop = min(nb - 1, wmax - 1 - lo);
-    if (lane > ktop && lane < nb) s_has[wave][lane] = 0u;  // skipped entries: nothing to add
-    if constexpr (MODE == kFull)
-      for (int k = max(ktop + 1, 0); k < nb; ++k) s_om[k][tid] = 0.0f;  // and zero weight
-#pragma unroll 1
-    for (int k = ktop; k >= 0; --k) {
-      const int pos = lo + k;
-      // the pixel's terms are products of these scalars, all zero where the
-      // pixel does not take part
-      float w = 0.0f, du1 = 0.0f, dv1 = 0.0f, dw1 = 0.0f, dzi = 0.0f, dop = 0.0f, ex = 0.0f, ey = 0.0f;
-      float gcx = 0.0f, gcy = 0.0f;  // low-pass term: direct gradient of the projected centre
-      bool contrib = false;
-      if (pos < my_last && ((band >> k) & 1u)) {
-        const LRec s = s_r.get(k);
+    // the pixel's selections in the batch as bits, so that the entry loop
+    // reads nothing from LDS for them: such a read is waited for together
+    // with the next record's scalar load, whose latency it would expose
+    uint32_t selbits = 0u;
+    if (MODE == kTopK) {
+      while (__any(cursel >= lo)) {
+        const bool in = cursel >= lo;
+        selbits |= in ? 1u << (cursel - lo) : 0u;
+        kq -= in ? 1 : 0;
+        const int q = max(kq, 0) * kTilePix + tid;
+        const int sq = Lmax <= 0xFFFF ? (int)s_sp[q] : selpos[tbase + q];
+        cursel = kq >= 0 ? sq : -1;
+      }
+    }
+    // what the combination below needs of the pair and its record
+    const int ce = (tid >> 2) & (kBB - 1), cq = tid & 3;
+    const bool comb = wave < 2 && ce < nb;
+    const uint32_t cid = (uint32_t)__shfl((int)id, ce, 64);
+    float ca0 = 0.f, ca1 = 0.f, ca2 = 0.f, ca3 = 0.f, ca4 = 0.f, ca5 = 0.f;
+    uint32_t cslot = 0u;
+    if (comb) cslot = eid[start + lo + ce];
+
+    uint32_t has = 0u;    // entries with a contributor in this wave
+    uint32_t group = 0u;  // the open group's entries, 8 bits each
+    int ng = 0;
+    // geometric products of the open pair (entries 2 h, 2 h + 1 of the group):
+    // entry i's row r, column j of block b in register r of lane 4 b + j
+    f4v dg[4];
+    const auto pair = [&](auto hc) {
+      constexpr int h = decltype(hc)::value;
+      wave_lds_sync();
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const f4v f = *reinterpret_cast<const f4v*>(&s_geo[wave][i][lane & 3][lane & ~3]);
+        const float off = s_off[wave][i][col], offl = s_off[wave][i][4 + col];
+        f4v d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int st = 0; st < 4; ++st) d = mfma_4x4x1(f[st], (bg[st] - off) - offl, d);
+        dg[2 * h + i] = d;
+      }
+      wave_lds_sync();
+    };
+    // the group's other products (entry i's column j in register i), then the
+    // 16 blocks added across lanes, which leaves entry i's sums in lane group i
+    const auto flush = [&]() {
+      f4v dc = {0.f, 0.f, 0.f, 0.f}, dn = dc, dl = dc;
+      wave_lds_sync();
+      const auto fac = [&](int f) { return *reinterpret_cast<const f4v*>(&s_col[wave][f][lane & 3][lane & ~3]); };
+      const f4v fw = fac(0), fz = fac(1);
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        dc = mfma_4x4x1(fw[st], bc[st], dc);
+        dn = mfma_4x4x1(fw[st], bn[st], dn);
+      }
+#pragma unroll
+      for (int st = 0; st < 4; ++st) dn = mfma_4x4x1(fz[st], unit2, dn);
+      if constexpr (LP) {
+        const f4v fx = fac(NC - 2), fy = fac(NC - 1);
+#pragma unroll
+        for (int st = 0; st < 4; ++st) {
+          dl = mfma_4x4x1(fx[st], col == 1 ? 1.0f : 0.0f, dl);
+          dl = mfma_4x4x1(fy[st], col == 2 ? 1.0f : 0.0f, dl);
+        }
+      }
+      wave_lds_sync();
+      float* dst = &s_part[wave][(group >> (8 * (lane >> 4))) & (kBB - 1)][0];
+      const bool put = (lane & 12) == 0 && (lane >> 4) < ng;
+      // x0..x3: the four entries' values; lane group i (16 lanes) gets entry i's
+      const auto sum4 = [&](float x0, float x1, float x2, float x3) {
+        float v = swap16_add(swap32_add(x0, x2), swap32_add(x1, x3));
+        v += dpp_mov<kDppRowRor8>(v);
+        v += dpp_mov<kDppRowRor4>(v);
+        return v;
+      };
+      const float t0 = sum4(dg[0][0], dg[1][0], dg[2][0], dg[3][0]), t1 = sum4(dg[0][1], dg[1][1], dg[2][1], dg[3][1]);
+      const float t2 = sum4(dg[0][2], dg[1][2], dg[2][2], dg[3][2]), t3 = sum4(dg[0][3], dg[1][3], dg[2][3], dg[3][3]);
+      const float tc = sum4(dc[0], dc[1], dc[2], dc[3]), tn = sum4(dn[0], dn[1], dn[2], dn[3]);
+      float tl = 0.0f;
+      if constexpr (LP) tl = sum4(dl[0], dl[1], dl[2], dl[3]);
+      if (put) {
+        if (col < 3) {
+          dst[col] = t0;
+          dst[4 + col] = t1;
+          dst[8 + col] = t2;
+          dst[4 * col + 3] = tn;
+        }
+        dst[12 + col] = tc;
+        if constexpr (LP) dst[16 + col] = col == 0 ? t3 : tl;
+        else if (col == 0) dst[16] = t3;
+      }
+      group = 0u;
+      ng = 0;
+    };
+
+    if (mask) {
+      int k = 31 - __builtin_clz(mask);
+      SRec next = load_rec(rec, lane_value(id, k));
+      do {
+        const int pos = lo + k, ke = k;
+        const LRec s = next.get();
+        mask &= ~(1u << k);
+        if (mask) {
+          k = 31 - __builtin_clz(mask);
+          next = load_rec(rec, lane_value(id, k));
+        }
+        // the pixel's factors, all zero where it does not take part
+        float w = 0.0f, du1 = 0.0f, dv1 = 0.0f, dw1 = 0.0f, dzi = 0.0f, dop = 0.0f;
+        float gcx = 0.0f, gcy = 0.0f;  // low-pass term: direct gradient of the projected centre
         PixEval e;
-        if (eval_pixel<LP>(s, X, Y, e)) {
-          contrib = true;
+        const bool contrib = eval_pixel<LP>(s, X, Y, e) & (pos < my_last);
+        const bool takes = contrib & ((selbits & (1u << ke)) != 0u);
+        if (contrib) {
           // 1 / (1 - alpha) once for both quotients: alpha <= 0.99, so the
           // reciprocal's relative error (about 1 ulp) stays that small
           const float r1m = __builtin_amdgcn_rcpf(1.0f - e.alpha);
@@ -511,20 +664,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
           w = e.alpha * Tb;
           const float u = e.u, vv = e.v, z = s.mz * e.iw;
           float eF = 0.0f;
-          if (MODE == kTopK) {
-            if (pos == nextsel) {
-              eF = nextdot;
-              --kp;
-              nextsel = kp >= 0 ? s_sp[kp * kTilePix + tid] : -1;
-              nextdot = kp >= 0 ? g_sd[(size_t)kp * kTilePix] : 0.0f;
-            }
-          } else {
-#pragma unroll
-            for (int q = 0; q < kBB; ++q)
-              if (q == k) eF = phi[q];
-          }
+          if (MODE == kTopK) eF = takes ? nextdot : 0.0f;
+          else eF = s_om[ke][tid];
           const float ei = gC0 * s.r + gC1 * s.g + gC2 * s.b + gD * z + gN0 * s.n0 + gN1 * s.n1 + gN2 * s.n2 + eF;
-          const float da = Tb * ei - (suffix - gA * Tfin) * r1m;
+          const float da = Tb * ei - (suffix - gAT) * r1m;
           suffix = fmaf(w, ei, suffix);
           T = Tb;
           dop = e.clamped ? 0.0f : da * e.G;
@@ -541,64 +684,101 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
             dv1 = dv * e.iw;
             dw1 = -(du * u + dv * vv + dz * z) * e.iw;
             dzi = dz * e.iw;
-            ex = e.dx;
-            ey = e.dy;
           }
         }
-      }
-      if constexpr (MODE == kFull) s_om[k][tid] = w;
-      const bool any = __any(contrib);
-      if (any) {
-        float v16[16] = {du1 * ex, du1 * ey, du1, dv1 * ex, dv1 * ey, dv1, dw1 * ex, dw1 * ey,
-                         dw1,      dzi,      dop, w * gC0,  w * gC1,  w * gC2, w * gN0,  w * gN1};
-        const float tot = wave_reduce16(v16);
-        const float last = wave_sum(w * gN2);
-        if ((lane & 3) == 0) s_part[wave][k][(lane >> 2) & 15] = tot;
-        if (lane == 0) s_part[wave][k][16] = last;
-        if constexpr (LP) {
-          const float c0 = wave_sum(gcx), c1 = wave_sum(gcy);
-          if (lane == 0) {
-            s_part[wave][k][17] = c0;
-            s_part[wave][k][18] = c1;
+        if constexpr (MODE == kFull) s_om[ke][tid] = w;
+        if (MODE == kTopK && __any(takes)) {
+          // the next selection's dot, read by every lane, so that the load in
+          // flight is waited for where it is used and not at once (as the
+          // lanes that keep theirs would have it)
+          kp -= takes ? 1 : 0;
+          nextdot = g_sd[max(kp, 0) * kTilePix];
+        }
+        if (__any(contrib)) {
+          float* f = &s_geo[wave][ng & 1][0][lane];
+          f[0] = du1;
+          f[64] = dv1;
+          f[128] = dw1;
+          f[192] = dop;
+          float* fc = &s_col[wave][0][ng][lane];
+          fc[0] = w;
+          fc[256] = dzi;
+          if constexpr (LP) {
+            fc[512] = gcx;
+            fc[768] = gcy;
+          }
+          // the offsets keep their relative accuracy where they are small (a
+          // thin surfel's chain rule amplifies their error by its aspect)
+          const double offd = (col == 1 ? s.xc : s.yc) - mcol;
+          const float off = (float)offd, offl = (float)(offd - (double)off);
+          const bool xy = col == 1 || col == 2;
+          if (lane < 8) s_off[wave][ng & 1][lane] = xy ? (lane < 4 ? off : offl) : 0.0f;
+          has |= 1u << ke;
+          group |= (uint32_t)ke << (8 * ng);
+          ++ng;
+          if (ng == 2) pair(std::integral_constant<int, 0>{});
+          if (ng == 4) {
+            pair(std::integral_constant<int, 1>{});
+            flush();
           }
         }
+      } while (mask);
+      if (ng) {
+        if (ng == 1) pair(std::integral_constant<int, 0>{});
+        if (ng == 3) pair(std::integral_constant<int, 1>{});
+        flush();
       }
-      if (lane == 0) s_has[wave][k] = any ? 1u : 0u;
+    }
+    if (lane == 0) s_has[wave] = has;
+
+    // combine the 4 waves, four threads per entry, each one float4 of the
+    // pair's 16 accumulators
+    if (comb && cq == 1) {
+      const WalkRec& rr = rec[cid];
+      ca0 = (float)rr.d0.x; ca1 = (float)rr.d0.y;
+      ca2 = (float)rr.d1.x; ca3 = (float)rr.d1.y;
+      ca4 = (float)rr.d2.x; ca5 = (float)rr.d2.y;
     }
     __syncthreads();
-
-    // combine the 4 waves, convert to the 16 per-surfel accumulators
-    if (tid < nb) {
-      const int k = tid;
-      if (s_has[0][k] | s_has[1][k] | s_has[2][k] | s_has[3][k]) {
-        float t[kNV];
+    if (comb) {
+      bool any = false;
+      // the rows a thread needs: 0, 1 (and 2 for the second); 2, 3, 4; 0, 1, 3
+      f4v A = {0.f, 0.f, 0.f, 0.f}, B = A, C4 = A, E = A;
+      const int ra = cq == 2 ? 8 : 0, rb = cq == 2 ? 16 : 4, rc = cq < 2 ? 8 : 12;
 #pragma unroll
-        for (int i = 0; i < kNV; ++i) {
-          float a = 0.0f;
-#pragma unroll
-          for (int w = 0; w < 4; ++w) a += s_has[w][k] ? s_part[w][k][i] : 0.0f;
-          t[i] = a;
-        }
-        const uint32_t id = s_id[k];
-        const WalkRec& rr = rec[id];
-        const float a00 = (float)rr.d0.x, a01 = (float)rr.d0.y, a10 = (float)rr.d1.x, a11 = (float)rr.d1.y;
-        const float e0 = (float)rr.d2.x, e1 = (float)rr.d2.y;
-        const size_t slot = eid[start + lo + k];
+      for (int w = 0; w < 4; ++w) {
+        if (!((s_has[w] >> ce) & 1u)) continue;
+        any = true;
+        const float* x = s_part[w][ce];
+        A += *reinterpret_cast<const f4v*>(x + ra);
+        B += *reinterpret_cast<const f4v*>(x + rb);
+        C4 += *reinterpret_cast<const f4v*>(x + rc);
+        if constexpr (LP) E += *reinterpret_cast<const f4v*>(x + 16);
+      }
+      if (any) {
+        const size_t slot = cslot;
         float4* g = reinterpret_cast<float4*>(gpart + slot * 16);
         // u' = A^-1 d, w' = 1 - e.d with d = pixel - centre; d depends on the
         // centre with slope -1
-        g[0] = make_float4(t[0], t[1], t[3], t[4]);
-        float gxc = -(a00 * t[2] + a10 * t[5] - e0 * t[8]), gyc = -(a01 * t[2] + a11 * t[5] - e1 * t[8]);
-        if constexpr (LP) {
-          gxc += t[17];
-          gyc += t[18];
+        if (cq == 0) {
+          g[0] = make_float4(A[1], A[2], B[1], B[2]);
+          gflag[slot] = 1;
+        } else if (cq == 1) {
+          float gxc = -(ca0 * A[0] + ca2 * B[0] - ca4 * C4[0]);
+          float gyc = -(ca1 * A[0] + ca3 * B[0] - ca5 * C4[0]);
+          if constexpr (LP) {
+            gxc += E[1];
+            gyc += E[2];
+          }
+          g[1] = make_float4(-C4[1], -C4[2], gxc, gyc);
+        } else if (cq == 2) {
+          g[2] = make_float4(A[3], B[0], C4[0], C4[1]);
+        } else {
+          g[3] = make_float4(C4[2], C4[3], A[3], B[3]);
         }
-        g[1] = make_float4(-t[6], -t[7], gxc, gyc);
-        g[2] = make_float4(t[9], t[10], t[11], t[12]);
-        g[3] = make_float4(t[13], t[14], t[15], t[16]);
-        gflag[slot] = 1;
       }
     }
+    __syncthreads();
 
     // dense mode: dL/df_k = sum_p w_k(p) g_F(p) for the batch, the product
     // R = W^T G on the matrix cores: units (entry block of 16, channel block
@@ -610,7 +790,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
       // 256 pixels 8 at a time (8 independent upstream loads in flight;
       // pixels outside the image have zero weight and read as zero)
       if (g_feat) {
-        __syncthreads();
         constexpr int PER = kBB / 4;
         // the tile's pixels inside the image: wl columns, hl rows; pixel
         // offsets from the tile's first one are below 2^29 (W, C and the tile
@@ -661,7 +840,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
     }
     if constexpr (MODE == kFull && DM) {
       if (g_feat) {
-        __syncthreads();
         const int li = lane & 15, lk = lane >> 4;
         const int ncb = (C + 15) >> 4;
         // the tile's pixels inside the image: wl columns, hl rows
@@ -1145,9 +1323,9 @@ static void feat_bwd_k(const SurfelArgs& s, const Layout& L, const CamTable& ct,
 template <int MODE, typename FT, bool LP, bool DM>
 static void walk_bwd_launch_d(const SurfelArgs& s, const Layout& L, const CamTable& ct, const Tuning& tu,
                               const ImageGradArgs& g, bool want_f, char* ws, hipStream_t st) {
-  const size_t shm = MODE == kTopK ? (size_t)L.k * kTilePix * 4 : 0;  // selection positions
+  const size_t shm = MODE == kTopK ? (size_t)L.k * kTilePix * 2 : 0;  // selection positions
   hipLaunchKernelGGL((k_walk_bwd<MODE, FT, LP, DM>), dim3(xcd_grid(L.tiles)), dim3(256), shm,
-                     st, (const WalkRec*)(ws + L.rec), (const CullRec*)(ws + L.ext), (const uint32_t*)(ws + L.pid),
+                     st, (const WalkRec*)(ws + L.rec), (const uint32_t*)(ws + L.pid),
                      (const uint32_t*)(ws + L.eid0), (const uint2*)(ws + L.ranges), ct,
                      tile_order(L, tu.sched_bwd, ws), L.k,
                      (const uint32_t*)(ws + L.nlast), (const float*)(ws + L.tfinal), (const int32_t*)(ws + L.selpos),

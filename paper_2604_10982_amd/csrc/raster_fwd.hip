@@ -56,7 +56,7 @@ constexpr int kWalkChunk = 64;  // list entries a wave examines at once
 // (64 vector instructions for K = 16; a heap of 64-bit keys with a search for
 // the new minimum took 123, in sequence).
 template <int KMAX, bool TOPK, bool LP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_walk(const WalkRec* __restrict__ rec, const CullRec* __restrict__ ext,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_walk(const WalkRec* __restrict__ rec,
                                               const uint32_t* __restrict__ pid,
                                               const uint2* __restrict__ ranges, CamTable ct, TileOrder tq,
                                               int K, float* __restrict__ o_rgb, float* __restrict__ o_depth,
@@ -97,13 +97,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   // records one
   const auto id_at = [&](int j) { return j < L ? ids[j] : 0u; };
   uint32_t id = id_at(lane), nid = id_at(kWalkChunk + lane);
-  CullRec c = ext[id];
+  CullRec c = rec[id].c;
   for (int base = 0; base < L; base += kWalkChunk) {
     uint64_t mask = __ballot(base + lane < L && rect_meets<LP>(c, sr.x0, sr.x1, sr.y0, sr.y1));
     const uint32_t cid = id;
     id = nid;
     nid = id_at(base + 2 * kWalkChunk + lane);
-    c = ext[id];
+    c = rec[id].c;
     if (mask == 0) continue;
     int k = __builtin_ctzll(mask);
     SRec next = load_rec(rec, lane_value(cid, k));
@@ -585,7 +585,7 @@ template <int KMAX, bool TOPK, bool LP>
 static void walk_launch_t(const Layout& L, const CamTable& ct, const Tuning& tu, const ImageArgs& out,
                           bool feat_only, char* ws, hipStream_t st) {
   hipLaunchKernelGGL((k_walk<KMAX, TOPK, LP>), dim3(xcd_grid(L.tiles)), dim3(256), 0, st,
-                     (const WalkRec*)(ws + L.rec), (const CullRec*)(ws + L.ext), (const uint32_t*)(ws + L.pid),
+                     (const WalkRec*)(ws + L.rec), (const uint32_t*)(ws + L.pid),
                      (const uint2*)(ws + L.ranges), ct, tile_order(L, tu.sched, ws), L.k, out.rgb, out.depth,
                      out.normal, out.alpha,
                      (uint32_t*)(ws + L.nlast), (float*)(ws + L.tfinal), (int32_t*)(ws + L.selpos),
