@@ -201,7 +201,9 @@ inline Layout make_layout(const CamTable& ct, int k, int c, int64_t cap) {
   const int64_t nb = cdiv(big, kSortTile);
   L.hist = take((256 * nb + 256) * 4);
   L.bsum = take((cdiv(n1, kScanTile) + 1) * 8);
-  L.ubits = take(cdiv(n1, 32) * 4);  // one bit per virtual surfel: selected somewhere (stats read-back)
+  // one bit per virtual surfel: selected somewhere (stats read-back); in the
+  // backward, per surfel: its pairs are summed by a block of its own
+  L.ubits = take(cdiv(n1, 32) * 4);
   // surfels with more than kHeavyRows flagged rows: the rows are pairs, whose
   // ranges are disjoint inside the capacity, so at most cap / (kHeavyRows + 1)
   L.heavy = take((cap1 / (kHeavyRows + 1) + 1) * 4);

@@ -17,7 +17,8 @@
 //   are summed over the wave by small matrix products, then over the 4 waves
 //   through LDS, and written as the pair's 16 partial sums.  In dense-blend mode each batch also forms
 //   the feature dot products and feature-gradient rows tile-wide.
-// k_reduce_geo / k_reduce_feat: per surfel, sum of its pairs' partials, then
+// k_reduce_geo / k_reduce_feat (and their _heavy forms for surfels with many
+//   pairs): per surfel, sum of its pairs' partials, then
 //   the chain rule to mu, s, q (FP64, as the forward's walk record).
 #include <type_traits>
 
@@ -984,54 +985,79 @@ __device__ __forceinline__ void chain_rule(const double (&G)[16], const CamArgs&
   acc.rgb[2] += G[12];
 }
 
-// Thread per surfel: for each camera in order, the sum of its pairs' partials
-// (its emitted range [vbase, vbase + count), in emission order), then that
-// camera's chain rule; the cameras' contributions are added in camera order.
-// A surfel's pair count ranges from 0 to several hundred (a heavy tail), so
-// the wave's 64 ranges are read as one flat sequence: lane l loads pair
-// t0 + l of it (coalesced), the batch is staged in LDS, and each surfel's
-// lane adds its own pairs of the batch.  The sums are the same, term by
-// term, as a per-surfel loop over its range.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_reduce_geo(int64_t n, CamTable ct, const uint32_t* __restrict__ vbase,
-                                                    const uint32_t* __restrict__ count, int64_t cap,
-                                                    const float* __restrict__ gpart,
-                                                    const uint8_t* __restrict__ gflag,
-                                                    const float* __restrict__ means, const float* __restrict__ scales,
-                                                    const float* __restrict__ quats, const int32_t* __restrict__ cull,
-                                                    float* __restrict__ d_means, float* __restrict__ d_scales,
-                                                    float* __restrict__ d_quats, float* __restrict__ d_opacity,
-                                                    float* __restrict__ d_rgb) {
+// The surfel parameters the chain rule takes.
+struct SurfelParams {
+  double mu[3], su, sv, rn, qn[4], Rq[3][3];
+};
+__device__ __forceinline__ void load_params(SurfelParams& P, int64_t i, const float* __restrict__ means,
+                                            const float* __restrict__ scales, const float* __restrict__ quats) {
+  P.mu[0] = means[3 * i]; P.mu[1] = means[3 * i + 1]; P.mu[2] = means[3 * i + 2];
+  P.su = scales[2 * i]; P.sv = scales[2 * i + 1];
+  const double q0 = quats[4 * i], q1 = quats[4 * i + 1], q2 = quats[4 * i + 2], q3 = quats[4 * i + 3];
+  const double qq = q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3;
+  P.rn = qq > 0.0 ? 1.0 / sqrt(qq) : 0.0;
+  P.qn[0] = q0 * P.rn; P.qn[1] = q1 * P.rn; P.qn[2] = q2 * P.rn; P.qn[3] = q3 * P.rn;
+  const double w = P.qn[0], x = P.qn[1], y = P.qn[2], z = P.qn[3];
+  P.Rq[0][0] = 1. - 2. * (y * y + z * z); P.Rq[0][1] = 2. * (x * y - w * z); P.Rq[0][2] = 2. * (x * z + w * y);
+  P.Rq[1][0] = 2. * (x * y + w * z); P.Rq[1][1] = 1. - 2. * (x * x + z * z); P.Rq[1][2] = 2. * (y * z - w * x);
+  P.Rq[2][0] = 2. * (x * z - w * y); P.Rq[2][1] = 2. * (y * z + w * x); P.Rq[2][2] = 1. - 2. * (x * x + y * y);
+}
+__device__ __forceinline__ void clear_grad(SurfelGrad& g) {
+  for (int j = 0; j < 3; ++j) g.mu[j] = g.rgb[j] = 0.0;
+  for (int j = 0; j < 4; ++j) g.q[j] = 0.0;
+  g.su = g.sv = g.o = 0.0;
+}
+struct GeoGrads {
+  float *means, *scales, *quats, *opacity, *rgb;
+};
+__device__ __forceinline__ void write_grad(const SurfelGrad& acc, const SurfelParams& P, int64_t i,
+                                           const GeoGrads& d) {
+  // unit quaternion: project out the radial component
+  const double dot = P.qn[0] * acc.q[0] + P.qn[1] * acc.q[1] + P.qn[2] * acc.q[2] + P.qn[3] * acc.q[3];
+  for (int j = 0; j < 4; ++j) d.quats[4 * i + j] = (float)((acc.q[j] - P.qn[j] * dot) * P.rn);
+  for (int j = 0; j < 3; ++j) d.means[3 * i + j] = (float)acc.mu[j];
+  d.scales[2 * i] = (float)acc.su;
+  d.scales[2 * i + 1] = (float)acc.sv;
+  d.opacity[i] = (float)acc.o;
+  for (int j = 0; j < 3; ++j) d.rgb[3 * i + j] = (float)acc.rgb[j];
+}
+
+// Wave per 64 surfels: for each camera in order, the sum of a surfel's pairs'
+// partials (its emitted range [vbase, vbase + count), in emission order), then
+// that camera's chain rule (a lane per surfel); the cameras' contributions are
+// added in camera order.  The wave's 64 ranges are read as one flat sequence:
+// lane l loads pair t0 + l of it (coalesced) and the batch is staged in LDS;
+// then a group of 16 lanes (lane = component) takes every fourth surfel of the
+// batch and adds its pairs to the surfel's FP64 sums in LDS.  The sums are the
+// same, term by term, as a per-surfel loop over its range, and a batch that
+// holds a surfel's 64 pairs costs 64 steps of one read instead of 64 of 16.
+// A surfel with more than kHeavyGeo flagged pairs of one camera (a near, large
+// one: up to several thousand) would still hold its wave: it is marked in
+// `heavy` (a bit per surfel) and left to k_reduce_geo_heavy.  The choice
+// depends on its flagged pairs alone.
+constexpr int kHeavyGeo = 64;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_reduce_geo(
+    int64_t n, CamTable ct, const uint32_t* __restrict__ vbase, const uint32_t* __restrict__ count, int64_t cap,
+    const float* __restrict__ gpart, const uint8_t* __restrict__ gflag, const float* __restrict__ means,
+    const float* __restrict__ scales, const float* __restrict__ quats, const int32_t* __restrict__ cull, GeoGrads d,
+    uint64_t* __restrict__ heavy) {
   constexpr int kPS = 17;  // LDS row stride of a staged pair (16 partials)
   __shared__ float s_part[4][64 * kPS];
+  constexpr int kSS = 65;  // row stride of the sums: a group's 16 components fall in distinct banks
+  __shared__ double s_sum[4][16 * kSS];
   __shared__ uint32_t s_pre[4][64];
   __shared__ uint32_t s_vb[4][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t i = ((int64_t)blockIdx.x * 4 + wave) * 64 + lane;
-  const bool valid = i < n;  // every lane stays: the wave shares the pair loads
+  if (i - lane >= n) return;  // no block barriers below
+  const bool valid = i < n;   // every lane stays: the wave shares the pair loads
   const int64_t ii = valid ? i : 0;
+  const int grp = lane >> 4, comp = lane & 15;
   SurfelGrad acc;
-  for (int j = 0; j < 3; ++j) acc.mu[j] = acc.rgb[j] = 0.0;
-  for (int j = 0; j < 4; ++j) acc.q[j] = 0.0;
-  acc.su = acc.sv = acc.o = 0.0;
-  // the surfel's parameters are re-read (an L1/L2 hit) where they are used
-  // rather than held through the pair sums: it keeps the kernel's registers
-  // to what the sums and the chain rule need
-  struct Params {
-    double mu[3], su, sv, rn, qn[4], Rq[3][3];
-  };
-  auto params = [&](Params& P) {
-    P.mu[0] = means[3 * ii]; P.mu[1] = means[3 * ii + 1]; P.mu[2] = means[3 * ii + 2];
-    P.su = scales[2 * ii]; P.sv = scales[2 * ii + 1];
-    const double q0 = quats[4 * ii], q1 = quats[4 * ii + 1], q2 = quats[4 * ii + 2], q3 = quats[4 * ii + 3];
-    const double qq = q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3;
-    P.rn = qq > 0.0 ? 1.0 / sqrt(qq) : 0.0;
-    P.qn[0] = q0 * P.rn; P.qn[1] = q1 * P.rn; P.qn[2] = q2 * P.rn; P.qn[3] = q3 * P.rn;
-    const double w = P.qn[0], x = P.qn[1], y = P.qn[2], z = P.qn[3];
-    P.Rq[0][0] = 1. - 2. * (y * y + z * z); P.Rq[0][1] = 2. * (x * y - w * z); P.Rq[0][2] = 2. * (x * z + w * y);
-    P.Rq[1][0] = 2. * (x * y + w * z); P.Rq[1][1] = 1. - 2. * (x * x + z * z); P.Rq[1][2] = 2. * (y * z - w * x);
-    P.Rq[2][0] = 2. * (x * z - w * y); P.Rq[2][1] = 2. * (y * z + w * x); P.Rq[2][2] = 1. - 2. * (x * x + y * y);
-  };
+  clear_grad(acc);
   float* part = s_part[wave];
+  double* sums = s_sum[wave];
+  bool is_heavy = false;
   // the next camera's pair range is loaded while this camera's is summed
   int32_t ncv = valid ? cull[i] : 1;
   uint32_t nvb = valid ? vbase[i] : 0u, nvc = valid ? count[i] : 0u;
@@ -1047,7 +1073,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       nvc = count[v];
     }
     const bool live = valid && (cv & 0xFF) == 0;
-    const uint32_t cnt = live && end > (int64_t)vb ? (uint32_t)(end - (int64_t)vb) : 0u;
+    uint32_t cnt = live && end > (int64_t)vb ? (uint32_t)(end - (int64_t)vb) : 0u;
+    // long ranges: count the flagged pairs, four flag bytes a lane
+    for (uint64_t m = __ballot(cnt > (uint32_t)kHeavyGeo); m; m &= m - 1) {
+      const int o = __builtin_ctzll(m);
+      const uint32_t p0 = lane_value(vb, o), p1 = p0 + lane_value(cnt, o);
+      int nf = 0;
+      for (uint32_t w = (p0 >> 2) + (uint32_t)lane; w <= (p1 - 1) >> 2; w += 64) {
+        uint32_t x = reinterpret_cast<const uint32_t*>(gflag)[w] & 0x01010101u;
+        if (4 * w < p0) x &= 0xFFFFFFFFu << (8 * (p0 - 4 * w));
+        if (4 * w + 4 > p1) x &= 0xFFFFFFFFu >> (8 * (4 * w + 4 - p1));
+        nf += __popc(x);
+      }
+#pragma unroll
+      for (int s = 32; s > 0; s >>= 1) nf += __shfl_xor(nf, s, 64);
+      if (nf > kHeavyGeo && lane == o) {
+        is_heavy = true;
+        cnt = 0u;
+      }
+    }
     // the wave's pairs as one flat sequence: surfel l owns [pre_l, pre_l + cnt_l)
     uint32_t xs = cnt;
 #pragma unroll
@@ -1058,10 +1102,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     const uint32_t pre = xs - cnt, total = __shfl(xs, 63, 64);
     s_pre[wave][lane] = pre;
     s_vb[wave][lane] = vb;
-    wave_lds_sync();
-    double G[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) G[j] = 0.0;
+    for (int j = 0; j < 16; ++j) sums[j * kSS + lane] = 0.0;
+    wave_lds_sync();
     for (uint32_t t0 = 0; t0 < total; t0 += 64) {
       // 64 consecutive pairs of the sequence, one per lane; unflagged pairs
       // stage zeros (adding +0 leaves a sum unchanged)
@@ -1069,11 +1112,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       float4 r[4];
 #pragma unroll
       for (int qd = 0; qd < 4; ++qd) r[qd] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (t < total) {
-        int o = 0;  // owner: the last surfel whose range starts at or before t
+      int o = 0;  // owner: the last surfel whose range starts at or before t
 #pragma unroll
-        for (int step = 32; step > 0; step >>= 1)
-          if (s_pre[wave][o + step] <= t) o += step;
+      for (int step = 32; step > 0; step >>= 1)
+        if (s_pre[wave][o + step] <= min(t, total - 1)) o += step;
+      if (t < total) {
         const uint32_t pr = s_vb[wave][o] + (t - s_pre[wave][o]);
         if (gflag[pr]) {
           const float4* g = reinterpret_cast<const float4*>(gpart + (size_t)pr * 16);
@@ -1089,32 +1132,114 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         part[lane * kPS + 4 * qd + 3] = r[qd].w;
       }
       wave_lds_sync();
-      // each surfel adds its pairs of this batch in emission order
-      const uint32_t lo = max(pre, t0), hi = min(pre + cnt, t0 + 64u);
-      for (uint32_t u = lo; u < hi; ++u) {
-        const float* pp = part + (u - t0) * kPS;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) G[j] += pp[j];
+      // each surfel's pairs of this batch in emission order
+      const int s0 = __shfl(o, 0, 64), s1 = __shfl(o, 63, 64);
+      for (int s = s0 + ((grp - s0) & 3); s <= s1; s += 4) {
+        const uint32_t ps = s_pre[wave][s], pe = s < 63 ? s_pre[wave][s + 1] : total;
+        const uint32_t lo = max(ps, t0), hi = min(pe, t0 + 64u);
+        if (lo >= hi) continue;
+        double g = sums[comp * kSS + s];
+        for (uint32_t u = lo; u < hi; ++u) g += part[(u - t0) * kPS + comp];
+        sums[comp * kSS + s] = g;
       }
       wave_lds_sync();
     }
     if (live) {
-      Params P;
-      params(P);
+      double G[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) G[j] = sums[j * kSS + lane];
+      SurfelParams P;
+      load_params(P, ii, means, scales, quats);
       chain_rule(G, ct.cam[b], ((cv >> 8) & 1) != 0, P.mu, P.su, P.sv, P.qn, P.Rq, acc);
     }
+    wave_lds_sync();
   }
-  if (!valid) return;
-  Params P;
-  params(P);
-  // unit quaternion: project out the radial component
-  const double dot = P.qn[0] * acc.q[0] + P.qn[1] * acc.q[1] + P.qn[2] * acc.q[2] + P.qn[3] * acc.q[3];
-  for (int j = 0; j < 4; ++j) d_quats[4 * i + j] = (float)((acc.q[j] - P.qn[j] * dot) * P.rn);
-  for (int j = 0; j < 3; ++j) d_means[3 * i + j] = (float)acc.mu[j];
-  d_scales[2 * i] = (float)acc.su;
-  d_scales[2 * i + 1] = (float)acc.sv;
-  d_opacity[i] = (float)acc.o;
-  for (int j = 0; j < 3; ++j) d_rgb[3 * i + j] = (float)acc.rgb[j];
+  const uint64_t hm = __ballot(is_heavy);
+  if (lane == 0) heavy[i >> 6] = hm;
+  if (!valid || is_heavy) return;
+  SurfelParams P;
+  load_params(P, ii, means, scales, quats);
+  write_grad(acc, P, i, d);
+}
+
+// Heavy surfels (bits of `heavy`), a block each: per camera the flagged slots
+// are compacted in emission order (256 a step, block prefix count) into an LDS
+// list; row lane r of 16 adds, in FP64 and rank order, the rows whose rank
+// among the camera's flagged pairs is r mod 16 (lane = component), the 16
+// partials are added in row-lane order, and one thread applies the chain rule.
+// The partition depends only on the sequence of flagged pairs.
+__global__ __launch_bounds__(256) void k_reduce_geo_heavy(
+    int64_t n, CamTable ct, const uint32_t* __restrict__ vbase, const uint32_t* __restrict__ count, int64_t cap,
+    const float* __restrict__ gpart, const uint8_t* __restrict__ gflag, const float* __restrict__ means,
+    const float* __restrict__ scales, const float* __restrict__ quats, const int32_t* __restrict__ cull, GeoGrads d,
+    const uint64_t* __restrict__ heavy) {
+  constexpr int kList = 2048;
+  __shared__ uint32_t s_slot[kList];
+  __shared__ double s_row[16][16];
+  __shared__ uint64_t s_bits[256];
+  __shared__ uint32_t s_red[8];
+  const int t = threadIdx.x, comp = t & 15, rl = t >> 4;
+  const int64_t words = cdiv(n, 64);
+  // this block's words: blockIdx.x, + gridDim.x, ... (read 256 at a time)
+  for (int64_t w0 = blockIdx.x; w0 < words; w0 += 256 * (int64_t)gridDim.x) {
+    __syncthreads();
+    const int64_t wt = w0 + (int64_t)t * gridDim.x;
+    s_bits[t] = wt < words ? heavy[wt] : 0ull;
+    const int any = __syncthreads_or(s_bits[t] != 0ull);
+    if (!any) continue;
+    const int nq = (int)min((int64_t)256, cdiv(words - w0, gridDim.x));
+    for (int q = 0; q < nq; ++q) {
+      for (uint64_t m = s_bits[q]; m; m &= m - 1) {
+        const int64_t i = (w0 + (int64_t)q * gridDim.x) * 64 + __builtin_ctzll(m);
+        SurfelGrad acc;
+        clear_grad(acc);
+        SurfelParams P;
+        if (t == 0) load_params(P, i, means, scales, quats);
+        for (int b = 0; b < ct.n; ++b) {
+          const int64_t v = (int64_t)b * n + i;
+          const int32_t cv = cull[v];
+          if ((cv & 0xFF) != 0) continue;
+          const int64_t base = vbase[v], end = min(base + (int64_t)count[v], cap);
+          double sum = 0.0;
+          uint32_t nl = 0, rank0 = 0;  // listed slots, rank of the first (block-uniform)
+          auto drain = [&]() {
+            __syncthreads();
+            for (uint32_t j = (rl - rank0) & 15u; j < nl; j += 64) {
+              float x[4];
+#pragma unroll
+              for (int u = 0; u < 4; ++u) x[u] = j + 16 * u < nl ? gpart[(size_t)s_slot[j + 16 * u] * 16 + comp] : 0.0f;
+#pragma unroll
+              for (int u = 0; u < 4; ++u) sum += x[u];
+            }
+            rank0 += nl;
+            nl = 0;
+            __syncthreads();
+          };
+          for (int64_t c0 = base; c0 < end; c0 += 256) {
+            const bool f = c0 + t < end && gflag[c0 + t];
+            uint32_t total;
+            const uint32_t pre = block_scan_excl(f ? 1u : 0u, s_red, total);
+            if (f) s_slot[nl + pre] = (uint32_t)(c0 + t);  // nl <= kList - 256 here
+            nl += total;
+            if (nl > (uint32_t)(kList - 256)) drain();
+          }
+          drain();
+          s_row[rl][comp] = sum;
+          __syncthreads();
+          if (t == 0) {
+            double G[16];
+            for (int j = 0; j < 16; ++j) {
+              G[j] = s_row[0][j];
+              for (int r = 1; r < 16; ++r) G[j] += s_row[r][j];
+            }
+            chain_rule(G, ct.cam[b], ((cv >> 8) & 1) != 0, P.mu, P.su, P.sv, P.qn, P.Rq, acc);
+          }
+          __syncthreads();
+        }
+        if (t == 0) write_grad(acc, P, i, d);
+      }
+    }
+  }
 }
 
 // Lane group per surfel: dL/df = sum over cameras (in order) of the sum of its
@@ -1377,9 +1502,17 @@ static void backward_typed(const SurfelArgs& s, const CamTable& ct, int blend, c
   const uint32_t* vbase = (const uint32_t*)(ws + L.vbase);
   const uint32_t* count = (const uint32_t*)(ws + L.count);
   if (s.n > 0) {
+    const GeoGrads gg{gr.means, gr.scales, gr.quats, gr.opacity, gr.rgb};
+    uint64_t* hbits = (uint64_t*)(ws + L.ubits);  // a bit per surfel (the region holds one per virtual surfel)
     hipLaunchKernelGGL(k_reduce_geo, dim3((unsigned)cdiv(s.n, 256)), dim3(256), 0, st, s.n, ct, vbase, count, L.cap,
                        (const float*)(ws + L.gpart), (const uint8_t*)(ws + L.gflag), s.means, s.scales, s.quats,
-                       (const int32_t*)(ws + L.cull), gr.means, gr.scales, gr.quats, gr.opacity, gr.rgb);
+                       (const int32_t*)(ws + L.cull), gg, hbits);
+    if (L.cap > kHeavyGeo) {
+      const unsigned gh = (unsigned)std::min<int64_t>(cdiv(s.n, 64), 1024);
+      hipLaunchKernelGGL(k_reduce_geo_heavy, dim3(gh), dim3(256), 0, st, s.n, ct, vbase, count, L.cap,
+                         (const float*)(ws + L.gpart), (const uint8_t*)(ws + L.gflag), s.means, s.scales, s.quats,
+                         (const int32_t*)(ws + L.cull), gg, (const uint64_t*)hbits);
+    }
     if (s.c > 0 && (gr.feat || gr.feat_ext)) {
       // two channel groups per lane (at most 4 for C = 1024): more surfels,
       // and so more independent row loads, in flight per wave
