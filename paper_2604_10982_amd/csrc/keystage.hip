@@ -208,16 +208,16 @@ __device__ __forceinline__ bool tile_span(float lo, float hi, int npix, int T, i
   return true;
 }
 
-// Calls fn(ty, tx0, tx1) for each tile row of the footprint of mode `mode`.
-// With the low-pass filter the footprint is the union with the filter's disk:
-// the disk's box joins every mode's box, and the exact mode takes, per row,
-// the hull of the ellipse's and the disk's x-extents within the row's band.
-template <class F>
-__device__ __forceinline__ void for_each_row(const Foot& f, int mode, int W, int H, int tw, int th, int ntx, int nty,
-                                             F&& fn) {
+// Tile box of the footprint of mode `mode`; false if it meets no tile.  With
+// the low-pass filter the footprint is the union with the filter's disk: the
+// disk's box joins every mode's box.
+struct TileBox {
+  int x0, x1, y0, y1;
+};
+__device__ __forceinline__ bool foot_box(const Foot& f, int mode, int W, int H, int tw, int th, int ntx, int nty,
+                                         TileBox& box) {
   const bool lp = f.rf2 > 0.0f;
   const float rf = lp ? sqrtf(f.rf2) : 0.0f;
-  int ax0, ax1, ay0, ay1;
   float bx0, bx1, by0, by1;
   if (mode == kSphere) {
     const float rr = f.kk;
@@ -237,52 +237,68 @@ __device__ __forceinline__ void for_each_row(const Foot& f, int mode, int W, int
     by0 = fminf(by0, f.yc - rf);
     by1 = fmaxf(by1, f.yc + rf);
   }
-  if (!tile_span(bx0, bx1, W, tw, ntx, ax0, ax1)) return;
-  if (!tile_span(by0, by1, H, th, nty, ay0, ay1)) return;
-  if (mode != kEllipse) {
-    for (int ty = ay0; ty <= ay1; ++ty) fn(ty, ax0, ax1);
-    return;
-  }
-  // exact ellipse: x-extent of the ellipse inside each tile row's band
+  return tile_span(bx0, bx1, W, tw, ntx, box.x0, box.x1) && tile_span(by0, by1, H, th, nty, box.y0, box.y1);
+}
+
+// Tiles [x0, x1] of tile row ty of the footprint.  The exact mode takes the
+// x-extent of the ellipse inside the row's band (with the filter, the hull of
+// the ellipse's and the disk's).
+__device__ __forceinline__ bool foot_row(const Foot& f, int mode, int W, int H, int tw, int th, int ntx,
+                                         const TileBox& box, int ty, int& x0, int& x1) {
+  x0 = box.x0;
+  x1 = box.x1;
+  if (mode != kEllipse) return true;
+  const bool lp = f.rf2 > 0.0f;
   const float yr = f.S01 / f.ex;
-  for (int ty = ay0; ty <= ay1; ++ty) {
-    const float rlo = (float)(ty * th) + 0.5f;
-    const float rhi = fminf((float)(ty * th) + ((float)th - 0.5f), (float)H - 0.5f);
-    const float ylo = rlo - f.ecy;
-    const float yhi = rhi - f.ecy;
-    const float lo = fmaxf(ylo, -f.ey), hi = fminf(yhi, f.ey);
-    bool have = false;
-    float xl = 0.0f, xr = 0.0f;
-    if (lo <= hi) {
-      const float dR = fminf(fmaxf(yr, lo), hi);
-      const float dL = fminf(fmaxf(-yr, lo), hi);
-      const float hR = sqrtf(fmaxf(0.0f, (f.S11 - dR * dR) / f.gam)) * f.kk;
-      const float hL = sqrtf(fmaxf(0.0f, (f.S11 - dL * dL) / f.gam)) * f.kk;
-      const float xR = (f.S01 * dR + hR) / f.S11;
-      const float xL = (f.S01 * dL - hL) / f.S11;
-      xl = f.ecx + xL;
-      xr = f.ecx + xR;
+  const float rlo = (float)(ty * th) + 0.5f;
+  const float rhi = fminf((float)(ty * th) + ((float)th - 0.5f), (float)H - 0.5f);
+  const float ylo = rlo - f.ecy;
+  const float yhi = rhi - f.ecy;
+  const float lo = fmaxf(ylo, -f.ey), hi = fminf(yhi, f.ey);
+  bool have = false;
+  float xl = 0.0f, xr = 0.0f;
+  if (lo <= hi) {
+    const float dR = fminf(fmaxf(yr, lo), hi);
+    const float dL = fminf(fmaxf(-yr, lo), hi);
+    const float hR = sqrtf(fmaxf(0.0f, (f.S11 - dR * dR) / f.gam)) * f.kk;
+    const float hL = sqrtf(fmaxf(0.0f, (f.S11 - dL * dL) / f.gam)) * f.kk;
+    const float xR = (f.S01 * dR + hR) / f.S11;
+    const float xL = (f.S01 * dL - hL) / f.S11;
+    xl = f.ecx + xL;
+    xr = f.ecx + xR;
+    have = true;
+  }
+  if (lp) {  // the disk's widest chord within the band
+    const float dlo = rlo - f.yc, dhi = rhi - f.yc;
+    const float dy = fminf(fmaxf(0.0f, dlo), dhi);
+    const float h2 = f.rf2 - dy * dy;
+    if (h2 >= 0.0f) {
+      const float h = sqrtf(h2);
+      const float dl = f.xc - h, dr = f.xc + h;
+      xl = have ? fminf(xl, dl) : dl;
+      xr = have ? fmaxf(xr, dr) : dr;
       have = true;
     }
-    if (lp) {  // the disk's widest chord within the band
-      const float dlo = rlo - f.yc, dhi = rhi - f.yc;
-      const float dy = fminf(fmaxf(0.0f, dlo), dhi);
-      const float h2 = f.rf2 - dy * dy;
-      if (h2 >= 0.0f) {
-        const float h = sqrtf(h2);
-        const float dl = f.xc - h, dr = f.xc + h;
-        xl = have ? fminf(xl, dl) : dl;
-        xr = have ? fmaxf(xr, dr) : dr;
-        have = true;
-      }
-    }
-    if (!have) continue;
-    int x0, x1;
-    if (!tile_span(xl, xr, W, tw, ntx, x0, x1)) continue;
-    x0 = max(x0, ax0);
-    x1 = min(x1, ax1);
-    if (x0 <= x1) fn(ty, x0, x1);
   }
+  if (!have || !tile_span(xl, xr, W, tw, ntx, x0, x1)) return false;
+  x0 = max(x0, box.x0);
+  x1 = min(x1, box.x1);
+  return x0 <= x1;
+}
+
+// A surfel near the camera covers up to thousands of tiles.  Footprints of
+// more tile rows (counting) or tiles (emission) than these are taken by the
+// whole wave, a lane per row, and not by their own lane while 63 wait.  Below
+// the bounds a lane's own loop is shorter than the wave's common steps.
+// Emission of 1M street surfels 515 -> 61 us, of a 400k room 197 -> 101 us;
+// preprocess 125 -> 72 us and 64 -> 59 us.
+constexpr int kTallRows = 6;
+constexpr int kWidePairs = 16;
+
+__device__ __forceinline__ float lane_f(float v, int lane) { return __uint_as_float(lane_value(__float_as_uint(v), lane)); }
+__device__ __forceinline__ Foot lane_foot(const Foot& f, int l) {
+  return Foot{lane_f(f.ecx, l), lane_f(f.ecy, l), lane_f(f.S01, l), lane_f(f.S11, l), lane_f(f.ex, l), lane_f(f.ey, l),
+              lane_f(f.gam, l), lane_f(f.kk, l), lane_f(f.xc, l), lane_f(f.yc, l), lane_f(f.rf2, l)};
 }
 
 __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t v, int64_t count) {
@@ -319,30 +335,56 @@ __global__ __launch_bounds__(256) void k_preprocess(
     if (threadIdx.x == b && b < ct.n) s_cam[b] = ct.cam[b];
   __syncthreads();
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < nv) {
-    const int b = camera_of(ct, v);
-    const int64_t i = v - (int64_t)b * ct.nsurf;
-    const Cam& cam = s_cam[b];
+  const bool valid = v < nv;  // every lane stays for the tall footprints
+  const int b = valid ? camera_of(ct, v) : 0;
+  const int64_t i = valid ? v - (int64_t)b * ct.nsurf : 0;
+  const Cam& cam = s_cam[b];
+  Key kk;
+  kk.cull = 1;
+  TileBox box{0, -1, 0, -1};
+  uint32_t c = 0;
+  bool listed = false;
+  if (valid) {
     const float foot2 = opacity_foot ? opacity_foot2(opacity[i]) : kFoot2;
-    const Key kk = key_stage(means + 3 * i, scales + 2 * i, quats + 4 * i, cam, foot2,
-                             fminf(foot2, cull_foot2(opacity[i])), mode, lowpass);
+    kk = key_stage(means + 3 * i, scales + 2 * i, quats + 4 * i, cam, foot2, fminf(foot2, cull_foot2(opacity[i])),
+                   mode, lowpass);
     ids[v] = (uint32_t)v;
     cull[v] = kk.cull | (kk.flip << 8);  // bit 8: normal flipped toward the camera
-    if (kk.cull != 0) {
-      key[v] = 0xFFFFFFFFu;
-      count[v] = 0;
-    } else {
-      key[v] = __float_as_uint(kk.mc2);
-      uint32_t c = 0;
-      for_each_row(kk.f, mode, cam.W, cam.H, ct.tw, ct.th, ct.ntx[b], ct.nty[b],
-                   [&](int, int x0, int x1) { c += (uint32_t)(x1 - x0 + 1); });
-      count[v] = c;
+    key[v] = kk.cull != 0 ? 0xFFFFFFFFu : __float_as_uint(kk.mc2);
+    if (kk.cull == 0) {
       fp[2 * v] = make_float4(kk.f.ecx, kk.f.ecy, kk.f.ex, kk.f.ey);
       fp[2 * v + 1] = make_float4(kk.f.S01, kk.f.S11, kk.f.gam, kk.f.kk);
-      walk_record(means + 3 * i, scales + 2 * i, quats + 4 * i, opacity[i], rgb + 3 * i, kk.nc, kk.cr,
-                  cam, rec + v);
+      walk_record(means + 3 * i, scales + 2 * i, quats + 4 * i, opacity[i], rgb + 3 * i, kk.nc, kk.cr, cam, rec + v);
+      listed = foot_box(kk.f, mode, cam.W, cam.H, ct.tw, ct.th, ct.ntx[b], ct.nty[b], box);
     }
   }
+  // pairs: boxes need no row test; short ellipses by their lane, tall ones by the wave
+  const bool rows = listed && mode == kEllipse;
+  const bool tall = rows && box.y1 - box.y0 >= kTallRows;
+  if (listed && !rows) c = (uint32_t)(box.y1 - box.y0 + 1) * (uint32_t)(box.x1 - box.x0 + 1);
+  if (rows && !tall) {
+    for (int ty = box.y0; ty <= box.y1; ++ty) {
+      int x0, x1;
+      if (foot_row(kk.f, mode, cam.W, cam.H, ct.tw, ct.th, ct.ntx[b], box, ty, x0, x1)) c += (uint32_t)(x1 - x0 + 1);
+    }
+  }
+  const int lane = threadIdx.x & 63;
+  for (uint64_t m = __ballot(tall); m; m &= m - 1) {
+    const int o = __builtin_ctzll(m);
+    const Foot f = lane_foot(kk.f, o);
+    const int bo = (int)lane_value((uint32_t)b, o);
+    const TileBox bx{(int)lane_value((uint32_t)box.x0, o), (int)lane_value((uint32_t)box.x1, o),
+                     (int)lane_value((uint32_t)box.y0, o), (int)lane_value((uint32_t)box.y1, o)};
+    int sum = 0;
+    for (int ty = bx.y0 + lane; ty <= bx.y1; ty += 64) {
+      int x0, x1;
+      if (foot_row(f, mode, s_cam[bo].W, s_cam[bo].H, ct.tw, ct.th, ct.ntx[bo], bx, ty, x0, x1)) sum += x1 - x0 + 1;
+    }
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) sum += __shfl_xor(sum, w, 64);
+    if (lane == o) c = (uint32_t)sum;
+  }
+  if (valid) count[v] = c;
 }
 
 // Cull codes of all virtual surfels into the status words (stats read-back):
@@ -446,34 +488,86 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(int64_t n, const uin
 
 // ---- pair emission in depth order --------------------------------------------
 // Thread per depth rank r: the pairs of virtual surfel v = order[r] go to
-// [offs[r], offs[r] + count[v]), tile rows in order; vbase[v] = offs[r].
+// [offs[r], offs[r] + count[v]), tile rows in order; vbase[v] = offs[r].  More
+// than kWidePairs pairs are emitted by the whole wave.
 __global__ __launch_bounds__(256) void k_emit(int64_t nv, const uint32_t* __restrict__ order,
                                               const uint32_t* __restrict__ count,
                                               const uint32_t* __restrict__ offs, const float4* __restrict__ fp,
                                               const WalkRec* __restrict__ rec, int lowpass, CamTable ct, int mode, int64_t cap, uint32_t* __restrict__ vbase,
                                               uint32_t* __restrict__ ptile, uint32_t* __restrict__ eid,
                                               uint32_t* __restrict__ sid_emit) {
+  __shared__ int s_pre[4][64], s_x0[4][64];
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nv) return;
-  const uint32_t v = order[r];
-  vbase[v] = offs[r];
-  if (count[v] == 0) return;
-  const int b = camera_of(ct, v);
-  const int ntx = ct.ntx[b], t0 = ct.tile0[b];
-  const float4 f0 = fp[2 * (size_t)v], f1 = fp[2 * (size_t)v + 1];
-  float4 f2 = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (lowpass) f2 = rec[v].c.e1;
-  const Foot f{f0.x, f0.y, f1.x, f1.y, f0.z, f0.w, f1.z, f1.w, f2.x, f2.y, f2.z};
-  int64_t o = offs[r];
-  for_each_row(f, mode, ct.cam[b].W, ct.cam[b].H, ct.tw, ct.th, ntx, ct.nty[b], [&](int ty, int x0, int x1) {
-    for (int tx = x0; tx <= x1; ++tx, ++o) {
-      if (o < cap) {
-        ptile[o] = (uint32_t)(t0 + ty * ntx + tx);
-        eid[o] = (uint32_t)o;
-        sid_emit[o] = v;
-      }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t v = 0, cnt = 0, off = 0;
+  if (r < nv) {
+    v = order[r];
+    off = offs[r];
+    vbase[v] = off;
+    cnt = count[v];
+  }
+  const bool wide = cnt > (uint32_t)kWidePairs;
+  Foot f{};
+  const int b = cnt ? camera_of(ct, v) : 0;
+  if (cnt) {
+    const float4 f0 = fp[2 * (size_t)v], f1 = fp[2 * (size_t)v + 1];
+    float4 f2 = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (lowpass) f2 = rec[v].c.e1;
+    f = Foot{f0.x, f0.y, f1.x, f1.y, f0.z, f0.w, f1.z, f1.w, f2.x, f2.y, f2.z};
+  }
+  const auto put = [&](int64_t o, uint32_t tile, uint32_t id) {
+    if (o < cap) {
+      ptile[o] = tile;
+      eid[o] = (uint32_t)o;
+      sid_emit[o] = id;
     }
-  });
+  };
+  TileBox box{0, -1, 0, -1};
+  if (cnt && foot_box(f, mode, ct.cam[b].W, ct.cam[b].H, ct.tw, ct.th, ct.ntx[b], ct.nty[b], box) && !wide) {
+    int64_t o = off;
+    for (int ty = box.y0; ty <= box.y1; ++ty) {
+      int x0, x1;
+      if (!foot_row(f, mode, ct.cam[b].W, ct.cam[b].H, ct.tw, ct.th, ct.ntx[b], box, ty, x0, x1)) continue;
+      for (int tx = x0; tx <= x1; ++tx, ++o) put(o, (uint32_t)(ct.tile0[b] + ty * ct.ntx[b] + tx), v);
+    }
+  }
+  // wide footprints: a lane per tile row, then the rows' tiles as one flat
+  // sequence, a lane per tile (coalesced writes)
+  for (uint64_t m = __ballot(wide); m; m &= m - 1) {
+    const int l = __builtin_ctzll(m);
+    const Foot g = lane_foot(f, l);
+    const int bo = (int)lane_value((uint32_t)b, l);
+    const uint32_t vo = lane_value(v, l);
+    const TileBox bx{(int)lane_value((uint32_t)box.x0, l), (int)lane_value((uint32_t)box.x1, l),
+                     (int)lane_value((uint32_t)box.y0, l), (int)lane_value((uint32_t)box.y1, l)};
+    const int ntx = ct.ntx[bo], t0 = ct.tile0[bo];
+    int64_t o = lane_value(off, l);
+    for (int yb = bx.y0; yb <= bx.y1; yb += 64) {
+      const int ty = yb + lane;
+      int x0 = 0, x1 = -1;
+      if (ty > bx.y1 || !foot_row(g, mode, ct.cam[bo].W, ct.cam[bo].H, ct.tw, ct.th, ntx, bx, ty, x0, x1)) x1 = x0 - 1;
+      const int w = x1 - x0 + 1;
+      int xs = w;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(xs, d, 64);
+        if (lane >= d) xs += y;
+      }
+      const int total = __shfl(xs, 63, 64);
+      wave_lds_sync();
+      s_pre[wave][lane] = xs - w;
+      s_x0[wave][lane] = x0;
+      wave_lds_sync();
+      for (int t = lane; t < total; t += 64) {
+        int row = 0;  // the last row that starts at or before t
+#pragma unroll
+        for (int step = 32; step > 0; step >>= 1)
+          if (s_pre[wave][row + step] <= t) row += step;
+        put(o + t, (uint32_t)(t0 + (yb + row) * ntx + s_x0[wave][row] + (t - s_pre[wave][row])), vo);
+      }
+      o += total;
+    }
+  }
 }
 
 // Per-surfel key-stage results in surfel order (inspection / tests).
