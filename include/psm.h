@@ -105,7 +105,7 @@ typedef struct {
   int32_t bwd_schedule; /* psm_schedule of the backward's tile kernels */
   /* Tile shape: tile_w x (256 / tile_w) pixels, tile_w in {8, 16, 32, 64};
    * 0 = 16 (16 x 16 tiles, Sec. 5's tile-based rasterisation).  One 256-thread
-   * block owns one tile, a wave 64 / tile_w of its rows.  The pair lists
+   * block owns one tile, a wave 8 x 8 of its pixels (16 x 4 at 64).  The pair lists
    * follow the tiles; images and the Top-K selection do not depend on the
    * shape (gradients only through the order of their sums).  The read-backs
    * and the backward must use the forward's value. */
@@ -113,10 +113,9 @@ typedef struct {
 } psm_config;
 
 /* Tile scheduling of the per-tile kernels (forward: schedule, backward:
- * bwd_schedule).  GRID: one workgroup per tile, tiles of neighbouring
- * ids kept on one XCD.  PERSISTENT: a grid that fills the device once takes
- * tiles from a work queue ordered longest lists first (the forward orders the
- * tiles when either schedule is persistent). */
+ * bwd_schedule), one workgroup per tile.  GRID: tiles of neighbouring ids kept
+ * on one XCD.  PERSISTENT: the tiles of the longest lists first (the forward
+ * orders the tiles when either schedule is persistent). */
 typedef enum { PSM_SCHED_GRID = 0, PSM_SCHED_PERSISTENT = 1 } psm_schedule;
 
 /* Skip the end-of-call status read-back (graph-safe; the caller checks

@@ -328,29 +328,36 @@ void enqueue_forward(const SurfelArgs& sa, const CamTable& ct, const psm_config*
   const int64_t nb_max = cdiv(std::max<int64_t>(big, 1), kSortTile);
   uint32_t* status = (uint32_t*)(ws + L.status);
   uint32_t* hist = (uint32_t*)(ws + L.hist);
-  prof.begin(kStageFill, st);
-  launch_init_forward(L, ws, st);
-  prof.end(kStageFill, st);
-  prof.begin(kStagePreprocess, st);
   const bool lp = (cfg->flags & PSM_FLAG_LOWPASS) != 0;
+  const bool small_n = L.n <= kSingleSurfels, small_p = L.cap > 0 && L.cap <= kSinglePairs;
+  if (!small_n) {
+    prof.begin(kStageFill, st);
+    launch_init_forward(L, ws, st);
+    prof.end(kStageFill, st);
+  }
+  prof.begin(kStagePreprocess, st);
   launch_preprocess(sa, ct, cfg->tile_mode, (cfg->flags & PSM_FLAG_OPACITY_FOOTPRINT) != 0, lp, L, ws, st);
   prof.end(kStagePreprocess, st);
   prof.begin(kStageDepthSort, st);
-  radix_sort_pairs((uint32_t*)(ws + L.key0), (uint32_t*)(ws + L.id0), (uint32_t*)(ws + L.key1),
-                   (uint32_t*)(ws + L.id1), status + kStN, L.n, 32, hist, nb_max, st);
+  if (small_n) launch_single_depth(L, ws, st);
+  else
+    radix_sort_pairs((uint32_t*)(ws + L.key0), (uint32_t*)(ws + L.id0), (uint32_t*)(ws + L.key1),
+                     (uint32_t*)(ws + L.id1), status + kStN, L.n, 32, hist, nb_max, st);
   prof.end(kStageDepthSort, st);
   prof.begin(kStageScan, st);
-  launch_scan_counts(L, ws, st);
+  if (!small_n) launch_scan_counts(L, ws, st);
   prof.end(kStageScan, st);
   prof.begin(kStageEmit, st);
   launch_emit(ct, cfg->tile_mode, lp, L, ws, st);
   prof.end(kStageEmit, st);
   prof.begin(kStagePairSort, st);
-  radix_sort_pairs((uint32_t*)(ws + L.ptile0), (uint32_t*)(ws + L.eid0), (uint32_t*)(ws + L.ptile1),
-                   (uint32_t*)(ws + L.eid1), status + kStP, L.cap, bits_for(L.tiles), hist, nb_max, st);
+  if (small_p) launch_single_pairs(L, bits_for(L.tiles), ws, st);
+  else
+    radix_sort_pairs((uint32_t*)(ws + L.ptile0), (uint32_t*)(ws + L.eid0), (uint32_t*)(ws + L.ptile1),
+                     (uint32_t*)(ws + L.eid1), status + kStP, L.cap, bits_for(L.tiles), hist, nb_max, st);
   prof.end(kStagePairSort, st);
   prof.begin(kStageRanges, st);
-  launch_ranges(L, ws, st);
+  if (!small_p) launch_ranges(L, ws, st);
   if (tu.sched == kSchedPersistent || tu.sched_bwd == kSchedPersistent) launch_tile_order(L, ws, st);
   prof.end(kStageRanges, st);
   ImageArgs ia{out->rgb, out->depth, out->normal, out->alpha, out->feat};

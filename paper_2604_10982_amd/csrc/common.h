@@ -223,6 +223,26 @@ __host__ __device__ inline int stat_slots(const Layout& L) {
   return lines >= 256 ? 256 : (lines >= 64 ? 64 : 16);
 }
 
+// Initial value of status word i of a forward.
+__device__ inline uint32_t init_word(uint32_t i, uint32_t n, uint32_t tiles, uint64_t total, uint32_t cap) {
+  uint32_t v = 0u;
+  v = i == kStN ? n : v;
+  v = i == kStTiles ? tiles : v;
+  v = i == kStSigLo ? (uint32_t)total : v;
+  v = i == kStSigHi ? (uint32_t)(total >> 32) : v;
+  v = i == kStSigCap ? cap : v;
+  v = i == kStSigTiles ? tiles : v;
+  return v;
+}
+
+// The pairs the frame needs: required (64-bit), emitted, overflow.
+__device__ inline void write_pair_total(uint32_t* status, uint64_t total, uint64_t cap) {
+  status[kStReqLo] = (uint32_t)total;
+  status[kStReqHi] = (uint32_t)(total >> 32);
+  status[kStP] = (uint32_t)(total < cap ? total : cap);
+  status[kStOverflow] = total > cap ? 1u : 0u;
+}
+
 // ------------------------------------------------------------ walk record
 // Sub-tile culling of the walks: a wave skips a surfel no pixel centre of its
 // sub-tile can blend.  Per surfel the key stage keeps the ellipse of

@@ -81,6 +81,15 @@ void launch_export_keys(const Layout& L, char* ws, int32_t* cull, uint32_t* dept
 void radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, const uint32_t* n_dev,
                       int64_t cap_n, int bits, uint32_t* hist, int64_t nb_max, hipStream_t st);
 
+// One-block forms for small inputs: depth sort + count scan + status and
+// ranges; pair sort + ranges.  Chosen by what the host knows, the virtual
+// surfels and the pair capacity.  One block needs 7 to 25 us up to these
+// bounds, the launches it replaces 52 (depth) and 25 (pairs) us at any size.
+constexpr int64_t kSingleSurfels = 16384;  // fits LDS
+constexpr int64_t kSinglePairs = 32768;    // two chunks at most
+void launch_single_depth(const Layout& L, char* ws, hipStream_t st);
+void launch_single_pairs(const Layout& L, int bits, char* ws, hipStream_t st);
+
 // Tile order of a per-tile kernel (sorted by the forward).
 inline TileOrder tile_order(const Layout& L, int sched, const char* ws) {
   return TileOrder{sched == kSchedPersistent ? (const uint32_t*)(ws + L.torder0) : nullptr, (int)L.tiles};

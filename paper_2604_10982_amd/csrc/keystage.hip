@@ -311,14 +311,7 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t v, int64_t count) 
 __global__ __launch_bounds__(256) void k_init_forward(uint32_t* __restrict__ st, uint32_t n, uint32_t tiles,
                                                       uint64_t total, uint32_t cap, uint2* __restrict__ ranges) {
   const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-  uint32_t v = 0u;
-  v = i == kStN ? n : v;
-  v = i == kStTiles ? tiles : v;
-  v = i == kStSigLo ? (uint32_t)total : v;
-  v = i == kStSigHi ? (uint32_t)(total >> 32) : v;
-  v = i == kStSigCap ? cap : v;
-  v = i == kStSigTiles ? tiles : v;
-  if (i < kStWords) st[i] = v;
+  if (i < kStWords) st[i] = init_word(i, n, tiles, total, cap);
   if (i < tiles) ranges[i] = make_uint2(0u, 0u);
 }
 
@@ -447,11 +440,7 @@ __global__ __launch_bounds__(1024) void k_scan_top(int64_t nb, uint64_t* __restr
     run += v;
   }
   if (t == 1023) {
-    const uint64_t total = s[1023];
-    status[kStReqLo] = (uint32_t)total;
-    status[kStReqHi] = (uint32_t)(total >> 32);
-    status[kStP] = (uint32_t)(total < (uint64_t)cap ? total : (uint64_t)cap);
-    status[kStOverflow] = total > (uint64_t)cap ? 1u : 0u;
+    write_pair_total(status, s[1023], (uint64_t)cap);
   }
 }
 
