@@ -114,8 +114,8 @@ typedef struct {
 
 /* Tile scheduling of the per-tile kernels (forward: schedule, backward:
  * bwd_schedule), one workgroup per tile.  GRID: tiles of neighbouring ids kept
- * on one XCD.  PERSISTENT: the tiles of the longest lists first (the forward
- * orders the tiles when either schedule is persistent). */
+ * on one XCD, as long as all tiles fit on the device at once (1024); beyond,
+ * and with PERSISTENT always, the tiles of the longest lists first. */
 typedef enum { PSM_SCHED_GRID = 0, PSM_SCHED_PERSISTENT = 1 } psm_schedule;
 
 /* Skip the end-of-call status read-back (graph-safe; the caller checks

@@ -358,7 +358,7 @@ void enqueue_forward(const SurfelArgs& sa, const CamTable& ct, const psm_config*
   prof.end(kStagePairSort, st);
   prof.begin(kStageRanges, st);
   if (!small_p) launch_ranges(L, ws, st);
-  if (tu.sched == kSchedPersistent || tu.sched_bwd == kSchedPersistent) launch_tile_order(L, ws, st);
+  if (longest_first(L, tu.sched) || longest_first(L, tu.sched_bwd)) launch_tile_order(L, ws, st);
   prof.end(kStageRanges, st);
   ImageArgs ia{out->rgb, out->depth, out->normal, out->alpha, out->feat};
   prof.begin(kStageWalk, st);
@@ -790,8 +790,12 @@ psm_status psm_autotune(psm_ctx* ctx, const psm_surfels* s, const psm_camera* ca
     if (res == PSM_OK) {
       const Tuning base = best;
       best_ms = 1e300;
-      for (int sched = 0; sched < 2 && res == PSM_OK; ++sched)
-        for (int sched_bwd = 0; sched_bwd < 2 && res == PSM_OK; ++sched_bwd)
+      psm_config cs = *cfg;
+      cs.tile_w = best_tw;
+      const Layout Ls = make_layout(cam_table(cams, n_cams, s->n, &cs), cs.k, feat_channels(s), pair_capacity);
+      const int sched0 = longest_first(Ls, kSchedGrid) ? 1 : 0;  // beyond kOrderTiles both schedules are one
+      for (int sched = sched0; sched < 2 && res == PSM_OK; ++sched)
+        for (int sched_bwd = bwd ? sched0 : 0; sched_bwd < 2 && res == PSM_OK; ++sched_bwd)
           for (int bp : {16, 32})
             for (int gp : {16, 32}) {
               if (res != PSM_OK) break;

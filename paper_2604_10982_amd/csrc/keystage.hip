@@ -597,34 +597,71 @@ __global__ __launch_bounds__(256) void k_finalize_pairs(const uint32_t* __restri
   if (j == P - 1 || ptile[j + 1] != t) ranges[t].y = j + 1;
 }
 
-// Tile work order for the persistent scheduler, longest lists first: tiles
-// binned by the bit length of their list length (one block), the bins taken
-// in descending order.  The order within a bin does not matter: it only
-// decides which block starts a tile, never a result.
-__global__ __launch_bounds__(1024) void k_tile_order(int64_t tiles, const uint2* __restrict__ ranges,
+// Tile order, longest lists first: tiles binned by length (four bins per power
+// of two, one block, a set of counters per wave so that equal lengths meet in one
+// wave only), the bins taken in descending order.  The order within a bin does
+// not matter: it only decides when a tile starts, never a result.
+constexpr int kOrderBins = 132;
+__device__ __forceinline__ int length_bin(uint32_t len) {
+  if (len < 4) return (int)len;
+  const int e = 31 - __clz(len);
+  return 4 * (e - 1) + (int)((len >> (e - 2)) & 3u);
+}
+__global__ __launch_bounds__(1024) void k_tile_order(int tiles, const uint2* __restrict__ ranges,
                                                      uint32_t* __restrict__ order) {
-  __shared__ uint32_t s_cnt[33], s_off[33];
-  const int tid = threadIdx.x;
-  if (tid < 33) s_cnt[tid] = 0u;
+  __shared__ uint32_t s_off[16][kOrderBins + 1];
+  __shared__ uint32_t s_wave[16];
+  const int tid = threadIdx.x, wave = tid >> 6;
+  for (int i = tid; i < 16 * (kOrderBins + 1); i += 1024) (&s_off[0][0])[i] = 0u;
   __syncthreads();
-  for (int64_t t = tid; t < tiles; t += 1024) {
-    const uint2 r = ranges[t];
-    const uint32_t len = r.y - r.x;
-    atomicAdd(&s_cnt[len ? 32 - __clz(len) : 0], 1u);
-  }
-  __syncthreads();
-  if (tid == 0) {
-    uint32_t run = 0;
-    for (int bin = 32; bin >= 0; --bin) {
-      s_off[bin] = run;
-      run += s_cnt[bin];
+  constexpr int kItems = 8;  // lengths loaded together
+  for (int pass = 0; pass < 2; ++pass) {
+    for (int t0 = 0; t0 < tiles; t0 += 1024 * kItems) {
+      uint32_t len[kItems];
+#pragma unroll
+      for (int j = 0; j < kItems; ++j) {
+        const int t = t0 + j * 1024 + tid;
+        const uint2 r = t < tiles ? ranges[t] : make_uint2(0u, 0u);
+        len[j] = r.y - r.x;
+      }
+#pragma unroll
+      for (int j = 0; j < kItems; ++j) {
+        const int t = t0 + j * 1024 + tid;
+        if (t >= tiles) continue;
+        const uint32_t at = atomicAdd(&s_off[wave][length_bin(len[j])], 1u);
+        if (pass == 1) order[at] = (uint32_t)t;
+      }
     }
-  }
-  __syncthreads();
-  for (int64_t t = tid; t < tiles; t += 1024) {
-    const uint2 r = ranges[t];
-    const uint32_t len = r.y - r.x;
-    order[atomicAdd(&s_off[len ? 32 - __clz(len) : 0], 1u)] = (uint32_t)t;
+    __syncthreads();
+    if (pass == 1) break;
+    // bins descending, then waves: first position of each (wave, bin); thread
+    // t has bin kOrderBins - 1 - t
+    const int bin = kOrderBins - 1 - tid;
+    uint32_t c[16], tot = 0;
+    if (bin >= 0) {
+#pragma unroll
+      for (int w = 0; w < 16; ++w) c[w] = s_off[w][bin];
+#pragma unroll
+      for (int w = 0; w < 16; ++w) tot += c[w];
+    }
+    uint32_t x = tot;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o, 64);
+      if ((tid & 63) >= o) x += y;
+    }
+    if ((tid & 63) == 63) s_wave[wave] = x;
+    __syncthreads();
+    if (bin >= 0) {
+      uint32_t run = x - tot;
+      for (int w = 0; w < wave; ++w) run += s_wave[w];
+#pragma unroll
+      for (int w = 0; w < 16; ++w) {
+        s_off[w][bin] = run;
+        run += c[w];
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -702,7 +739,7 @@ void launch_ranges(const Layout& L, char* ws, hipStream_t st) {
 
 void launch_tile_order(const Layout& L, char* ws, hipStream_t st) {
   if (L.tiles == 0) return;
-  hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(1024), 0, st, L.tiles, (const uint2*)(ws + L.ranges),
+  hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(1024), 0, st, (int)L.tiles, (const uint2*)(ws + L.ranges),
                      (uint32_t*)(ws + L.torder0));
 }
 
