@@ -94,7 +94,7 @@ void launch_single_pairs(const Layout& L, int bits, char* ws, hipStream_t st);
 // always beyond kOrderTiles, where they are not all resident at once (256 CUs
 // x 4 blocks) and the long ones, met late, end the kernel: 1M street surfels at
 // 1080p, XCD order against longest first: walk 644 / 413 us, backward walk
-// 1544 / 847 us, feature adjoint 1808 / 1712 us; the ordering itself 8 us.
+// 1544 / 847 us, feature adjoint 1808 / 1712 us; the ordering itself 12 us.
 constexpr int64_t kOrderTiles = 1024;
 inline bool longest_first(const Layout& L, int sched) { return sched == kSchedPersistent || L.tiles > kOrderTiles; }
 
