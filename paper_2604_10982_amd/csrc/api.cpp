@@ -801,8 +801,7 @@ psm_status psm_autotune(psm_ctx* ctx, const psm_surfels* s, const psm_camera* ca
               if (res != PSM_OK) break;
               if (!bwd && sched_bwd != 0) continue;
               if (!feat && bp != 32) continue;
-              if (!feat && !dense_bwd && gp != 16) continue;
-              if (feat && !bwd && gp != 16) continue;
+              if (!dense_bwd && gp != 16) continue;
               const Tuning tu{sched, sched_bwd, bp, gp};
               double med = 0.0;
               bool usable = false;

@@ -33,65 +33,95 @@ constexpr int kBB = 32;          // surfels per backward batch
 // ------------------------------------------------------------ Top-K feature
 // Per tile, the distinct selected surfels of the tile (a few dozen: each is
 // chosen by about a hundred of the 256 pixels for K = 16) get slots in list
-// order, 64 per chunk.  With G = the pixels' feature gradients (256 x C),
+// order, 48 per chunk.  With G = the pixels' feature gradients (256 x C),
 // F = the slots' feature rows and W = the selection weights (pixel x slot,
 // zero where the pixel did not select the slot), the adjoint needs
 //   dots = G F^T  at the selected (pixel, slot) entries   (alpha adjoint)
 //   rows = W^T G                                           (feature gradient)
 // and the weight matrix of a tile is dense enough (about half its entries)
-// that both run as dense FP32 matrix-core products.  Wave w owns pixels
-// [64 w, 64 w + 64): its dots tiles, and its share of the rows (a sum over
-// its pixels), added across the 4 waves in wave order.  The number of
-// 16-slot blocks of a chunk is a compile-time parameter of the product
-// loops (one instantiation per count), so they carry no branches.  Per pass
-// of GC channels G and F are staged in LDS; every layout below keeps the
-// operand reads free of bank conflicts (see the strides).  Every sum has a
-// fixed order: results do not depend on the pass width or the tile
-// schedule.
-constexpr int kFbSlots = 64;   // slots per chunk: 4 blocks of 16
-constexpr int kQStride = 72;   // bytes per pixel row of the selection map
+// that both run as dense FP32 matrix-core products.
+//
+// Eight waves, 32 pixels each: a wave's dots and weight operands then take 48
+// registers for 48 slots, and four waves fit on a SIMD (with four waves of 64
+// pixels and 64 slots it was two, and half of the time no wave had an
+// instruction ready; 64 slots for eight waves spill inside the passes: 945
+// against 832 us, and 32 slots read G more often).
+// Both operands of the dots come straight from memory, 4 channels a lane, and
+// are put in step order by lane swaps; G goes through the wave's own LDS slab only to be read with pixels
+// along the contraction.  So a pass of 16 channels has one block barrier,
+// before the sum of the waves' partial rows (in wave order; two buffers).  Weights and dots
+// cross between a pixel's selections and the matrix layout through the same
+// slab, 16 slots at a time.  Every sum has a fixed order.
+// 1080p, K = 16: 1M plane surfels, C = 128: 1065 -> 826 us; 1M street surfels,
+// C = 256 (bf16): 1680 -> 1293 us.  Of the 826: 330 the slots and operands of
+// the tiles with one pass, the matrix products about 300, waiting for G 80.
+constexpr int kFbSlots = 48;                  // slots per chunk: 3 blocks of 16
+constexpr int kFbThreads = 512;
+constexpr int kFbWaves = kFbThreads / 64;
+constexpr int kFbPix = kTilePix / kFbWaves;   // pixels per wave
+constexpr int kFbPass = 16;                   // channels per pass
+constexpr int kFbPart = kFbWaves * kFbSlots * kFbPass;  // partial rows of a pass
+// Slab strides in floats: rows of G 4 apart are 16 banks apart (one step's
+// four pixels); a slot's 32 pixels at 37, so that 16 slots spread over the banks.
+constexpr int kFbGS = 20, kFbWS = 37;
+static_assert(kFbPix == 32 && 16 * kFbWS + kFbPix <= kFbPix * kFbGS, "slab");
 
-// Selection map: the byte of (pixel p, slot s) holds the index q of the
-// pixel's selection of s (0xFF = none); the 4 slots s = li + 16 sb share one
-// dword, so a lane reads its 4 slot blocks at once.
-__device__ __forceinline__ int qmap_off(int p, int s) { return p * kQStride + (s & 15) * 4 + (s >> 4); }
+// Keeps what is derived from v from being formed before this point (and held
+// in registers through the products).
+__device__ __forceinline__ uint32_t formed_here(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
 
-template <typename FT, int KMAX, int GC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 16 ? 2 : 1))) void k_feat_bwd_topk(
+// Four lane groups hold four channels each (group k: channels 4 k ..); after
+// this, component s of every group k is channel 4 s + k: the order in which
+// the dots are summed (their rounding is amplified by the geometric chain of
+// surfels seen edge-on, so it stays the order of channels).
+__device__ __forceinline__ float4 by_step(float4 v) {
+  const auto u = [](float x) { return __float_as_uint(x); };
+  const auto a = __builtin_amdgcn_permlane32_swap(u(v.x), u(v.z), false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(u(v.y), u(v.w), false, false);
+  const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+  const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  return make_float4(__uint_as_float(c[0]), __uint_as_float(c[1]), __uint_as_float(d[0]), __uint_as_float(d[1]));
+}
+
+// SPLIT: features in two arrays.
+template <typename FT, int KMAX, bool SPLIT>
+__global__ __launch_bounds__(kFbThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_feat_bwd_topk(
     const uint32_t* __restrict__ pid, const uint32_t* __restrict__ eid, const uint2* __restrict__ ranges,
     const int32_t* __restrict__ selpos, const float* __restrict__ selw, const FeatSrc<FT> feat,
     const float* __restrict__ gfeat, int C, int K, CamTable ct, TileOrder tq, float* __restrict__ seldot,
     float* __restrict__ fpart, uint8_t* __restrict__ fflag, int renorm) {
-  static_assert(GC % 16 == 0, "pass width is a multiple of the MFMA tile");
-  // Row stride of the staged G and F: = 2 mod 4, so a 16-row x 2-column read
-  // (lanes 0-31 of an operand fetch) touches 32 distinct banks, and 8 rows
-  // apart is 16 banks apart.
-  constexpr int GS = GC + 2;
-  constexpr int NCB = GC / 16;              // channel blocks per pass
-  constexpr int FPT = kFbSlots * GC / 256;  // staged F values per thread
+  constexpr int QH = KMAX / 2;  // selections per lane: a pixel's are shared by lanes l and l + 32
   __shared__ SelShared S;
-  __shared__ __align__(16) float s_G[kTilePix * GS];  // G rows of the pass; then the waves' partial rows
-  __shared__ float s_F[kFbSlots * GS];
-  __shared__ __align__(16) uint8_t s_q[kTilePix * kQStride];
+  __shared__ __align__(16) float s_slab[kFbWaves][kFbPix * kFbGS];
   __shared__ uint32_t s_fe[kFbSlots];  // emitted pair index per slot
-  extern __shared__ float s_w[];       // selection weights, replaced by dots
+  extern __shared__ float s_part[];    // the waves' partial rows of a pass, two passes
 
   with_tile(tq, [&](const int tile) {
   const TileLoc tl = locate(ct, tile);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  const int px = tl.tx * ct.tw + tile_lx(ct, tid), py = tl.ty * ct.th + tile_ly(ct, tid);
-  const bool inside = px < tl.W && py < tl.H;
+  const int li = lane & 15, lk = lane >> 4, pl = lane & 31;
   const uint32_t start = ranges[tile].x;
+  const int q0 = (lane >> 5) * QH;
+  // the tile's selections: uniform bases, this lane's first at sel0
   const size_t tbase = (size_t)tile * K * kTilePix;
-  const float* grow = gfeat + (tl.pix0 + (int64_t)py * tl.W + px) * C;
-  const int p0 = wave * 64;  // first pixel of this wave
+  const int32_t* const spos = selpos + tbase;
+  const float* const sw = selw + tbase;
+  float* const sdot = seldot + tbase;
+  const uint32_t sel0 = (uint32_t)(q0 * kTilePix + wave * kFbPix + pl);
+  float* const slab = s_slab[wave];
 
   // the selection positions are re-read where needed (an L2 hit) rather
   // than held in registers through the products
-  auto load_pos = [&](int (&pos)[KMAX]) {
+  // in range also for q0 + j >= K
+  auto sel_at = [&](int j) { return formed_here(sel0) + (uint32_t)(min(j, K - 1 - q0) * kTilePix); };
+  auto load_pos = [&](int (&pos)[QH]) {
 #pragma unroll
-    for (int q = 0; q < KMAX; ++q) pos[q] = q < K ? selpos[tbase + (size_t)q * kTilePix + tid] : -1;
+    for (int j = 0; j < QH; ++j) pos[j] = spos[sel_at(j)];
+#pragma unroll
+    for (int j = 0; j < QH; ++j) pos[j] = q0 + j < K ? pos[j] : -1;
   };
   // list positions are below the tile's list length, which bounds the
   // windows (no block-wide maximum of the selections needed)
@@ -99,42 +129,53 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 16 
   int Uw0 = 0;
   float rw = 1.0f;  // renormalised Top-K: 1 / (sum of the pixel's selected weights)
   {
-    int pos[KMAX];
+    int pos[QH];
     load_pos(pos);
-    float wsum = 0.0f;
 #pragma unroll
-    for (int q = 0; q < KMAX; ++q) {  // unselected entries keep weight 0 and report dot 0
-      const float wq = q < K && pos[q] >= 0 ? selw[tbase + (size_t)q * kTilePix + tid] : 0.0f;
-      if (q < K) s_w[wsel_off(q, tid)] = wq;
-      wsum += wq;
+    for (int j = 0; j < QH; ++j)  // unselected entries report dot 0
+      if (q0 + j < K && pos[j] < 0) sdot[sel0 + j * kTilePix] = 0.0f;
+    if (renorm) {
+      float wsum = 0.0f;
+#pragma unroll
+      for (int j = 0; j < QH; ++j) {
+        const float x = sw[sel_at(j)];
+        wsum += pos[j] >= 0 ? x : 0.0f;
+      }
+      wsum += __shfl_xor(wsum, 32, 64);
+      rw = wsum > 0.0f ? 1.0f / wsum : 0.0f;
     }
-    if (renorm) rw = wsum > 0.0f ? 1.0f / wsum : 0.0f;
-    if (lastpos >= 0) Uw0 = build_window(S, pos, K, 0, window_words(lastpos, 0));
+    if (lastpos >= 0) Uw0 = build_window<QH, kFbThreads>(S, pos, QH, 0, window_words(lastpos, 0));
   }
-
+  // the two pixels whose gradients this lane loads
+  uint32_t gpix[2];  // ~0: outside the image
+#pragma unroll
+  for (int pb = 0; pb < 2; ++pb) {
+    const int p = wave * kFbPix + 16 * pb + li;
+    const int px = tl.tx * ct.tw + tile_lx(ct, p), py = tl.ty * ct.th + tile_ly(ct, p);
+    gpix[pb] = px < tl.W && py < tl.H ? (uint32_t)(tl.pix0 + (int64_t)py * tl.W + px) : ~0u;
+  }
   for (int w0 = 0; w0 <= lastpos; w0 += kWinPos) {
     const int nw = window_words(lastpos, w0);
     int Uw = Uw0;
     if (w0 > 0) {
-      int pos[KMAX];
+      int pos[QH];
       load_pos(pos);
-      Uw = build_window(S, pos, K, w0, nw);
+      Uw = build_window<QH, kFbThreads>(S, pos, QH, w0, nw);
     }
     for (int c0 = 0; c0 < Uw; c0 += kFbSlots) {
       const int ns = min(kFbSlots, Uw - c0), nb = (ns + 15) >> 4;
-      for (int i = tid; i < kTilePix * kQStride / 16; i += 256)
-        reinterpret_cast<uint4*>(s_q)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
-      __syncthreads();
+      uint32_t sl[QH / 4];  // slot of each selection, a byte each: 255 = not in this chunk
+#pragma unroll
+      for (int j = 0; j < QH / 4; ++j) sl[j] = 0u;
       {
-        int pos[KMAX];
+        int pos[QH];
         load_pos(pos);
 #pragma unroll
-        for (int q = 0; q < KMAX; ++q) {
-          const int sl = q < K ? slot_of(S, pos[q], w0, nw) - c0 : -1;
-          if (sl >= 0 && sl < ns) {
-            s_q[qmap_off(tid, sl)] = (uint8_t)q;
-            S.lpos[sl] = (uint32_t)pos[q];  // same value from every selecting pixel
-          }
+        for (int j = 0; j < QH; ++j) {
+          const int x = slot_of(S, pos[j], w0, nw) - c0;
+          const bool in = x >= 0 && x < ns;
+          sl[j / 4] |= (in ? (uint32_t)x : 255u) << (8 * (j % 4));
+          if (in) S.lpos[x] = (uint32_t)pos[j];  // same value from every selecting pixel
         }
       }
       __syncthreads();
@@ -147,148 +188,167 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 16 
 
       auto chunk = [&](auto nb_c) {
         constexpr int NB = decltype(nb_c)::value;
-        f4v dacc[4][NB];
+        // operands of a pass: 4 channels of the lane's two pixels and of its
+        // slot of each block (slots past the last read a valid row: their
+        // column of the dots is not used, their weights are 0)
+        uint32_t fr[NB];
 #pragma unroll
-        for (int pb = 0; pb < 4; ++pb)
+        for (int sb = 0; sb < NB; ++sb) fr[sb] = S.fid[min(16 * sb + li, ns - 1)];
+        float4 g[2], f[NB];
+        auto load_g = [&](int cc) {
+          const int c = cc + 4 * lk;
 #pragma unroll
-          for (int sb = 0; sb < NB; ++sb) dacc[pb][sb] = f4v{0.f, 0.f, 0.f, 0.f};
-        // rows A operand for the whole chunk: W[p][s] at lane (s, p) of step
-        // ks, whose 4 pixels are base + 8 k (k = lane group)
-        float wa[NB][16];
-#pragma unroll
-        for (int ks = 0; ks < 16; ++ks) {
-          const int p = p0 + (ks & 7) + 32 * (ks >> 3) + 8 * lk;
-          const uint32_t qd = *reinterpret_cast<const uint32_t*>(s_q + p * kQStride + 4 * li);
-#pragma unroll
-          for (int sb = 0; sb < NB; ++sb) {
-            const int q = (int)((qd >> (8 * sb)) & 0xFFu);
-            const float x = s_w[wsel_off(min(q, K - 1), p)];  // always in range
-            wa[sb][ks] = q != 0xFF ? x : 0.0f;
-          }
-        }
-        float gv[GC], fv[FPT];
-        auto load_pass = [&](int cc) {
-#pragma unroll
-          for (int j = 0; j < GC / 4; ++j) {
-            const int c = cc + 4 * j;
-            const float4 g =
-                inside && c < C ? *reinterpret_cast<const float4*>(grow + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-            // renormalised Top-K: the rows and dots see g / W (rw = 1 otherwise)
-            gv[4 * j] = g.x * rw;
-            gv[4 * j + 1] = g.y * rw;
-            gv[4 * j + 2] = g.z * rw;
-            gv[4 * j + 3] = g.w * rw;
-          }
-#pragma unroll
-          for (int u = 0; u < FPT; ++u) {
-            const int item = tid + 256 * u, sidx = item / GC, c = cc + item % GC;
-            fv[u] = sidx < ns && c < C ? feat.load1(S.fid[sidx], c) : 0.0f;
+          for (int pb = 0; pb < 2; ++pb) {
+            const uint32_t pix = formed_here(gpix[pb]);
+            g[pb] = c < C && pix != ~0u ? *reinterpret_cast<const float4*>(gfeat + (size_t)pix * C + c)
+                                        : make_float4(0.f, 0.f, 0.f, 0.f);
           }
         };
-        load_pass(0);
-        for (int cc = 0; cc < C; cc += GC) {
-#pragma unroll
-          for (int c = 0; c < GC; c += 2)
-            *reinterpret_cast<float2*>(s_G + tid * GS + c) = make_float2(gv[c], gv[c + 1]);
-#pragma unroll
-          for (int u = 0; u < FPT; ++u) {
-            const int item = tid + 256 * u;
-            s_F[(item / GC) * GS + item % GC] = fv[u];
-          }
-          __syncthreads();
-          if (cc + GC < C) load_pass(cc + GC);
-          // dots: D[p][s] += G[p][c] F[s][c], 4 channels per step
-#pragma unroll 2
-          for (int ks = 0; ks < GC / 4; ++ks) {
-            float fb[NB], ga[4];
-#pragma unroll
-            for (int sb = 0; sb < NB; ++sb) fb[sb] = s_F[(16 * sb + li) * GS + 4 * ks + lk];
-#pragma unroll
-            for (int pb = 0; pb < 4; ++pb) ga[pb] = s_G[(p0 + 16 * pb + li) * GS + 4 * ks + lk];
-#pragma unroll
-            for (int pb = 0; pb < 4; ++pb)
-#pragma unroll
-              for (int sb = 0; sb < NB; ++sb) dacc[pb][sb] = mfma_16x16x4(ga[pb], fb[sb], dacc[pb][sb]);
-          }
-          // rows: R[s][c] += W[p][s] G[p][c] over this wave's pixels; step ks
-          // takes the 4 pixels base + 8 k (k = lane group)
-          f4v racc[NB][NCB];
+        auto load_f = [&](int cc) {
+          const int c = cc + 4 * lk;
 #pragma unroll
           for (int sb = 0; sb < NB; ++sb)
+            f[sb] = c >= C ? make_float4(0.f, 0.f, 0.f, 0.f)
+                    : SPLIT ? feat.load4(formed_here(fr[sb]), c)
+                            : load4<FT>(feat.a + (size_t)formed_here(fr[sb]) * C + c);
+        };
+        load_g(0);
+        load_f(0);
+        // weights: W[p][s] at lane (s = li, lk) of step ks, pixel of the step
+        // and lane group (ks & 3) + 4 lk + 16 (ks >> 2)
+        float wa[NB][8];
+        {
+          float wq[QH];
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) racc[sb][cb] = f4v{0.f, 0.f, 0.f, 0.f};
+          for (int j = 0; j < QH; ++j)
+            wq[j] = sw[sel_at(j)];
 #pragma unroll
-          for (int ks = 0; ks < 16; ++ks) {
-            const int p = p0 + (ks & 7) + 32 * (ks >> 3) + 8 * lk;
-            float gb[NCB];
+          for (int sb = 0; sb < NB; ++sb) {
+            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+            reinterpret_cast<float4*>(slab)[lane] = z;
+            reinterpret_cast<float4*>(slab)[64 + lane] = z;
+            if (lane < 32) reinterpret_cast<float4*>(slab)[128 + lane] = z;
+            wave_lds_sync();
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) gb[cb] = s_G[p * GS + 16 * cb + li];
+            for (int j = 0; j < QH; ++j) {
+              const uint32_t x = (sl[j / 4] >> (8 * (j % 4))) & 255u;
+              slab[((x >> 4) == sb ? x & 15u : 16u) * kFbWS + pl] = wq[j];  // row 16: not read
+            }
+            wave_lds_sync();
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-              for (int sb = 0; sb < NB; ++sb) racc[sb][cb] = mfma_16x16x4(wa[sb][ks], gb[cb], racc[sb][cb]);
+            for (int ks = 0; ks < 8; ++ks) wa[sb][ks] = slab[li * kFbWS + (ks & 3) + 4 * lk + 16 * (ks >> 2)];
+            wave_lds_sync();
           }
-          __syncthreads();  // every wave is done with the staged G
-          // partial row of slot s of wave w at row 64 w + perm(s), perm
-          // swapping bits 2 and 3 of s (lanes 0-31 then write 16 banks apart)
-#pragma unroll
-          for (int sb = 0; sb < NB; ++sb)
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-              for (int r = 0; r < 4; ++r)
-                s_G[(p0 + 16 * sb + 8 * (lk & 1) + 4 * (lk >> 1) + r) * GS + 16 * cb + li] = racc[sb][cb][r];
-          __syncthreads();
-          for (int item = tid; item < ns * GC; item += 256) {
-            const int sidx = item / GC, c = item % GC;
-            const int row = (sidx & ~12) | ((sidx & 4) << 1) | ((sidx & 8) >> 1);
-            const float* r = s_G + row * GS + c;
-            const float v = ((r[0] + r[64 * GS]) + r[128 * GS]) + r[192 * GS];
-            if (cc + c < C) fpart[(size_t)s_fe[sidx] * C + cc + c] = v;
-          }
-          __syncthreads();
         }
-        // dots of the selected entries replace their (already consumed) weights
+        f4v dacc[2][NB];
 #pragma unroll
-        for (int pb = 0; pb < 4; ++pb)
+        for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int p = p0 + 16 * pb + 4 * lk + r;
-            const uint32_t qd = *reinterpret_cast<const uint32_t*>(s_q + p * kQStride + 4 * li);
+          for (int sb = 0; sb < NB; ++sb) dacc[pb][sb] = f4v{0.f, 0.f, 0.f, 0.f};
+        for (int cc = 0; cc < C; cc += kFbPass) {
+          float* const part = s_part + (cc / kFbPass & 1) * kFbPart;
 #pragma unroll
-            for (int sb = 0; sb < NB; ++sb) {
-              const int q = (int)((qd >> (8 * sb)) & 0xFFu);
-              if (q != 0xFF) s_w[wsel_off(q, p)] = dacc[pb][sb][r];
+          for (int pb = 0; pb < 2; ++pb) {
+            if (renorm) {  // the rows and dots see g / W
+              const float r = __shfl(rw, 16 * pb + li, 64);
+              g[pb] = make_float4(g[pb].x * r, g[pb].y * r, g[pb].z * r, g[pb].w * r);
+            }
+            *reinterpret_cast<float4*>(slab + (16 * pb + li) * kFbGS + 4 * lk) = g[pb];
+          }
+          wave_lds_sync();
+          float gb[8];
+#pragma unroll
+          for (int ks = 0; ks < 8; ++ks) gb[ks] = slab[((ks & 3) + 4 * lk + 16 * (ks >> 2)) * kFbGS + li];
+          // dots: D[p][s] += G[p][c] F[s][c], 4 channels per step
+#pragma unroll
+          for (int pb = 0; pb < 2; ++pb) g[pb] = by_step(g[pb]);
+#pragma unroll
+          for (int sb = 0; sb < NB; ++sb) f[sb] = by_step(f[sb]);
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int sb = 0; sb < NB; ++sb)
+#pragma unroll
+              for (int pb = 0; pb < 2; ++pb)
+                dacc[pb][sb] = mfma_16x16x4((&g[pb].x)[ks], (&f[sb].x)[ks], dacc[pb][sb]);
+          if (cc + kFbPass < C) load_g(cc + kFbPass);
+          // rows: R[s][c] += W[p][s] G[p][c] over this wave's pixels
+#pragma unroll
+          for (int sb = 0; sb < NB; ++sb) {
+            f4v r = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) r = mfma_16x16x4(wa[sb][ks], gb[ks], r);
+            // slot 16 sb + 4 lk + i at row 16 sb + 4 i + lk: the lane groups 16 banks apart
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[(wave * kFbSlots + 16 * sb + 4 * i + lk) * kFbPass + li] = r[i];
+          }
+          if (cc + kFbPass < C) load_f(cc + kFbPass);
+          __syncthreads();
+          {
+            const int s = tid >> 3, c = 2 * (tid & 7);
+            if (s < ns && cc + c < C) {
+              const float* r = part + ((s & ~15) + 4 * (s & 3) + ((s >> 2) & 3)) * kFbPass + c;
+              float2 v = *reinterpret_cast<const float2*>(r);
+#pragma unroll
+              for (int w = 1; w < kFbWaves; ++w) {
+                const float2 x = *reinterpret_cast<const float2*>(r + w * kFbSlots * kFbPass);
+                v.x += x.x;
+                v.y += x.y;
+              }
+              *reinterpret_cast<float2*>(fpart + (size_t)s_fe[s] * C + cc + c) = v;
             }
           }
+        }
+        // dots of the selected entries, 16 slots at a time
+        uint32_t sd[QH / 4];
+#pragma unroll
+        for (int j = 0; j < QH / 4; ++j) sd[j] = formed_here(sl[j]);
+        float dq[QH] = {};
+#pragma unroll
+        for (int sb = 0; sb < NB; ++sb) {
+          wave_lds_sync();
+#pragma unroll
+          for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) slab[li * kFbWS + 16 * pb + 4 * lk + r] = dacc[pb][sb][r];
+          wave_lds_sync();
+#pragma unroll
+          for (int j = 0; j < QH; ++j) {
+            const uint32_t x = (sd[j / 4] >> (8 * (j % 4))) & 255u;
+            const float d = slab[(x & 15u) * kFbWS + pl];
+            dq[j] = (x >> 4) == sb ? d : dq[j];
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < QH; ++j)
+          if (((sd[j / 4] >> (8 * (j % 4))) & 255u) != 255u) sdot[sel_at(j)] = dq[j];
+        wave_lds_sync();
       };
       switch (nb) {
         case 1: chunk(std::integral_constant<int, 1>{}); break;
         case 2: chunk(std::integral_constant<int, 2>{}); break;
-        case 3: chunk(std::integral_constant<int, 3>{}); break;
-        default: chunk(std::integral_constant<int, 4>{}); break;
+        default: chunk(std::integral_constant<int, 3>{}); break;
       }
       if (tid < ns) fflag[s_fe[tid]] = 1;
       __syncthreads();
     }
   }
-  __syncthreads();
   // renormalised Top-K: d/dw_q of F = sum w f / W is g.(f_q - F) / W, i.e.
   // dot'_q - sum_j (w_j / W) dot'_j with dot' = (g / W) . f
-  float cshift = 0.0f;
   if (renorm) {
+    float cshift = 0.0f;
 #pragma unroll
-    for (int q = 0; q < KMAX; ++q)
-      if (q < K) {
-        const float wq = selpos[tbase + (size_t)q * kTilePix + tid] >= 0 ? selw[tbase + (size_t)q * kTilePix + tid] : 0.0f;
-        cshift = fmaf(wq, s_w[wsel_off(q, tid)], cshift);
+    for (int j = 0; j < QH; ++j)
+      if (q0 + j < K) {
+        const uint32_t at = sel0 + j * kTilePix;
+        cshift = fmaf(spos[at] >= 0 ? sw[at] : 0.0f, sdot[at], cshift);  // this lane's own store
       }
+    cshift += __shfl_xor(cshift, 32, 64);
     cshift *= rw;
-  }
 #pragma unroll
-  for (int q = 0; q < KMAX; ++q)
-    if (q < K) seldot[tbase + (size_t)q * kTilePix + tid] = s_w[wsel_off(q, tid)] - cshift;
-  __syncthreads();
+    for (int j = 0; j < QH; ++j)
+      if (q0 + j < K) sdot[sel0 + j * kTilePix] -= cshift;
+  }
   });
 }
 
@@ -1426,23 +1486,23 @@ __global__ __launch_bounds__(256) void k_reduce_feat_heavy(int64_t n, int ncam, 
 }
 
 // ------------------------------------------------------------- host wrappers
-template <typename FT, int KMAX, int GC>
+template <typename FT, int KMAX, bool SPLIT>
 static void feat_bwd_launch(const SurfelArgs& s, const Layout& L, const CamTable& ct, const Tuning& tu,
                             const ImageGradArgs& g, bool renorm, char* ws, hipStream_t st) {
-  const size_t shm = (size_t)kWRow * L.k * sizeof(float);  // weights, then dots
-  hipLaunchKernelGGL((k_feat_bwd_topk<FT, KMAX, GC>), dim3(xcd_grid(L.tiles)), dim3(256), shm, st,
+  hipLaunchKernelGGL((k_feat_bwd_topk<FT, KMAX, SPLIT>), dim3(xcd_grid(L.tiles)), dim3(kFbThreads),
+                     2 * kFbPart * sizeof(float), st,
                      (const uint32_t*)(ws + L.pid), (const uint32_t*)(ws + L.eid0), (const uint2*)(ws + L.ranges),
                      (const int32_t*)(ws + L.selpos), (const float*)(ws + L.selw), feat_src<FT>(s), g.feat, s.c, L.k,
                      ct, tile_order(L, tu.sched_bwd, ws), (float*)(ws + L.seldot), (float*)(ws + L.fpart),
                      (uint8_t*)(ws + L.fflag), renorm ? 1 : 0);
 }
 
-template <typename FT, int GC>
+template <typename FT, bool SPLIT>
 static void feat_bwd_k(const SurfelArgs& s, const Layout& L, const CamTable& ct, const Tuning& tu,
                        const ImageGradArgs& g, bool rn, char* ws, hipStream_t st) {
-  if (L.k <= 8) feat_bwd_launch<FT, 8, GC>(s, L, ct, tu, g, rn, ws, st);
-  else if (L.k <= 16) feat_bwd_launch<FT, 16, GC>(s, L, ct, tu, g, rn, ws, st);
-  else feat_bwd_launch<FT, 32, GC>(s, L, ct, tu, g, rn, ws, st);
+  if (L.k <= 8) feat_bwd_launch<FT, 8, SPLIT>(s, L, ct, tu, g, rn, ws, st);
+  else if (L.k <= 16) feat_bwd_launch<FT, 16, SPLIT>(s, L, ct, tu, g, rn, ws, st);
+  else feat_bwd_launch<FT, 32, SPLIT>(s, L, ct, tu, g, rn, ws, st);
 }
 
 template <int MODE, typename FT, bool LP, bool DM>
@@ -1483,8 +1543,8 @@ static void backward_typed(const SurfelArgs& s, const CamTable& ct, int blend, c
     if (blend == kTopK) {
       prof.begin(kStageBwdFeature, st);
       if (want_f) {
-        if (tu.bwd_pass == 32) feat_bwd_k<FT, 32>(s, L, ct, tu, g, renorm, ws, st);
-        else feat_bwd_k<FT, 16>(s, L, ct, tu, g, renorm, ws, st);
+        if (feat_src<FT>(s).cb > 0) feat_bwd_k<FT, true>(s, L, ct, tu, g, renorm, ws, st);
+        else feat_bwd_k<FT, false>(s, L, ct, tu, g, renorm, ws, st);
       } else {
         launch_fill_u32(ws + L.seldot, 0u, L.spix * (int64_t)L.k, st);
       }

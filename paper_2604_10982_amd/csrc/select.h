@@ -28,7 +28,8 @@ struct SelShared {
   uint32_t lpos[kSlotChunk]; // list position of each slot of the chunk
 };
 
-// Block-wide (256 threads) exclusive prefix sum of one value per thread.
+// Block-wide (NT threads) exclusive prefix sum of one value per thread.
+template <int NT = 256>
 __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* red, uint32_t& total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t x = v;
@@ -41,7 +42,7 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* red, u
   __syncthreads();
   uint32_t pre = 0, tot = 0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
+  for (int w = 0; w < NT / 64; ++w) {
     const uint32_t t = red[w];
     pre += w < wave ? t : 0u;
     tot += t;
@@ -73,10 +74,11 @@ __device__ __forceinline__ int window_words(int maxpos, int w0) {
 
 // Marks the selected positions of the window and ranks them; returns the
 // number of distinct selected positions in the window.
-template <int KMAX>
+template <int KMAX, int NT = 256>
 __device__ int build_window(SelShared& S, const int (&pos)[KMAX], int K, int w0, int nwords) {
+  constexpr int WPT = kWinWords / NT;  // consecutive words per thread
   const int tid = threadIdx.x;
-  for (int i = tid; i < nwords; i += 256) S.bits[i] = 0u;
+  for (int i = tid; i < nwords; i += NT) S.bits[i] = 0u;
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < KMAX; ++q) {
@@ -84,13 +86,21 @@ __device__ int build_window(SelShared& S, const int (&pos)[KMAX], int K, int w0,
     if (q < K && pos[q] >= 0 && r >= 0 && r < nwords * 32) atomicOr(&S.bits[r >> 5], 1u << (r & 31));
   }
   __syncthreads();
-  const int w = 2 * tid;
-  const uint32_t b0 = w < nwords ? S.bits[w] : 0u;
-  const uint32_t b1 = w + 1 < nwords ? S.bits[w + 1] : 0u;
+  uint32_t cnt[WPT], sum = 0;
+#pragma unroll
+  for (int i = 0; i < WPT; ++i) {
+    const int w = WPT * tid + i;
+    cnt[i] = (uint32_t)__popc(w < nwords ? S.bits[w] : 0u);
+    sum += cnt[i];
+  }
   uint32_t total;
-  const uint32_t ex = block_scan_excl((uint32_t)(__popc(b0) + __popc(b1)), S.red, total);
-  if (w < nwords) S.pref[w] = ex;
-  if (w + 1 < nwords) S.pref[w + 1] = ex + (uint32_t)__popc(b0);
+  uint32_t ex = block_scan_excl<NT>(sum, S.red, total);
+#pragma unroll
+  for (int i = 0; i < WPT; ++i) {
+    const int w = WPT * tid + i;
+    if (w < nwords) S.pref[w] = ex;
+    ex += cnt[i];
+  }
   __syncthreads();
   return (int)total;
 }
