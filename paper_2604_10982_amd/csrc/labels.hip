@@ -271,92 +271,134 @@ __global__ __launch_bounds__(256) void k_lab_dfg(int64_t n, LabelQueries q, cons
   }
 }
 
-// Partial dF_q = dZ^T F_g over one surfel segment: a wave computes 16 queries x
-// 16 channels (MFMA over the segment's surfels).
+// Partial dF_q = dZ^T F_g over one surfel segment: 16 queries x 16 channels
+// (MFMA over the segment's surfels).  Four waves take its steps of 4 surfels in
+// turn, eight steps' loads in flight: one wave stepping alone through 1024
+// surfels waited for each step's loads (120k surfels, 64 queries, 32 channels:
+// 94 -> 35 us).  The waves' sums are added in wave order.
+constexpr int kLabFly = 8;
 template <typename FT, int NQB>
-__global__ __launch_bounds__(64) void k_lab_dfq(int64_t n, int64_t seg_len, LabelQueries q,
-                                                const float* __restrict__ dZ, const FT* __restrict__ fg,
-                                                float* __restrict__ part) {
+__global__ __launch_bounds__(256) void k_lab_dfq(int64_t n, int64_t seg_len, LabelQueries q,
+                                                 const float* __restrict__ dZ, const FT* __restrict__ fg,
+                                                 float* __restrict__ part) {
   constexpr int NQP = NQB * 16;
-  const int lane = threadIdx.x & 63, i = lane & 15, k = lane >> 4;
+  __shared__ float s_acc[4][256];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, k = lane >> 4;
   const int j0 = blockIdx.x * 16, c0 = blockIdx.y * 16, s = blockIdx.z;
   const int64_t gs = (int64_t)s * seg_len, ge = min(n, gs + seg_len);
+  const int cl = min(c0 + i, q.c - 1);  // columns past c are not used
   f4v acc = {0.f, 0.f, 0.f, 0.f};
-  for (int64_t g = gs; g < ge; g += 4) {
-    const int64_t gk = g + k;
-    const float a = gk < ge ? dZ[gk * NQP + j0 + i] : 0.0f;
-    const float b = (gk < ge && c0 + i < q.c) ? load_one<FT>(fg + gk * q.c + c0 + i) : 0.0f;
-    acc = mfma_16x16x4(a, b, acc);
+  for (int64_t g = gs + 4 * wave + k; g - k < ge; g += 16 * kLabFly) {
+    float a[kLabFly], b[kLabFly];
+#pragma unroll
+    for (int u = 0; u < kLabFly; ++u) {
+      const int64_t gu = g + 16 * u;
+      const int64_t gl = min(gu, ge - 1);
+      a[u] = dZ[gl * NQP + j0 + i];
+      b[u] = load_one<FT>(fg + gl * q.c + cl);
+      if (gu >= ge) a[u] = b[u] = 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < kLabFly; ++u) acc = mfma_16x16x4(a[u], b[u], acc);
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int j = j0 + 4 * k + r;
-    if (c0 + i < q.c) part[((size_t)s * NQP + j) * q.c + c0 + i] = acc[r];
-  }
+  for (int r = 0; r < 4; ++r) s_acc[wave][(4 * k + r) * 16 + i] = acc[r];
+  __syncthreads();
+  const int t = threadIdx.x, j = j0 + (t >> 4), c = c0 + (t & 15);
+  if (c < q.c) part[((size_t)s * NQP + j) * q.c + c] = ((s_acc[0][t] + s_acc[1][t]) + s_acc[2][t]) + s_acc[3][t];
 }
 
 // Partial query-mean / precision gradients over one surfel segment (FP64
-// accumulation, fixed-order block reduction).
+// accumulation, fixed order).  A block takes 16 queries: lane i of 16 one
+// query, so that wD is read in whole lines (a block per query read 4 bytes of
+// each line), and each of the 16 lane groups every 16th surfel; the
+// precision is applied to the sums.  120k
+// surfels, 64 queries: 52 -> 40 us.
 template <int NQB>
 __global__ __launch_bounds__(256) void k_lab_qgeo(int64_t n, int64_t seg_len, const float* __restrict__ means,
                                                   LabelQueries q, const float* __restrict__ wD,
                                                   double* __restrict__ part) {
   constexpr int NQP = NQB * 16;
-  __shared__ double s_red[256];
-  const int j = blockIdx.x, s = blockIdx.y, tid = threadIdx.x;
+  __shared__ double s_red[4][16][9];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15;
+  const int j = blockIdx.x * 16 + i, s = blockIdx.y;
   const int64_t gs = (int64_t)s * seg_len, ge = min(n, gs + seg_len);
-  const QGeo gq = load_qgeo(q, j);
+  const QGeo gq = load_qgeo(q, min(j, q.nq - 1));
   double v[9];
 #pragma unroll
   for (int x = 0; x < 9; ++x) v[x] = 0.0;
-  for (int64_t g = gs + tid; g < ge; g += 256) {
+#pragma unroll 4
+  for (int64_t g = gs + (threadIdx.x >> 4); g < ge; g += 16) {
     const double w = wD[g * NQP + j];
     const double dx = (double)means[3 * g] - gq.mx, dy = (double)means[3 * g + 1] - gq.my,
                  dz = (double)means[3 * g + 2] - gq.mz;
-    const double Px = gq.pxx * dx + gq.pxy * dy + gq.pxz * dz;
-    const double Py = gq.pxy * dx + gq.pyy * dy + gq.pyz * dz;
-    const double Pz = gq.pxz * dx + gq.pyz * dy + gq.pzz * dz;
-    v[0] += w * Px;
-    v[1] += w * Py;
-    v[2] += w * Pz;
-    // dL/dP = -wD/2 d d^T; an off-diagonal number appears twice in P
-    v[3] += -0.5 * w * dx * dx;
-    v[4] += -w * dx * dy;
-    v[5] += -w * dx * dz;
-    v[6] += -0.5 * w * dy * dy;
-    v[7] += -w * dy * dz;
-    v[8] += -0.5 * w * dz * dz;
+    const double wx = w * dx, wy = w * dy, wz = w * dz;
+    v[0] += wx;
+    v[1] += wy;
+    v[2] += wz;
+    v[3] = __builtin_fma(wx, dx, v[3]);
+    v[4] = __builtin_fma(wx, dy, v[4]);
+    v[5] = __builtin_fma(wx, dz, v[5]);
+    v[6] = __builtin_fma(wy, dy, v[6]);
+    v[7] = __builtin_fma(wy, dz, v[7]);
+    v[8] = __builtin_fma(wz, dz, v[8]);
   }
+  {  // dL/dmu = P sum w d;  dL/dP = -w/2 d d^T, an off-diagonal number appears twice in P
+    const double x = v[0], y = v[1], z = v[2];
+    v[0] = gq.pxx * x + gq.pxy * y + gq.pxz * z;
+    v[1] = gq.pxy * x + gq.pyy * y + gq.pyz * z;
+    v[2] = gq.pxz * x + gq.pyz * y + gq.pzz * z;
+    v[3] *= -0.5; v[6] *= -0.5; v[8] *= -0.5;
+    v[4] = -v[4]; v[5] = -v[5]; v[7] = -v[7];
+  }
+#pragma unroll
   for (int x = 0; x < 9; ++x) {
-    s_red[tid] = v[x];
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if (tid < o) s_red[tid] += s_red[tid + o];
-      __syncthreads();
-    }
-    if (tid == 0) part[((size_t)s * NQP + j) * 9 + x] = s_red[0];
-    __syncthreads();
+    v[x] += __shfl_xor(v[x], 16, 64);
+    v[x] += __shfl_xor(v[x], 32, 64);
+    if (lane < 16) s_red[wave][i][x] = v[x];
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < 16 * 9; t += 256) {
+    const int jj = blockIdx.x * 16 + t / 9, x = t % 9;
+    if (jj < q.nq)
+      part[((size_t)s * NQP + jj) * 9 + x] =
+          ((s_red[0][t / 9][x] + s_red[1][t / 9][x]) + s_red[2][t / 9][x]) + s_red[3][t / 9][x];
   }
 }
 
-// Sum of the segment partials in segment order.
+// Sum of the segment partials: a block takes 32 results, 8 threads each, thread
+// y every 8th segment, then the 8 in order (one thread per result waited for
+// 117 loads in turn: 30 -> 6 us).
 __global__ __launch_bounds__(256) void k_lab_sum(int nseg, int nq, int nqp, int c, const float* __restrict__ pfq,
                                                  const double* __restrict__ pgeo, float* __restrict__ d_qfeat,
                                                  float* __restrict__ d_qmean, float* __restrict__ d_qprec) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t nf = (int64_t)nq * c;
+  __shared__ double s_sum[8][32];
+  const int x32 = threadIdx.x & 31, y = threadIdx.x >> 5;
+  const int64_t t = (int64_t)blockIdx.x * 32 + x32;
+  const int64_t nf = (int64_t)nq * c, tot = nf + (int64_t)nq * 9;
+  const int64_t u = t - nf;
+  double a = 0.0;
   if (t < nf) {
-    const int j = (int)(t / c), cc = (int)(t % c);
-    double a = 0.0;
-    for (int s = 0; s < nseg; ++s) a += pfq[((size_t)s * nqp + j) * c + cc];
-    d_qfeat[t] = (float)a;
-  } else if (t < nf + (int64_t)nq * 9) {
-    const int64_t u = t - nf;
+    const float* p = pfq + t;  // query-major: element (j, cc) at j c + cc
+#pragma unroll 4
+    for (int s = y; s < nseg; s += 8) a += p[(size_t)s * nqp * c];
+  } else if (t < tot) {
+    const double* p = pgeo + u;
+#pragma unroll 4
+    for (int s = y; s < nseg; s += 8) a += p[(size_t)s * nqp * 9];
+  }
+  s_sum[y][x32] = a;
+  __syncthreads();
+  if (y != 0 || t >= tot) return;
+  double r = s_sum[0][x32];
+#pragma unroll
+  for (int w = 1; w < 8; ++w) r += s_sum[w][x32];
+  if (t < nf) {
+    d_qfeat[t] = (float)r;
+  } else {
     const int j = (int)(u / 9), x = (int)(u % 9);
-    double a = 0.0;
-    for (int s = 0; s < nseg; ++s) a += pgeo[((size_t)s * nqp + j) * 9 + x];
-    if (x < 3) d_qmean[3 * j + x] = (float)a;
-    else d_qprec[6 * j + (x - 3)] = (float)a;
+    if (x < 3) d_qmean[3 * j + x] = (float)r;
+    else d_qprec[6 * j + (x - 3)] = (float)r;
   }
 }
 
@@ -405,12 +447,12 @@ static void lab_bwd_t(int64_t n, const float* means, const void* fg, const Label
     hipLaunchKernelGGL((k_lab_dfg<NQB>), dim3(nb, (unsigned)cdiv(q.c, 16)), dim3(256), 0, st, n, q, (const float*)dZ,
                        d_fg);
   }
-  hipLaunchKernelGGL((k_lab_dfq<FT, NQB>), dim3(NQB, (unsigned)cdiv(q.c, 16), (unsigned)nseg), dim3(64), 0, st, n,
+  hipLaunchKernelGGL((k_lab_dfq<FT, NQB>), dim3(NQB, (unsigned)cdiv(q.c, 16), (unsigned)nseg), dim3(256), 0, st, n,
                      seg_len, q, (const float*)dZ, (const FT*)fg, pfq);
-  hipLaunchKernelGGL((k_lab_qgeo<NQB>), dim3((unsigned)q.nq, (unsigned)nseg), dim3(256), 0, st, n, seg_len, means, q,
+  hipLaunchKernelGGL((k_lab_qgeo<NQB>), dim3((unsigned)cdiv(q.nq, 16), (unsigned)nseg), dim3(256), 0, st, n, seg_len, means, q,
                      (const float*)wD, pgeo);
   const int64_t tot = (int64_t)q.nq * (q.c + 9);
-  hipLaunchKernelGGL(k_lab_sum, dim3((unsigned)cdiv(tot, 256)), dim3(256), 0, st, (int)nseg, q.nq, NQP, q.c,
+  hipLaunchKernelGGL(k_lab_sum, dim3((unsigned)cdiv(tot, 32)), dim3(256), 0, st, (int)nseg, q.nq, NQP, q.c,
                      (const float*)pfq, (const double*)pgeo, d_qfeat, d_qmean, d_qprec);
 }
 
