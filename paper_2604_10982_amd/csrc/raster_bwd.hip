@@ -1404,15 +1404,17 @@ __global__ __launch_bounds__(256) void k_reduce_feat(int64_t n, int ncam, const 
 
 // Block per heavy surfel (a fixed grid strides over the heavy list, whose
 // length it reads on the device): CL channel lanes (float4 groups) x R =
-// 256 / CL row lanes.  The surfel's flagged slots are compacted in emission
-// order (camera by camera, 256 slots a step, block prefix count) into an LDS
+// 1024 / CL row lanes.  The surfel's flagged slots are compacted in emission
+// order (camera by camera, 1024 slots a step, block prefix count) into an LDS
 // list; row lane r adds, in rank order, the rows whose rank among the
-// surfel's flagged rows is r mod R, four rows in flight, and the R partial
+// surfel's flagged rows is r mod R, eight rows in flight, and the R partial
 // rows are then added in row-lane order.  The partition depends only on the
 // sequence of flagged rows: the result is deterministic, the same for every
-// launch choice, and unchanged by pairs that carry no row.
-constexpr int kHvList = 2048;
-__global__ __launch_bounds__(256) void k_reduce_feat_heavy(int64_t n, int ncam, const uint32_t* __restrict__ vbase,
+// launch choice, and unchanged by pairs that carry no row.  The longest
+// surfel's rows bound the kernel, so as many as registers allow are in flight:
+// 1M street surfels, C = 256: 390 -> 167 us against 256 threads and four rows.
+constexpr int kHvList = 2048, kHvThreads = 1024, kHvFly = 8;
+__global__ __launch_bounds__(kHvThreads) void k_reduce_feat_heavy(int64_t n, int ncam, const uint32_t* __restrict__ vbase,
                                                            const uint32_t* __restrict__ count, int64_t cap,
                                                            const float* __restrict__ fpart,
                                                            const uint8_t* __restrict__ fflag, int C,
@@ -1420,10 +1422,10 @@ __global__ __launch_bounds__(256) void k_reduce_feat_heavy(int64_t n, int ncam, 
                                                            const uint32_t* __restrict__ heavy,
                                                            const uint32_t* __restrict__ status) {
   __shared__ uint32_t s_slot[kHvList];
-  __shared__ float4 s_acc[256];
-  __shared__ uint32_t s_red[8];
+  __shared__ float4 s_acc[kHvThreads];
+  __shared__ uint32_t s_red[kHvThreads / 64];
   const int t = threadIdx.x;
-  const int G = C / 4, CL = min(G, 64), R = 256 / CL;
+  const int G = C / 4, CL = min(G, 64), R = kHvThreads / CL;
   const int rl = t / CL, cl = t % CL;
   const uint32_t nh = status[kStHeavy];
   for (uint32_t h = blockIdx.x; h < nh; h += gridDim.x) {
@@ -1436,16 +1438,16 @@ __global__ __launch_bounds__(256) void k_reduce_feat_heavy(int64_t n, int ncam, 
       auto drain = [&]() {
         __syncthreads();
         if (rl < R && g < G) {
-          for (uint32_t j = (uint32_t)((rl + R - (int)(rank0 % (uint32_t)R)) % R); j < nl; j += 4u * R) {
-            float4 x[4];
+          for (uint32_t j = (uint32_t)((rl + R - (int)(rank0 % (uint32_t)R)) % R); j < nl; j += (uint32_t)(kHvFly * R)) {
+            float4 x[kHvFly];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < kHvFly; ++u) {
               const uint32_t jj = j + (uint32_t)(u * R);
               x[u] = jj < nl ? *reinterpret_cast<const float4*>(fpart + (size_t)s_slot[jj] * C + 4 * g)
                              : make_float4(0.f, 0.f, 0.f, 0.f);
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < kHvFly; ++u) {
               acc.x += x[u].x; acc.y += x[u].y; acc.z += x[u].z; acc.w += x[u].w;
             }
           }
@@ -1457,13 +1459,13 @@ __global__ __launch_bounds__(256) void k_reduce_feat_heavy(int64_t n, int ncam, 
       for (int b = 0; b < ncam; ++b) {
         const int64_t v = (int64_t)b * n + i, base = vbase[v];
         const int64_t end = min(base + (int64_t)count[v], cap);
-        for (int64_t c0 = base; c0 < end; c0 += 256) {
+        for (int64_t c0 = base; c0 < end; c0 += kHvThreads) {
           const bool f = c0 + t < end && fflag[c0 + t];
           uint32_t total;
-          const uint32_t pre = block_scan_excl(f ? 1u : 0u, s_red, total);
-          if (f) s_slot[nl + pre] = (uint32_t)(c0 + t);  // nl <= kHvList - 256 here
+          const uint32_t pre = block_scan_excl<kHvThreads>(f ? 1u : 0u, s_red, total);
+          if (f) s_slot[nl + pre] = (uint32_t)(c0 + t);  // nl <= kHvList - kHvThreads here
           nl += total;
-          if (nl > (uint32_t)(kHvList - 256)) drain();
+          if (nl > (uint32_t)(kHvList - kHvThreads)) drain();
         }
       }
       drain();
@@ -1588,7 +1590,7 @@ static void backward_typed(const SurfelArgs& s, const CamTable& ct, int blend, c
                          count, L.cap, (const float*)(ws + L.fpart), (const uint8_t*)(ws + L.fflag), s.c, lpp2,
                          gr.feat, gr.feat_ext, s.ca, heavy, status);
       const unsigned gh = (unsigned)std::min<int64_t>(L.cap / (kHeavyRows + 1) + 1, 1024);
-      hipLaunchKernelGGL(k_reduce_feat_heavy, dim3(gh), dim3(256), 0, st, s.n, ct.n, vbase, count, L.cap,
+      hipLaunchKernelGGL(k_reduce_feat_heavy, dim3(gh), dim3(kHvThreads), 0, st, s.n, ct.n, vbase, count, L.cap,
                          (const float*)(ws + L.fpart), (const uint8_t*)(ws + L.fflag), s.c, gr.feat, gr.feat_ext, s.ca,
                          (const uint32_t*)heavy, (const uint32_t*)status);
     }
