@@ -486,7 +486,8 @@ def geometry_workload(psm, means, scales, quats, sc, steps, warmup, k=512):
     flops = 23.0 * n * k   # per (surfel, component) score: 3 sub, 9 mul, 8 add (FP32), 3 for the minimum
     return {"ms": ms, "surfels": n, "components": k, "surfels_per_s": n / (ms * 1e-3),
             "alu_tflops": flops / (ms * 1e-3) / 1e12, "alu_frac": flops / (ms * 1e-3) / 1e12 / FP32_VALU_PEAK_TFLOPS,
-            "note": "psm_geometry_loss: FP32 MAP scan over the components staged in LDS, FP64 loss terms and "
+            "note": "psm_geometry_loss: MAP component by a matrix-core bound and exact FP32 scores of the contenders "
+                    "(alu_tflops: the operations of a full scan over the time), FP64 loss terms and "
                     "gradients, ordered FP64 sums"}
 
 

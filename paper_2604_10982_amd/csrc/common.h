@@ -554,6 +554,19 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Four lane groups hold four channels each (group k: channels 4 k ..); after
+// this, component s of every group k is channel 4 s + k: four matrix steps of
+// four channels in order, from one 16-byte load a lane.  (The order matters:
+// the geometric chain of surfels seen edge-on amplifies a dot's rounding.)
+__device__ __forceinline__ float4 by_step(float4 v) {
+  const auto u = [](float x) { return __float_as_uint(x); };
+  const auto a = __builtin_amdgcn_permlane32_swap(u(v.x), u(v.z), false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(u(v.y), u(v.w), false, false);
+  const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+  const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  return make_float4(__uint_as_float(c[0]), __uint_as_float(c[1]), __uint_as_float(d[0]), __uint_as_float(d[1]));
+}
+
 // FP32 matrix-core product on a 16 x 16 tile, k = 4 (v_mfma_f32_16x16x4f32):
 // lane l supplies A[l & 15][l >> 4] and B[l >> 4][l & 15] and holds
 // D[4 (l >> 4) + r][l & 15] in component r.  Products are exact and summed in

@@ -76,7 +76,23 @@ __device__ __forceinline__ void logits(int64_t n, const FT* __restrict__ fg, con
   const int64_t ga = g0 + i;
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) acc[qb] = f4v{0.f, 0.f, 0.f, 0.f};
-  for (int c0 = 0; c0 < q.c; c0 += 4) {
+  int c0 = 0;
+  // 16 channels a step: one load a lane of each operand instead of four (each
+  // touches 16 rows); the arrays may start anywhere, so only where they are
+  // aligned.  120k surfels, 64 queries, 32 channels: the forward 59 -> 37 us,
+  // the surfel backward 77 -> 59 us.
+  const bool wide = ((uintptr_t)fg % (4 * sizeof(FT)) | (uintptr_t)q.feat % 16) == 0;
+  for (; wide && c0 + 16 <= q.c; c0 += 16) {
+    const float4 a = by_step(load4<FT>(fg + min(ga, n - 1) * q.c + c0 + 4 * kq));  // rows past n: not used
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) {  // columns past nq: not used
+      const float* bp = q.feat + (size_t)min(qb * 16 + i, q.nq - 1) * q.c + c0 + 4 * kq;
+      const float4 b = by_step(*reinterpret_cast<const float4*>(bp));
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc[qb] = mfma_16x16x4((&a.x)[s], (&b.x)[s], acc[qb]);
+    }
+  }
+  for (; c0 < q.c; c0 += 4) {
     const float a = ga < n ? load_one<FT>(fg + ga * q.c + c0 + kq) : 0.0f;
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {

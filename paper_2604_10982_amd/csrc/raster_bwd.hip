@@ -73,19 +73,6 @@ __device__ __forceinline__ uint32_t formed_here(uint32_t v) {
   return v;
 }
 
-// Four lane groups hold four channels each (group k: channels 4 k ..); after
-// this, component s of every group k is channel 4 s + k: the order in which
-// the dots are summed (their rounding is amplified by the geometric chain of
-// surfels seen edge-on, so it stays the order of channels).
-__device__ __forceinline__ float4 by_step(float4 v) {
-  const auto u = [](float x) { return __float_as_uint(x); };
-  const auto a = __builtin_amdgcn_permlane32_swap(u(v.x), u(v.z), false, false);
-  const auto b = __builtin_amdgcn_permlane32_swap(u(v.y), u(v.w), false, false);
-  const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
-  const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
-  return make_float4(__uint_as_float(c[0]), __uint_as_float(c[1]), __uint_as_float(d[0]), __uint_as_float(d[1]));
-}
-
 // SPLIT: features in two arrays.
 template <typename FT, int KMAX, bool SPLIT>
 __global__ __launch_bounds__(kFbThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_feat_bwd_topk(
