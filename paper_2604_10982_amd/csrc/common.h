@@ -27,7 +27,8 @@ constexpr float kTMin = 1e-4f;
 // pixels with tw in {8, 16, 32, 64} (a launch choice, 16 x 16 by default).
 // Wave w owns a sub-tile of 8 x 8 pixels (16 x 4 in a 64 x 4 tile), the
 // sub-tiles row-major in the tile and the pixels row-major in the sub-tile: a
-// compact sub-tile meets fewer of the tile's surfels than 16 x 4 rows do.
+// compact sub-tile meets fewer of the tile's surfels than 16 x 4 rows do.  (The
+// backward walk's waves own rows: the order of its sums is fixed.)
 constexpr int kTilePix = 256;
 constexpr int kTileDefault = 16;
 constexpr int kMaxK = 32;
@@ -111,6 +112,13 @@ __host__ __device__ inline int tile_lx(const CamTable& ct, int p) {
 }
 __host__ __device__ inline int tile_ly(const CamTable& ct, int p) {
   return ((p & 63) >> ct.ssh) + (((p >> 6) >> (ct.tsh - ct.ssh)) << (6 - ct.ssh));
+}
+
+// The same the other way: the index of the tile-local pixel (lx, ly).
+__host__ __device__ inline int tile_index(const CamTable& ct, int lx, int ly) {
+  const int sx = lx >> ct.ssh, sy = ly >> (6 - ct.ssh);
+  return 64 * (sx + (sy << (ct.tsh - ct.ssh))) + (lx & ((1 << ct.ssh) - 1)) +
+         ((ly & ((64 >> ct.ssh) - 1)) << ct.ssh);
 }
 
 // Where global tile g lies: its camera, tile coordinates and image.

@@ -340,39 +340,43 @@ __global__ __launch_bounds__(kFbThreads) __attribute__((amdgpu_waves_per_eu(4)))
 }
 
 // ------------------------------------------------------------- walk backward
-// The per-surfel sums of a wave's sub-tile as small matrix products.  Every
+// A wave owns 64 consecutive pixels of the tile in row-major order (16 x 4 in a
+// 16 x 16 tile), a lane one of them.
+//
+// The per-surfel sums of a wave's pixels as small matrix products.  Every
 // term is one of a few per-pixel factors times a column of the pixel: w times
 // the upstream gradients (dC, dn_c), dL/du', dL/dv', dL/dw' times (1, dx, dy)
 // with (dx, dy) the pixel's offset from the surfel's centre, and two plain
-// sums.  The wave puts the factors of its contributing entries in its LDS
+// sums.  The wave puts the factors of its contributing entries (and their
+// offsets) in its LDS
 // slice and multiplies them by the columns on v_mfma_f32_4x4x1 (16 blocks,
-// block b holding the pixels 4 b .. 4 b + 3, one per step); for four entries
+// block b holding four pixels, one per step); for four entries
 // together the 16 blocks are then added across lanes.  Rows of the first
 // product are an entry's four geometric factors (the offset columns are the
 // entry's own; formed every second entry, so that LDS holds two entries'),
-// rows of the others the four entries.  That is 28 matrix and 80 vector instructions for
-// four entries, where forming 17 products per pixel and reducing them over
+// rows of the others the four entries.  Forming 17 products per pixel and reducing them over
 // the wave took 65 vector instructions per entry of the 142 the walk issued
-// (it is bound by their issue).  Offsets from a fixed point of the sub-tile
-// instead of the surfel's centre would save 7 more per entry, but the sums
-// about the centre then cancel: 5 times the error in the quaternions.
-constexpr int kGeoFac = 4;   // du', dv', dw', dop
+// (it is bound by their issue).
+//
+// The order of the geometric sums is part of the result: of a surfel seen
+// edge-on the chain rule takes differences of these FP32 sums, which amplifies
+// their last bit by the ellipse's aspect (quaternion elements by up to a few
+// 1e-3), so another order gives other gradients, no nearer to the exact ones.
+// The order is a tree over the wave's 64 pixels: pixels i and i ^ 32, then ^ 16,
+// ^ 8, ^ 7, ^ 2 and ^ 1, every product rounded; the waves follow in order.  So step st of a block
+// takes pixel 16 st + c, each step's product is kept apart, and block b has the
+// column c for which the cross-lane adds (blocks ^ 8, ^ 4, ^ 2, ^ 1) are the
+// tree's last four levels.
+constexpr int kGeoFac = 6;   // du', dv', dw', dop; dx, dy
 // Sums per entry and wave, at 4 r + j: row r = 0, 1, 2: (du', dv', dw') times
 // (1, dx, dy); column 3 of these rows: dn_1, dn_2, dz; row 3: dC, dn_0; then
 // dop (and, low-pass, the filter term's centre gradient).
 constexpr int kSums = 20;
 
-// Quad broadcast: every lane of a quad gets the quad's lane S.
-template <int S>
-__device__ __forceinline__ float quad_lane(float v) {
-  return dpp_mov<S | (S << 2) | (S << 4) | (S << 6)>(v);
-}
-
-// Column value of lane (block b = lane >> 2, column j = lane & 3) for the pixel of lane 4 b + S.
-template <int S>
-__device__ __forceinline__ float quad_col(int j, float c0, float c1, float c2, float c3) {
-  const float a = quad_lane<S>(c0), b = quad_lane<S>(c1), c = quad_lane<S>(c2), d = quad_lane<S>(c3);
-  return j == 0 ? a : (j == 1 ? b : (j == 2 ? c : d));
+// Place of the wave's pixel i among the 16 blocks of four pixels.
+__device__ __forceinline__ int block_slot(int i) {
+  const int c = i & 7;
+  return 4 * ((i & 8) | (c < 4 ? c : 11 - c)) + (i >> 4);
 }
 
 __device__ __forceinline__ f4v mfma_4x4x1(float a, float b, f4v c) {
@@ -383,7 +387,7 @@ __device__ __forceinline__ f4v mfma_4x4x1(float a, float b, f4v c) {
 // (true) or in vector FMAs (false); a launch choice, whichever is faster for
 // the workload (the autotuner times both).
 template <int MODE, typename FT, bool LP, bool DM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTopK ? 4 : 1))) void k_walk_bwd(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTopK ? (LP ? 3 : 4) : 1))) void k_walk_bwd(
     const WalkRec* __restrict__ rec, const uint32_t* __restrict__ pid, const uint32_t* __restrict__ eid,
     const uint2* __restrict__ ranges, CamTable ct, TileOrder tq, int K, const uint32_t* __restrict__ nlast,
     const float* __restrict__ tfinal,
@@ -399,7 +403,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
   constexpr int NC = LP ? 4 : 2;  // w, dz (low-pass: and the filter term's centre gradient)
   __shared__ __align__(16) float s_geo[4][2][kGeoFac][64];  // [wave][entry of the pair][factor][pixel]
   __shared__ __align__(16) float s_col[4][NC][4][64];       // [wave][factor][entry of the group][pixel]
-  __shared__ float s_off[4][2][8];  // [wave][entry of the pair]: 0, centre x, y, 0, and what they lack to the FP64 centre
   __shared__ __align__(16) float s_part[4][kBB][kSums];
   __shared__ uint32_t s_has[4];
   __shared__ int s_lmax;
@@ -414,19 +417,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
   // tile whose pixels reach further takes them from memory), read back to
   // front by the pixel's own lane; the feature dots stay in global memory,
   // each loaded when the previous one is used.  (With K = 16 a block then
-  // takes 35 KB of LDS and four share a CU; at three the walk is 15% slower.)
+  // takes 39 KB of LDS and four share a CU; at three the walk is 15% slower.)
   extern __shared__ uint16_t s_sel[];
 
   with_tile(tq, [&](const int tile) {
   const TileLoc tl = locate(ct, tile);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tx = tl.tx, ty = tl.ty, W = tl.W, H = tl.H;
-  const int px = tx * ct.tw + tile_lx(ct, tid), py = ty * ct.th + tile_ly(ct, tid);
+  const int lx = tid & (ct.tw - 1), ly = tid >> ct.tsh, at = tile_index(ct, lx, ly);
+  const int px = tx * ct.tw + lx, py = ty * ct.th + ly;
   const bool inside = px < W && py < H;
   const double X = (double)px + 0.5, Y = (double)py + 0.5;
-  const SubRect sr = sub_rect(ct, tl, wave);
+  SubRect sr;  // pixel centres of the wave's rows (pixels past the image included)
+  sr.x0 = (float)(tx * ct.tw) + 0.5f;
+  sr.x1 = sr.x0 + (float)(ct.tw - 1);
+  sr.y0 = (float)(ty * ct.th + wave * (64 >> ct.tsh)) + 0.5f;
+  sr.y1 = sr.y0 + (float)((64 >> ct.tsh) - 1);
   const uint32_t start = ranges[tile].x;
-  const int sp = tile * kTilePix + tid;
+  const int sp = tile * kTilePix + at;
   const int my_last = (int)nlast[sp];
   float T = tfinal[sp];
   const int64_t pix = tl.pix0 + (int64_t)py * W + px;
@@ -438,21 +446,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
     if (g_alpha) gA = g_alpha[pix];
   }
   const float gAT = gA * T;
-  // the columns, a step per pixel of the quad: (1, x, y, -) about the
-  // sub-tile's centre, less the entry's centre; (dC, dn_0); (dn_1, dn_2, -, -);
+  // the columns, a step per pixel of the block: (dC, dn_0); (dn_1, dn_2, -, -);
   // and unit column 2 for the plain sum
-  const int col = lane & 3;
-  const float mx = 0.5f * (sr.x0 + sr.x1), my = 0.5f * (sr.y0 + sr.y1);
-  float bg[4], bc[4], bn[4];
+  const int col = lane & 3, slot = block_slot(lane);
+  f4v bc, bn;
   {
-    const float xs = (float)px + 0.5f - mx, ys = (float)py + 0.5f - my;
-    bg[0] = quad_col<0>(col, 1.f, xs, ys, 0.f); bc[0] = quad_col<0>(col, gC0, gC1, gC2, gN0); bn[0] = quad_col<0>(col, gN1, gN2, 0.f, 0.f);
-    bg[1] = quad_col<1>(col, 1.f, xs, ys, 0.f); bc[1] = quad_col<1>(col, gC0, gC1, gC2, gN0); bn[1] = quad_col<1>(col, gN1, gN2, 0.f, 0.f);
-    bg[2] = quad_col<2>(col, 1.f, xs, ys, 0.f); bc[2] = quad_col<2>(col, gC0, gC1, gC2, gN0); bn[2] = quad_col<2>(col, gN1, gN2, 0.f, 0.f);
-    bg[3] = quad_col<3>(col, 1.f, xs, ys, 0.f); bc[3] = quad_col<3>(col, gC0, gC1, gC2, gN0); bn[3] = quad_col<3>(col, gN1, gN2, 0.f, 0.f);
+    float* f = &s_geo[wave][0][0][0];
+    f[slot] = gC0;
+    f[64 + slot] = gC1;
+    f[128 + slot] = gC2;
+    f[192 + slot] = gN0;
+    wave_lds_sync();
+    bc = *reinterpret_cast<const f4v*>(f + 64 * col + (lane & ~3));
+    wave_lds_sync();
+    f[slot] = gN1;
+    f[64 + slot] = gN2;
+    f[128 + slot] = 0.0f;
+    wave_lds_sync();
+    bn = *reinterpret_cast<const f4v*>(f + 64 * min(col, 2) + (lane & ~3));
+    wave_lds_sync();
   }
   const float unit2 = col == 2 ? 1.0f : 0.0f;
-  const double mcol = col == 1 ? (double)mx : (double)my;
   // Top-K: walk the saved selection from its back end.  kq: the last selection
   // before the current batch, at position cursel; kp: the next one whose dot is
   // used (held in nextdot)
@@ -460,10 +474,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
   float nextdot = 0.0f;
   const size_t tbase = (size_t)tile * K * kTilePix;
   uint16_t* s_sp = s_sel;
-  const float* g_sd = seldot + tbase + tid;  // this pixel's dots, read one ahead of their use
+  const float* g_sd = seldot + tbase + at;  // this pixel's dots, read one ahead of their use
   if (MODE == kTopK) {
     for (int q = 0; q < K; ++q) {
-      const int sq = selpos[tbase + (size_t)q * kTilePix + tid];
+      const int sq = selpos[tbase + (size_t)q * kTilePix + at];
       s_sp[q * kTilePix + tid] = (uint16_t)sq;
       if (sq >= 0) {
         kp = q;
@@ -557,7 +571,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
       }
       for (int pb = 0; pb < 4; ++pb) {
         const int q = 64 * wave + 16 * pb + li;  // pixel of lane li
-        const int qx = tx * ct.tw + tile_lx(ct, q), qy = ty * ct.th + tile_ly(ct, q);
+        const int qx = tx * ct.tw + (q & (ct.tw - 1)), qy = ty * ct.th + (q >> ct.tsh);
         const float* gq = g_feat && qx < W && qy < H ? g_feat + (tl.pix0 + (int64_t)qy * W + qx) * C : nullptr;
         f4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
         // 128 channels at a time: every operand of the segment is loaded
@@ -602,8 +616,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
         const bool in = cursel >= lo;
         selbits |= in ? 1u << (cursel - lo) : 0u;
         kq -= in ? 1 : 0;
-        const int q = max(kq, 0) * kTilePix + tid;
-        const int sq = Lmax <= 0xFFFF ? (int)s_sp[q] : selpos[tbase + q];
+        const int q = max(kq, 0) * kTilePix;
+        const int sq = Lmax <= 0xFFFF ? (int)s_sp[q + tid] : selpos[tbase + q + at];
         cursel = kq >= 0 ? sq : -1;
       }
     }
@@ -618,7 +632,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
     uint32_t has = 0u;    // entries with a contributor in this wave
     uint32_t group = 0u;  // the open group's entries, 8 bits each
     int ng = 0;
-    // geometric products of the open pair (entries 2 h, 2 h + 1 of the group):
+    // geometric products of the open pair (entries 2 h, 2 h + 1 of the group),
+    // the first two levels of the tree added:
     // entry i's row r, column j of block b in register r of lane 4 b + j
     f4v dg[4];
     const auto pair = [&](auto hc) {
@@ -627,11 +642,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const f4v f = *reinterpret_cast<const f4v*>(&s_geo[wave][i][lane & 3][lane & ~3]);
-        const float off = s_off[wave][i][col], offl = s_off[wave][i][4 + col];
-        f4v d = {0.f, 0.f, 0.f, 0.f};
+        // column 0 is 1, columns 1 and 2 are dx and dy, column 3 is not used
+        const f4v xy = *reinterpret_cast<const f4v*>(&s_geo[wave][i][4 + (col >> 1)][lane & ~3]);
+        f4v d[4];
 #pragma unroll
-        for (int st = 0; st < 4; ++st) d = mfma_4x4x1(f[st], (bg[st] - off) - offl, d);
-        dg[2 * h + i] = d;
+        for (int st = 0; st < 4; ++st)
+          d[st] = mfma_4x4x1(f[st], col == 0 ? 1.0f : xy[st], f4v{0.f, 0.f, 0.f, 0.f});
+        dg[2 * h + i] = (d[0] + d[2]) + (d[1] + d[3]);
       }
       wave_lds_sync();
     };
@@ -699,7 +716,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
           next = load_rec(rec, lane_value(id, k));
         }
         // the pixel's factors, all zero where it does not take part
-        float w = 0.0f, du1 = 0.0f, dv1 = 0.0f, dw1 = 0.0f, dzi = 0.0f, dop = 0.0f;
+        float w = 0.0f, du1 = 0.0f, dv1 = 0.0f, dw1 = 0.0f, dzi = 0.0f, dop = 0.0f, ex = 0.0f, ey = 0.0f;
         float gcx = 0.0f, gcy = 0.0f;  // low-pass term: direct gradient of the projected centre
         PixEval e;
         const bool contrib = eval_pixel<LP>(s, X, Y, e) & (pos < my_last);
@@ -732,6 +749,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
             dv1 = dv * e.iw;
             dw1 = -(du * u + dv * vv + dz * z) * e.iw;
             dzi = dz * e.iw;
+            ex = e.dx;
+            ey = e.dy;
           }
         }
         if constexpr (MODE == kFull) s_om[ke][tid] = w;
@@ -743,24 +762,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
           nextdot = g_sd[max(kp, 0) * kTilePix];
         }
         if (__any(contrib)) {
-          float* f = &s_geo[wave][ng & 1][0][lane];
+          float* f = &s_geo[wave][ng & 1][0][slot];
           f[0] = du1;
           f[64] = dv1;
           f[128] = dw1;
           f[192] = dop;
-          float* fc = &s_col[wave][0][ng][lane];
+          f[256] = ex;
+          f[320] = ey;
+          float* fc = &s_col[wave][0][ng][slot];
           fc[0] = w;
           fc[256] = dzi;
           if constexpr (LP) {
             fc[512] = gcx;
             fc[768] = gcy;
           }
-          // the offsets keep their relative accuracy where they are small (a
-          // thin surfel's chain rule amplifies their error by its aspect)
-          const double offd = (col == 1 ? s.xc : s.yc) - mcol;
-          const float off = (float)offd, offl = (float)(offd - (double)off);
-          const bool xy = col == 1 || col == 2;
-          if (lane < 8) s_off[wave][ng & 1][lane] = xy ? (lane < 4 ? off : offl) : 0.0f;
           has |= 1u << ke;
           group |= (uint32_t)ke << (8 * ng);
           ++ng;
@@ -854,7 +869,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
               float g[8];
 #pragma unroll
               for (int u = 0; u < 8; ++u) {
-                const int p = p0 + u, lx = tile_lx(ct, p), ly = tile_ly(ct, p);
+                const int p = p0 + u, lx = p & (ct.tw - 1), ly = p >> ct.tsh;
                 g[u] = lx < wl && ly < hl ? gt[ly * wc + lx * C] : 0.0f;
               }
 #pragma unroll
@@ -898,7 +913,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
           f4v racc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
           const float* wrow = s_om[16 * eb + li];
           // G of the lane's first pixel (tile column lk, row 0); step t covers
-          // pixels 4 t + lk (four neighbours of a sub-tile row), whose offsets
+          // pixels 4 t + lk (four neighbours of a row), whose offsets
           // from it are the same for all lanes and below 2^29 (W, C and the
           // tile height are bounded)
           const float* gt = g_feat + (tl.pix0 + (int64_t)(ty * ct.th) * W + tx * ct.tw + lk) * C + c;
@@ -909,14 +924,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == kTo
             // the shape values go through an empty asm statement so that the
             // step offsets and bounds are formed here and not kept live
             // across units (64 of them would not fit in the registers)
-            int wc = W * C, cs = C, sw = ct.ssh, sn = ct.tsh - ct.ssh, wlim = wl - lk, hlim = hl;
-            asm volatile("" : "+s"(wc), "+s"(cs), "+s"(sw), "+s"(sn), "+v"(wlim), "+s"(hlim));
+            int wc = W * C, cs = C, sh = ct.tsh, wlim = wl - lk, hlim = hl;
+            asm volatile("" : "+s"(wc), "+s"(cs), "+s"(sh), "+v"(wlim), "+s"(hlim));
             float b[32];
 #pragma unroll
             for (int t = 0; t < 32; ++t) {
-              const int q4 = 4 * (t0 + t), sub = q4 >> 6;  // the sub-tile and the pixel in it
-              const int lx = (q4 & ((1 << sw) - 1)) + ((sub & ((1 << sn) - 1)) << sw);
-              const int ly = ((q4 & 63) >> sw) + ((sub >> sn) << (6 - sw));
+              const int q4 = 4 * (t0 + t), lx = q4 & ((1 << sh) - 1), ly = q4 >> sh;
               b[t] = lx < wlim && ly < hlim && c < C ? gt[ly * wc + lx * cs] : 0.0f;
             }
 #pragma unroll
