@@ -253,16 +253,18 @@ __device__ inline void write_pair_total(uint32_t* status, uint64_t total, uint64
 
 // ------------------------------------------------------------ walk record
 // Sub-tile culling of the walks: a wave skips a surfel no pixel centre of its
-// sub-tile can blend.  Per surfel the key stage keeps the ellipse of
+// pixels can blend.  Per surfel the key stage keeps the ellipse of
 // rho <= min(9, 2 ln(255 o)) (beyond it alpha < 1/255), widened like the
 // footprint, as centre (ecx, ecy), half-extents (ex, ey), the y offset of the
 // rightmost point yr, the slope of the chord midpoints and the half-chord
-// factor, so its x-extent over the rows [y0, y1] of the sub-tile is two
+// factor, so its x-extent over the rows [y0, y1] of the wave is two
 // clamps and two square roots.  One lane tests one list entry, so a test
-// costs each pixel 1/64 of that.  The slack covers the FP32 rounding of the
-// record and the test (relative 2^-16 of the extents: a thin ellipse's chord is a
-// difference of terms of the size of its extents).  With the low-pass filter
-// the record is the box of the ellipse and the filter's disk.
+// costs each pixel 1/64 of that.  The ellipse comes from the same FP64
+// projection as the walk record, so it is the hit test's own; the slack
+// covers the rounding of the record to FP32 and the FP32 test (relative 2^-16
+// of the extents: a thin ellipse's chord is a difference of terms of the size
+// of its extents).  With the low-pass filter the record is the box of the
+// ellipse and the filter's disk.
 struct CullRec {
   float4 e0;  // ecx, ecy, ex, ey
   float4 e1;  // yr, slope, half-chord factor, slack (low-pass: xc, yc, rf2, slack)

@@ -32,7 +32,6 @@ struct Key {
   float mc2, p, q, xc, yc, A00, A01, A10, A11, dA;
   float nc[3];
   Foot f;
-  CullRec cr;
 };
 
 // Opacity-aware footprint radius^2 (an exact work reduction): a pixel is
@@ -58,9 +57,8 @@ __device__ __forceinline__ float cull_foot2(float o) {
 // foot2: footprint radius^2 (kFoot2, or the opacity-aware bound).  The cull
 // decisions always use kFoot2, so both footprints keep the same visible set.
 // lowpass: the footprint also takes the low-pass filter's disk.
-// cull2: radius^2 of the walks' culling ellipse (at most foot2).
 __device__ __forceinline__ Key key_stage(const float* mu, const float* sc, const float* qq, const Cam& k, float foot2,
-                                      float cull2, int mode, int lowpass) {
+                                      int mode, int lowpass) {
   Key r;
   r.cull = 0;
   r.flip = 0;
@@ -131,23 +129,6 @@ __device__ __forceinline__ Key key_stage(const float* mu, const float* sc, const
   r.f.xc = xc;
   r.f.yc = yc;
   r.f.rf2 = lowpass ? 0.5f * foot2 + kLpPad : 0.0f;
-  if (lowpass) {
-    const float rf = sqrtf(r.f.rf2);
-    const float x0 = fminf(r.f.ecx - r.f.ex, xc - rf), x1 = fmaxf(r.f.ecx + r.f.ex, xc + rf);
-    const float y0 = fminf(r.f.ecy - r.f.ey, yc - rf), y1 = fmaxf(r.f.ecy + r.f.ey, yc + rf);
-    r.cr.e0 = make_float4(0.5f * (x0 + x1), 0.5f * (y0 + y1), 0.5f * (x1 - x0), 0.5f * (y1 - y0));
-    r.cr.e1 = make_float4(xc, yc, r.f.rf2, 0.0f);
-  } else {  // the same ellipse formulas at cull2 (not part of a decision)
-    const float gc = 1.0f - cull2 * g2, c2 = cull2 / gc;
-    const float T00 = c2 * ((A00 * A00 + A01 * A01) + c2 * (w0 * w0));
-    const float T01 = c2 * ((A00 * A10 + A01 * A11) + c2 * (w0 * w1));
-    const float T11 = c2 * ((A10 * A10 + A11 * A11) + c2 * (w1 * w1));
-    const float tx = __builtin_amdgcn_sqrtf(T00), it = __builtin_amdgcn_rcpf(T11);
-    r.cr.e0 = make_float4(xc - c2 * w0, yc - c2 * w1, tx, __builtin_amdgcn_sqrtf(T11));
-    r.cr.e1 = make_float4(T01 * __builtin_amdgcn_rcpf(tx), T01 * it,
-                          fabsf(c2 * dA) * it * __builtin_amdgcn_rsqf(gc), 0.0f);
-  }
-  r.cr.e1.w = 0x1p-6f + 0x1p-16f * (r.cr.e0.z + r.cr.e0.w) + 0x1p-20f * (fabsf(r.cr.e0.x) + fabsf(r.cr.e0.y));
   if (mode == kSphere) {
     const float hs = 0.5f * (S00 + S11);
     const float hd = 0.5f * (S00 - S11);
@@ -157,12 +138,54 @@ __device__ __forceinline__ Key key_stage(const float* mu, const float* sc, const
   return r;
 }
 
+// Culling record (CullRec) of a visible surfel from the walk record's FP64
+// quantities: the hit test is FP64, and in FP32 the camera-space position alone
+// is off by fx 2^-24 (|R mu| + |t|) / z pixels, more than any fixed slack once
+// the world's origin is some hundred metres from the camera.  Here only the
+// last steps are FP32, with relative errors near 2^-22 of the extents.  lp:
+// the low-pass filter, whose record is a box and keeps the key stage's
+// centre and rf2 (the emission's footprint).  A surfel that the FP64 values put
+// across the camera plane has no ellipse: infinite slack, never culled.
+__device__ __forceinline__ CullRec cull_record(double A00, double A01, double A10, double A11, double p, double q,
+                                               double xc, double yc, float cull2, int lp, const Foot& f) {
+  CullRec c;
+  const double gd = 1.0 - (double)cull2 * (p * p + q * q);
+  const float gc = (float)gd, a00 = (float)A00, a01 = (float)A01, a10 = (float)A10, a11 = (float)A11;
+  const float w0 = (float)(A00 * p + A01 * q), w1 = (float)(A10 * p + A11 * q);
+  const float c2 = cull2 * __builtin_amdgcn_rcpf(gc);
+  const float T00 = c2 * ((a00 * a00 + a01 * a01) + c2 * (w0 * w0));
+  const float T01 = c2 * ((a00 * a10 + a01 * a11) + c2 * (w0 * w1));
+  const float T11 = c2 * ((a10 * a10 + a11 * a11) + c2 * (w1 * w1));
+  const float ex = __builtin_amdgcn_sqrtf(T00), ey = __builtin_amdgcn_sqrtf(T11);
+  const double cx = xc - (double)(c2 * w0), cy = yc - (double)(c2 * w1);
+  if (lp) {
+    const float rf = sqrtf(f.rf2);
+    const double x0 = fmin(cx - (double)ex, xc - (double)rf), x1 = fmax(cx + (double)ex, xc + (double)rf);
+    const double y0 = fmin(cy - (double)ey, yc - (double)rf), y1 = fmax(cy + (double)ey, yc + (double)rf);
+    c.e0 = make_float4((float)(0.5 * (x0 + x1)), (float)(0.5 * (y0 + y1)), (float)(0.5 * (x1 - x0)),
+                       (float)(0.5 * (y1 - y0)));
+    c.e1 = make_float4(f.xc, f.yc, f.rf2, 0.0f);
+  } else {
+    const float it = __builtin_amdgcn_rcpf(T11);
+    c.e0 = make_float4((float)cx, (float)cy, ex, ey);
+    c.e1 = make_float4(T01 * __builtin_amdgcn_rcpf(ex), T01 * it,
+                       fabsf(c2 * (float)(A00 * A11 - A01 * A10)) * it * __builtin_amdgcn_rsqf(gc), 0.0f);
+  }
+  c.e1.w = 0x1p-6f + 0x1p-16f * (c.e0.z + c.e0.w) + 0x1p-20f * (fabsf(c.e0.x) + fabsf(c.e0.y));
+  if (!(gd > 0.0)) {
+    c.e0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    c.e1.w = INFINITY;
+  }
+  return c;
+}
+
 // Walk record of a visible surfel (not part of any decision): the centred,
 // depth-normalised homography's A^-1, e = (p, q) A^-1 and the projected centre,
-// evaluated and kept in FP64 (the per-pixel solve is FP64 as well).
+// evaluated and kept in FP64 (the per-pixel solve is FP64 as well).  cull2:
+// radius^2 of the walks' culling ellipse.
 __device__ __forceinline__ void walk_record(const float* mu_f, const float* sc, const float* qf, float o,
-                                         const float* rgb, const float* nc, const CullRec& cr, const Cam& k,
-                                         WalkRec* out) {
+                                         const float* rgb, const float* nc, const Foot& f, float cull2, int lp,
+                                         const Cam& k, WalkRec* out) {
   const double q0 = qf[0], q1 = qf[1], q2 = qf[2], q3 = qf[3];
   const double rn = 1.0 / sqrt(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
   const double w = q0 * rn, x = q1 * rn, y = q2 * rn, z = q3 * rn;
@@ -190,7 +213,7 @@ __device__ __forceinline__ void walk_record(const float* mu_f, const float* sc, 
   r.d3 = make_double2(xc, yc);
   r.f0 = make_float4((float)mc[2], o, rgb[0], rgb[1]);
   r.f1 = make_float4(rgb[2], nc[0], nc[1], nc[2]);
-  r.c = cr;
+  r.c = cull_record(A00, A01, A10, A11, p, q, xc, yc, cull2, lp, f);
   *out = r;
 }
 
@@ -339,15 +362,16 @@ __global__ __launch_bounds__(256) void k_preprocess(
   bool listed = false;
   if (valid) {
     const float foot2 = opacity_foot ? opacity_foot2(opacity[i]) : kFoot2;
-    kk = key_stage(means + 3 * i, scales + 2 * i, quats + 4 * i, cam, foot2, fminf(foot2, cull_foot2(opacity[i])),
-                   mode, lowpass);
+    kk = key_stage(means + 3 * i, scales + 2 * i, quats + 4 * i, cam, foot2, mode, lowpass);
     ids[v] = (uint32_t)v;
     cull[v] = kk.cull | (kk.flip << 8);  // bit 8: normal flipped toward the camera
     key[v] = kk.cull != 0 ? 0xFFFFFFFFu : __float_as_uint(kk.mc2);
     if (kk.cull == 0) {
       fp[2 * v] = make_float4(kk.f.ecx, kk.f.ecy, kk.f.ex, kk.f.ey);
       fp[2 * v + 1] = make_float4(kk.f.S01, kk.f.S11, kk.f.gam, kk.f.kk);
-      walk_record(means + 3 * i, scales + 2 * i, quats + 4 * i, opacity[i], rgb + 3 * i, kk.nc, kk.cr, cam, rec + v);
+      const float cull2 = lowpass ? foot2 : fminf(foot2, cull_foot2(opacity[i]));
+      walk_record(means + 3 * i, scales + 2 * i, quats + 4 * i, opacity[i], rgb + 3 * i, kk.nc, kk.f, cull2, lowpass,
+                  cam, rec + v);
       listed = foot_box(kk.f, mode, cam.W, cam.H, ct.tw, ct.th, ct.ntx[b], ct.nty[b], box);
     }
   }
