@@ -157,7 +157,7 @@ struct Layout {
   int64_t n, nreal, cap, tiles, spix;  // n = virtual surfels; spix = tiles * 256 (tile-major pixels)
   int k, c, ncam;
   size_t rec, fp, key0, key1, id0, id1, vbase, count, offs, cull, ptile0, ptile1, eid0, eid1, sid_emit, pid, ranges,
-      torder0, wide, nlast, tfinal, selpos, selw, seldot, gflag, fflag, gpart, fpart, hist, bsum, ubits, heavy,
+      torder0, wide, nlast, tfinal, selpos, selw, seldot, gflag, fflag, gpart, fpart, hist, bsum, ubits, heavy, hbits,
       status, total;
 };
 
@@ -209,12 +209,14 @@ inline Layout make_layout(const CamTable& ct, int k, int c, int64_t cap) {
   const int64_t nb = cdiv(big, kSortTile);
   L.hist = take((256 * nb + 256) * 4);
   L.bsum = take((cdiv(n1, kScanTile) + 1) * 8);
-  // one bit per virtual surfel: selected somewhere (stats read-back); in the
-  // backward, per surfel: its pairs are summed by a block of its own
-  L.ubits = take(cdiv(n1, 32) * 4);
+  L.ubits = take(cdiv(n1, 32) * 4);  // one bit per virtual surfel: selected somewhere (stats read-back)
   // surfels with more than kHeavyRows flagged rows: the rows are pairs, whose
   // ranges are disjoint inside the capacity, so at most cap / (kHeavyRows + 1)
   L.heavy = take((cap1 / (kHeavyRows + 1) + 1) * 4);
+  // in the backward, a bit per surfel: its pairs are summed by a block of its
+  // own.  In the depth sort's second buffer, which nothing reads after the sort
+  // (not with the read-back's bits: it may run beside a backward)
+  L.hbits = L.key1;
   L.total = o;
   return L;
 }

@@ -1565,7 +1565,7 @@ static void backward_typed(const SurfelArgs& s, const CamTable& ct, int blend, c
   const uint32_t* count = (const uint32_t*)(ws + L.count);
   if (s.n > 0) {
     const GeoGrads gg{gr.means, gr.scales, gr.quats, gr.opacity, gr.rgb};
-    uint64_t* hbits = (uint64_t*)(ws + L.ubits);  // a bit per surfel (the region holds one per virtual surfel)
+    uint64_t* hbits = (uint64_t*)(ws + L.hbits);  // a bit per surfel (the region holds a word per virtual surfel)
     hipLaunchKernelGGL(k_reduce_geo, dim3((unsigned)cdiv(s.n, 256)), dim3(256), 0, st, s.n, ct, vbase, count, L.cap,
                        (const float*)(ws + L.gpart), (const uint8_t*)(ws + L.gflag), s.means, s.scales, s.quats,
                        (const int32_t*)(ws + L.cull), gg, hbits);
