@@ -18,7 +18,7 @@
 //   A lower bound of every score comes from the matrix cores; only components
 //   whose bound does not exceed the best exact score are scored, in the
 //   prescribed order, so the assignment is bit for bit the full scan's.
-//   Bound (y = x - c0, m = mu - c0, c0 = component 0's mean; eigenpairs
+//   Bound (y = x - c0, m = mu - c0, c0 = the mean of the components'; eigenpairs
 //   l1 >= l2 >= l3, v1..v3 of the precision): the score is at least
 //     a |y - m|^2 + b1 (v1.(y-m))^2 + b2 (v2.(y-m))^2 + c - margins,
 //   a = l3, b_i = l_i - l3: one product linear in (y, |y|^2, 1) and two in
@@ -101,10 +101,36 @@ __device__ __forceinline__ void store_row(uint4* op, int row, const double u[4],
   op[48 + row] = uint4{k.h | k.m << 16, k.l, L.x, L.y};
 }
 
-// record: mean (3), precision xx xy xz yy yz zz (6), constant (1), normal (3)
-__global__ void k_gmm_prep(int k, const float* __restrict__ mean, const float* __restrict__ cov,
+// Origin of the bound's coordinates: the mean of up to 512 of the component
+// means, the same in every block; the margins grow with the distance to it.
+__device__ __forceinline__ void bound_origin(int k, const float* __restrict__ mean, float c[3]) {
+  float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  const int step = (k + 511) / 512;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int j = step * (64 * i + (int)threadIdx.x);
+    const float* m = mean + 3 * (size_t)min(j, k - 1);
+    const float x = m[0], y = m[1], z = m[2];
+    const bool in = j < k && fabsf(x) <= kGmmSpan && fabsf(y) <= kGmmSpan && fabsf(z) <= kGmmSpan;
+    s[0] += in ? x : 0.0f;
+    s[1] += in ? y : 0.0f;
+    s[2] += in ? z : 0.0f;
+    s[3] += in ? 1.0f : 0.0f;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s[i] += __shfl_xor(s[i], o, 64);
+  for (int i = 0; i < 3; ++i) c[i] = s[i] / fmaxf(s[3], 1.0f);
+}
+
+// record: mean (3), precision xx xy xz yy yz zz (6), constant (1), normal (3),
+// the bound's origin (3)
+__global__ __launch_bounds__(64) void k_gmm_prep(int k, const float* __restrict__ mean, const float* __restrict__ cov,
                            const float* __restrict__ weight, float* __restrict__ rec, uint4* __restrict__ ops) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  float org[3];
+  bound_origin(k, mean, org);
   uint4* op = ops + (size_t)(j / kGmmTile) * (kGmmTileBytes / 16);
   const int row = j % kGmmTile;
   const double zero[4] = {0.0, 0.0, 0.0, 0.0};
@@ -201,7 +227,9 @@ __global__ void k_gmm_prep(int k, const float* __restrict__ mean, const float* _
   r[10] = (float)v1[0];
   r[11] = (float)v1[1];
   r[12] = (float)v1[2];
-  r[13] = r[14] = r[15] = 0.0f;
+  r[13] = org[0];
+  r[14] = org[1];
+  r[15] = org[2];
 
   // the bound's rows
   const double cst = (double)r[9];
@@ -209,9 +237,9 @@ __global__ void k_gmm_prep(int k, const float* __restrict__ mean, const float* _
   bool safe = true;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    const float c0 = mean[q], mq = mean[3 * (size_t)j + q];
-    safe = safe && fabsf(c0) <= kGmmSpan && fabsf(mq) <= kGmmSpan;
-    m[q] = (double)mq - (double)c0;
+    const float mq = mean[3 * (size_t)j + q];
+    safe = safe && fabsf(mq) <= kGmmSpan;
+    m[q] = (double)mq - (double)org[q];
     mm += m[q] * m[q];
   }
   // the adjugate's FP64 rounding stays within the margins for e3^2 <= 1e12 e1 e2
@@ -271,11 +299,28 @@ __device__ __forceinline__ void keep_lower(float s, int j, float& bs, int& bi) {
   bi = up ? j : bi;
 }
 
+// Where bounds tell little (components much thinner than their distance from
+// the origin times 2^-17, or surfels so many deviations away that the share
+// kTheta of their scores exceeds the components' differences), a wave is
+// better off scoring every component, a lane per surfel.  Seen twice: after an
+// eighth of the components, by more than kGmmMany undecided lanes of its first
+// kGmmProbe tiles (from 256 components on: below, the bounds cost less than
+// the look); and by the number of lane groups left to score in the end, a scan
+// of one being about 30 instructions per 256 components and 200 for its
+// exchange, against 27 per component.  The whole call on 1M surfels, a fifth to
+// a third of them off the planes, as plain scan / with bounds and scans of lane
+// groups only / this, us: 60 m of planes, 512 components of 0.5 mm 352 / 410 /
+// 340, 2000 of 2 mm 1134 / 2572 / 1234; a 100 m street 512 of 2 mm 354 / 417 /
+// 325, of 0.5 mm 348 / 612 / 389, 2000 of 2 mm 1138 / 4267 / 1227; 3 cm (what
+// bounds are for) 364 / 136 / 142.
+constexpr int kGmmProbe = 2, kGmmMany = 4;
+__device__ __forceinline__ int plain_scans(int k) { return (int)(27ll * k / (30 * ((k + 255) / 256) + 200)); }
+
 // A wave takes 64 surfels in four column tiles: lane (g, c) of tile t sees
 // surfel 16 t + c against components 4 g .. 4 g + 3 of each component tile.
 // Per such quad the smallest bound is kept with the quad's number in its low
 // bits (`low` accounts for them), the smallest two per lane.
-__global__ __launch_bounds__(kGeoThreads) void k_geo_loss(
+__global__ __launch_bounds__(kGeoThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_geo_loss(
     int64_t n, const float* __restrict__ means, const float* __restrict__ scales, const float* __restrict__ quats,
     int k, const float* __restrict__ rec, const uint4* __restrict__ ops, float lambda_n, int32_t* __restrict__ assign,
     float* __restrict__ d_means, float* __restrict__ d_scales, float* __restrict__ d_quats,
@@ -297,7 +342,7 @@ __global__ __launch_bounds__(kGeoThreads) void k_geo_loss(
   bool wild;  // a surfel that the margins do not cover
   Bf8 pt[4];
   {
-    float y0 = x0 - rec[0], y1 = x1 - rec[1], y2 = x2 - rec[2];
+    float y0 = x0 - rec[13], y1 = x1 - rec[14], y2 = x2 - rec[15];
     wild = !(fabsf(y0) <= kGmmSpan && fabsf(y1) <= kGmmSpan && fabsf(y2) <= kGmmSpan);
     if (wild) y0 = y1 = y2 = 0.0f;
     const Split s0 = split3(y0), s1 = split3(y1), s2 = split3(y2), s3 = split3((y0 * y0 + y1 * y1) + y2 * y2);
@@ -316,13 +361,34 @@ __global__ __launch_bounds__(kGeoThreads) void k_geo_loss(
   float v1[4], v2[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) v1[t] = v2[t] = kNone;
+  // whether the wave scores every component instead
+  bool plain = 4 * __popcll(__ballot(wild)) > plain_scans(k);
+  const auto contended = [&]() {
+    int c = 0;
+#pragma unroll
+    for (int t = 0; t < kGmmProbe; ++t) {
+      const int from = 16 * t + (lane & 15);
+      float vm = fminf(v1[t], __shfl_xor(v1[t], 16, 64));
+      vm = fminf(vm, __shfl_xor(vm, 32, 64));
+      const float4* r = (const float4*)(rec + (size_t)kGmmRec * min((int)(__float_as_uint(vm) & idmask) * 4 + g, k - 1));
+      const float4 a0 = r[0], a1 = r[1], a2 = r[2];
+      float s = score(__shfl(x0, from, 64), __shfl(x1, from, 64), __shfl(x2, from, 64), a0, a1, a2.x, a2.y);
+      s = fminf(s, __shfl_xor(s, 16, 64));
+      s = fminf(s, __shfl_xor(s, 32, 64));
+      c += __popcll(__ballot(!(v2[t] - fabsf(v2[t]) * slack > s)));
+    }
+    return c > kGmmMany;
+  };
+  const int probe = tiles >= 16 ? tiles / 8 : -1;
   for (int k0 = 0; k0 < tiles; k0 += kGmmChunk) {
     const int nt = min(kGmmChunk, tiles - k0);
-    __syncthreads();
+    if (k0 == 0) __syncthreads();
+    else if (__syncthreads_and(plain)) break;
     for (int t = threadIdx.x; t < nt * (kGmmTileBytes / 16); t += kGeoThreads)
       s_op[t] = ops[(size_t)k0 * (kGmmTileBytes / 16) + t];
     __syncthreads();
-    for (int j = 0; j < nt; ++j) {
+    for (int j = 0; j < nt && !plain; ++j) {
+      if (k0 + j == probe) plain = contended();
       const uint4* o = s_op + j * (kGmmTileBytes / 16) + lane;
       const Bf8 U = __builtin_bit_cast(Bf8, o[0]), A = __builtin_bit_cast(Bf8, o[64]),
                 B = __builtin_bit_cast(Bf8, o[128]);
@@ -343,89 +409,129 @@ __global__ __launch_bounds__(kGeoThreads) void k_geo_loss(
       }
     }
   }
-  // exact scores: per surfel the quad of the smallest bound, a component a
-  // lane, while a lane's smallest bound does not exceed the best score
-  float bs[4], ball[4], x[4][3];
-  int bi[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    bs[t] = ball[t] = INFINITY;
-    bi[t] = 0x7fffffff;
-    const int from = 16 * t + (lane & 15);
-    x[t][0] = __shfl(x0, from, 64);
-    x[t][1] = __shfl(x1, from, 64);
-    x[t][2] = __shfl(x2, from, 64);
-    if (__shfl((int)wild, from, 64)) {
-      v1[t] = kNone;
-      v2[t] = -kNone;
-    }
-  }
-#pragma unroll 1
-  for (int it = 0; it < 4; ++it) {  // a lane group is taken once
-    bool act[4], any = false;
-    int cand[4];
-    float4 ra[4], rb[4];
-    float2 rc[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      float vm = fminf(v1[t], __shfl_xor(v1[t], 16, 64));
-      vm = fminf(vm, __shfl_xor(vm, 32, 64));
-      act[t] = vm < 2e38f && !(vm - fabsf(vm) * slack > ball[t]);
-      any = any || act[t];
-      cand[t] = act[t] ? (int)(__float_as_uint(vm) & idmask) * 4 + g : k;
-      v1[t] = (act[t] & (v1[t] == vm)) ? kNone : v1[t];
-    }
-    if (!__any(any)) break;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const float4* r = (const float4*)(rec + (size_t)kGmmRec * min(cand[t], k - 1));
-      ra[t] = r[0];
-      rb[t] = r[1];
-      rc[t] = *(const float2*)(r + 2);
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const float s = score(x[t][0], x[t][1], x[t][2], ra[t], rb[t], rc[t].x, rc[t].y);
-      keep_lower(cand[t] < k ? s : INFINITY, cand[t], bs[t], bi[t]);
-      ball[t] = fminf(bs[t], __shfl_xor(bs[t], 16, 64));
-      ball[t] = fminf(ball[t], __shfl_xor(ball[t], 32, 64));
-    }
-  }
-  // a lane whose second bound is not above the best score: its quads are
-  // scored by the whole wave
   float ms = INFINITY;
   int mi = 0x7fffffff;  // this lane's surfel (tile g, column lane & 15)
+  if (!plain) [&]() {
+    // exact scores: per surfel the quad of the smallest bound, a component a
+    // lane, while a lane's smallest bound does not exceed the best score
+    float bs[4], ball[4], x[4][3];
+    int bi[4];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    uint64_t todo = __ballot(!(v2[t] - fabsf(v2[t]) * slack > ball[t]));
-    while (todo) {
-      const int from = __ffsll((unsigned long long)todo) - 1;
-      todo &= todo - 1;
-      const float y0 = __shfl(x[t][0], from, 64), y1 = __shfl(x[t][1], from, 64), y2 = __shfl(x[t][2], from, 64);
-      float ws = INFINITY;
-      int wi = 0x7fffffff;
-      for (int j = 16 * (lane >> 2) + 4 * (from >> 4) + (lane & 3); j < k; j += 256) {
-        const float4* r = (const float4*)(rec + (size_t)kGmmRec * j);
-        const float4 a0 = r[0], a1 = r[1], a2 = r[2];
-        keep_lower(score(y0, y1, y2, a0, a1, a2.x, a2.y), j, ws, wi);
+    for (int t = 0; t < 4; ++t) {
+      bs[t] = ball[t] = INFINITY;
+      bi[t] = 0x7fffffff;
+      const int from = 16 * t + (lane & 15);
+      x[t][0] = __shfl(x0, from, 64);
+      x[t][1] = __shfl(x1, from, 64);
+      x[t][2] = __shfl(x2, from, 64);
+      if (__shfl((int)wild, from, 64)) {
+        v1[t] = kNone;
+        v2[t] = -kNone;
+      }
+    }
+#pragma unroll 1
+    for (int it = 0; it < 4; ++it) {  // a lane group is taken once
+      bool act[4], any = false;
+      int cand[4];
+      float4 ra[4], rb[4];
+      float2 rc[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        float vm = fminf(v1[t], __shfl_xor(v1[t], 16, 64));
+        vm = fminf(vm, __shfl_xor(vm, 32, 64));
+        act[t] = vm < 2e38f && !(vm - fabsf(vm) * slack > ball[t]);
+        any = any || act[t];
+        cand[t] = act[t] ? (int)(__float_as_uint(vm) & idmask) * 4 + g : k;
+        v1[t] = (act[t] & (v1[t] == vm)) ? kNone : v1[t];
+      }
+      if (!__any(any)) break;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const float4* r = (const float4*)(rec + (size_t)kGmmRec * min(cand[t], k - 1));
+        ra[t] = r[0];
+        rb[t] = r[1];
+        rc[t] = *(const float2*)(r + 2);
       }
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const float os = __shfl_xor(ws, o, 64);
-        const int oi = __shfl_xor(wi, o, 64);
-        keep_lower(os, oi, ws, wi);
+      for (int t = 0; t < 4; ++t) {
+        const float s = score(x[t][0], x[t][1], x[t][2], ra[t], rb[t], rc[t].x, rc[t].y);
+        keep_lower(cand[t] < k ? s : INFINITY, cand[t], bs[t], bi[t]);
+        ball[t] = fminf(bs[t], __shfl_xor(bs[t], 16, 64));
+        ball[t] = fminf(ball[t], __shfl_xor(ball[t], 32, 64));
       }
-      keep_lower(lane == from ? ws : INFINITY, wi, bs[t], bi[t]);
+    }
+    // a lane whose second bound is not above the best score: its quads are
+    // scored by the whole wave
+    uint64_t todos[4];
+    int scans = 0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      todos[t] = __ballot(!(v2[t] - fabsf(v2[t]) * slack > ball[t]));
+      scans += __popcll(todos[t]);
+    }
+    if (scans > plain_scans(k)) {
+      plain = true;
+      return;
     }
 #pragma unroll
-    for (int o = 16; o <= 32; o <<= 1) {
-      const float os = __shfl_xor(bs[t], o, 64);
-      const int oi = __shfl_xor(bi[t], o, 64);
-      keep_lower(os, oi, bs[t], bi[t]);
+    for (int t = 0; t < 4; ++t) {
+      uint64_t todo = todos[t];
+      while (todo) {
+        const int from = __ffsll((unsigned long long)todo) - 1;
+        todo &= todo - 1;
+        const float y0 = __shfl(x[t][0], from, 64), y1 = __shfl(x[t][1], from, 64), y2 = __shfl(x[t][2], from, 64);
+        float ws = INFINITY;
+        int wi = 0x7fffffff;
+        for (int j = 16 * (lane >> 2) + 4 * (from >> 4) + (lane & 3); j < k; j += 256) {
+          const float4* r = (const float4*)(rec + (size_t)kGmmRec * j);
+          const float4 a0 = r[0], a1 = r[1], a2 = r[2];
+          keep_lower(score(y0, y1, y2, a0, a1, a2.x, a2.y), j, ws, wi);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+          const float os = __shfl_xor(ws, o, 64);
+          const int oi = __shfl_xor(wi, o, 64);
+          keep_lower(os, oi, ws, wi);
+        }
+        keep_lower(lane == from ? ws : INFINITY, wi, bs[t], bi[t]);
+      }
+#pragma unroll
+      for (int o = 16; o <= 32; o <<= 1) {
+        const float os = __shfl_xor(bs[t], o, 64);
+        const int oi = __shfl_xor(bi[t], o, 64);
+        keep_lower(os, oi, bs[t], bi[t]);
+      }
+      if (t == g) {
+        ms = bs[t];
+        mi = bi[t];
+      }
     }
-    if (t == g) {
-      ms = bs[t];
-      mi = bi[t];
+  }();
+  if (plain) {
+    // records two ahead, through the scalar cache (the last one again past the
+    // end, which cannot win: strict, of equal scores the lowest index stays)
+    struct Rec {
+      float4 a, b;
+      float2 c;
+    };
+    const auto at = [&](int j) {
+      const float4* r = (const float4*)(rec + (size_t)kGmmRec * min(j, k - 1));
+      return Rec{r[0], r[1], *(const float2*)(r + 2)};
+    };
+    Rec r0 = at(0), r1 = at(1);
+#pragma unroll 2
+    for (int j = 0; j < k; j += 2) {
+      const Rec n0 = at(j + 2), n1 = at(j + 3);
+      const float s0 = score(x0, x1, x2, r0.a, r0.b, r0.c.x, r0.c.y);
+      const bool up0 = s0 < ms;
+      ms = up0 ? s0 : ms;
+      mi = up0 ? j : mi;
+      const float s1 = score(x0, x1, x2, r1.a, r1.b, r1.c.x, r1.c.y);
+      const bool up1 = s1 < ms;
+      ms = up1 ? s1 : ms;
+      mi = up1 ? j + 1 : mi;
+      r0 = n0;
+      r1 = n1;
     }
   }
   const int bk = ms < INFINITY ? mi : 0;
