@@ -379,8 +379,10 @@ struct PixEval {
 
 // Evaluated without branches: a wave reaches it with entries that meet its
 // sub-tile, of which nearly every one has a pixel that hits.  A pixel that
-// has stopped passes x = NaN, which fails the hit test.
-template <bool LP = false>
+// has stopped passes x = NaN, which fails the hit test.  EARLY: leave at the
+// hit test, for a walk that takes every entry of the tile (most have no pixel
+// of the wave).
+template <bool LP = false, bool EARLY = false>
 __device__ __forceinline__ bool eval_pixel(const LRec& s, double x, double y, PixEval& e) {
   const double dx = x - s.xc, dy = y - s.yc;
   const double u1 = fma(s.a00, dx, s.a01 * dy);
@@ -388,6 +390,7 @@ __device__ __forceinline__ bool eval_pixel(const LRec& s, double x, double y, Pi
   const double w1 = 1.0 - fma(s.e0, dx, s.e1 * dy);
   const double num = fma(u1, u1, v1 * v1), w2 = w1 * w1;
   bool hit = (w1 > 0.0) & (num <= 9.0 * w2);
+  if (EARLY && !LP && !hit) return false;
   e.filt = false;
   e.dx = (float)dx;
   e.dy = (float)dy;
@@ -399,6 +402,7 @@ __device__ __forceinline__ bool eval_pixel(const LRec& s, double x, double y, Pi
     const double rf = 2.0 * fma(dx, dx, dy * dy);
     const bool splat = (w1 > 0.0) & (num <= rf * w2);
     hit = splat ? num <= 9.0 * w2 : rf <= 9.0;
+    if (EARLY && !hit) return false;
     e.filt = !splat;
     e.iw = splat ? e.iw : 1.0f;
     e.u = splat ? e.u : 0.0f;

@@ -467,7 +467,7 @@ __global__ __launch_bounds__(256) void k_full_feat(const WalkRec* __restrict__ r
         if (base + k >= my_last) break;
         const LRec s = s_r.get(k);
         PixEval ev;
-        if (!eval_pixel<LP>(s, X, Y, ev)) continue;
+        if (!eval_pixel<LP, true>(s, X, Y, ev)) continue;
         const float w = ev.alpha * T;
 #pragma unroll
         for (int c = 0; c < CH; ++c) acc[c] = fmaf(w, s_f[k][c], acc[c]);
