@@ -11,7 +11,6 @@ namespace psm {
 
 // ----------------------------------------------------------------- constants
 // Cutoff r = 3 in tangent units ("3 sigma", Sec. 5), applied per pixel.
-constexpr float kCut2 = 9.0f;
 constexpr float kCut = 3.0f;
 // Footprint radius^2 = 9 (1 + 2^-10): a superset of the FP32 per-pixel test.
 constexpr float kFoot2 = 9.0087890625f;
@@ -484,9 +483,6 @@ __device__ __forceinline__ float dpp_mov(float v) {
 }
 constexpr int kDppRowRor8 = 0x128;      // lane l <- lane l ^ 8 within a row
 constexpr int kDppRowRor4 = 0x124;      // lane l <- lane l - 4 within a row
-constexpr int kDppRowHalfMirror = 0x141;  // lane l <- lane 7 - l within 8 lanes
-constexpr int kDppXor2 = 0x4E;          // quad_perm [2,3,0,1]
-constexpr int kDppXor1 = 0xB1;          // quad_perm [1,0,3,2]
 
 // x + x(lane ^ 32) (first) and y + y(lane ^ 32) (second), for the lanes whose
 // bit 5 selects x (lanes 0-31) or y (lanes 32-63).
@@ -499,70 +495,6 @@ __device__ __forceinline__ float swap16_add(float x, float y) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-  v = swap32_add(v, v);
-  v = swap16_add(v, v);
-  v += dpp_mov<kDppRowRor8>(v);
-  v += dpp_mov<kDppRowHalfMirror>(v);
-  v += dpp_mov<kDppXor2>(v);
-  v += dpp_mov<kDppXor1>(v);
-  return v;
-}
-
-// Sums 16 per-lane values over the wave: each step halves the number of
-// values a lane carries (16 -> 8 -> 4 -> 2 -> 1), pairing lanes that differ in
-// lane bit 5, 4, 3, 2; then two in-quad steps.  Lane l returns the wave total
-// of value index (l >> 2) & 15.
-__device__ __forceinline__ float wave_reduce16(const float (&v)[16]) {
-  const int lane = threadIdx.x & 63;
-  float a[8], b[4], c[2];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) a[i] = swap32_add(v[i], v[8 + i]);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) b[i] = swap16_add(a[i], a[4 + i]);
-  const bool b3 = lane & 8, b2 = lane & 4;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) c[i] = (b3 ? b[2 + i] : b[i]) + dpp_mov<kDppRowRor8>(b3 ? b[i] : b[2 + i]);
-  float d = (b2 ? c[1] : c[0]) + dpp_mov<kDppRowHalfMirror>(b2 ? c[0] : c[1]);
-  d += dpp_mov<kDppXor2>(d);
-  d += dpp_mov<kDppXor1>(d);
-  return d;
-}
-
-// ------------------------------------------------ feature loads (to float)
-// Storage types: float, __half, and uint16_t holding bf16 bits.
-template <typename FT>
-struct VecN {
-  static constexpr int N = 16 / sizeof(FT);  // elements per 16-byte load
-};
-
-template <typename FT>
-__device__ __forceinline__ void load_vec(const FT* p, float* v);
-template <>
-__device__ __forceinline__ void load_vec<float>(const float* p, float* v) {
-  const float4 x = *reinterpret_cast<const float4*>(p);
-  v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-}
-template <>
-__device__ __forceinline__ void load_vec<__half>(const __half* p, float* v) {
-  const uint4 x = *reinterpret_cast<const uint4*>(p);
-  const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    v[2 * i] = __half2float(__ushort_as_half((unsigned short)(w[i] & 0xFFFF)));
-    v[2 * i + 1] = __half2float(__ushort_as_half((unsigned short)(w[i] >> 16)));
-  }
-}
-template <>
-__device__ __forceinline__ void load_vec<uint16_t>(const uint16_t* p, float* v) {
-  const uint4 x = *reinterpret_cast<const uint4*>(p);
-  const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    v[2 * i] = __uint_as_float(w[i] << 16);
-    v[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-  }
-}
 // LDS ordering between the lanes of one wave (no block barrier involved).
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -593,6 +525,8 @@ __device__ __forceinline__ f4v mfma_16x16x4(float a, float b, f4v c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// ------------------------------------------------ feature loads (to float)
+// Storage types: float, __half, and uint16_t holding bf16 bits.
 template <typename FT>
 __device__ __forceinline__ float load_one(const FT* p);
 template <>
@@ -642,11 +576,5 @@ struct FeatSrc {
     return c < ca ? load_one<FT>(a + row * ca + c) : b[row * cb + (c - ca)];
   }
 };
-
-__device__ __forceinline__ int pow2_ge(int x) {
-  int p = 1;
-  while (p < x) p <<= 1;
-  return p;
-}
 
 }  // namespace psm
