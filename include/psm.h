@@ -105,7 +105,8 @@ typedef struct {
   int32_t bwd_schedule; /* psm_schedule of the backward's tile kernels */
   /* Tile shape: tile_w x (256 / tile_w) pixels, tile_w in {8, 16, 32, 64};
    * 0 = 16 (16 x 16 tiles, Sec. 5's tile-based rasterisation).  One 256-thread
-   * block owns one tile, a wave 8 x 8 of its pixels (16 x 4 at 64).  The pair lists
+   * block owns one tile; in the forward walk a wave owns 8 x 8 of its pixels (16 x 4
+ * at 64), in the backward walk 64 consecutive ones of its rows.  The pair lists
    * follow the tiles; images and the Top-K selection do not depend on the
    * shape (gradients only through the order of their sums).  The read-backs
    * and the backward must use the forward's value. */
@@ -114,8 +115,8 @@ typedef struct {
 
 /* Tile scheduling of the per-tile kernels (forward: schedule, backward:
  * bwd_schedule), one workgroup per tile.  GRID: tiles of neighbouring ids kept
- * on one XCD, as long as all tiles fit on the device at once (1024); beyond,
- * and with PERSISTENT always, the tiles of the longest lists first. */
+ * on one XCD up to 1024 tiles; beyond, and with PERSISTENT always, the tiles of
+ * the longest lists first. */
 typedef enum { PSM_SCHED_GRID = 0, PSM_SCHED_PERSISTENT = 1 } psm_schedule;
 
 /* Skip the end-of-call status read-back (graph-safe; the caller checks
@@ -223,10 +224,11 @@ psm_status psm_backward(psm_ctx* ctx, const psm_surfels* s, const psm_camera* ca
                         void* stream);
 
 /* Reads the counters of the last psm_forward in this workspace into *out
- * (host memory).  For the Top-K blend it first counts the selections on
- * `stream` (two small kernels over the saved selection; a bitmap region of
- * the workspace is overwritten, nothing the backward reads), then
- * synchronises `stream`.  n, cam, cfg, c and pair_capacity must be those of
+ * (host memory).  It first sums the walk's counters, counts the cull codes and,
+ * for the Top-K blend, the selections on `stream` (small kernels over the saved
+ * state; the status block and a bitmap region of the workspace are
+ * overwritten, nothing the backward reads or writes), then synchronises
+ * `stream`.  n, cam, cfg, c and pair_capacity must be those of
  * that forward: the forward records its workspace layout (total bytes, pair
  * capacity, tiles) in the workspace, and this call and the other read-backs
  * return PSM_ERR_INVALID_ARG, before touching anything else in the

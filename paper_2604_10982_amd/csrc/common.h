@@ -377,7 +377,7 @@ struct PixEval {
 };
 
 // Evaluated without branches: a wave reaches it with entries that meet its
-// sub-tile, of which nearly every one has a pixel that hits.  A pixel that
+// pixels, of which nearly every one has a pixel that hits.  A pixel that
 // has stopped passes x = NaN, which fails the hit test.  EARLY: leave at the
 // hit test, for a walk that takes every entry of the tile (most have no pixel
 // of the wave).

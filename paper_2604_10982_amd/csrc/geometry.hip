@@ -33,7 +33,7 @@
 //   score, a surfel out of them the full scan.
 //   One plain scan of 512 components is 27 vector instructions for 64 pairs;
 //   the bound is 3.25 and 3 MFMA for 256.
-//   1M surfels, 512 components: 345 us the scan, 125 us this (prep 17 and 10,
+//   1M surfels, 512 components: 345 us the scan, 129 us this (prep 17 and 10,
 //   the sums 16 and 4).  The loop is bound by issue (64 vector and 12 matrix
 //   instructions a tile of 1024 pairs), about half of the time; the rest is
 //   the split, the exact scores and the FP64 loss terms, once a surfel.

@@ -91,10 +91,15 @@ void launch_single_depth(const Layout& L, char* ws, hipStream_t st);
 void launch_single_pairs(const Layout& L, int bits, char* ws, hipStream_t st);
 
 // Whether a per-tile kernel takes its tiles longest first: when asked to, and
-// always beyond kOrderTiles, where they are not all resident at once (256 CUs
-// x 4 blocks) and the long ones, met late, end the kernel: 1M street surfels at
-// 1080p, XCD order against longest first: walk 644 / 413 us, backward walk
-// 1544 / 847 us, feature adjoint 1808 / 1712 us; the ordering itself 12 us.
+// always beyond kOrderTiles.  Blocks start in the order of their index, and with
+// more tiles than are resident the long ones, met late, end the kernel: 1M
+// street surfels at 1080p, XCD order against longest first: walk 644 / 400 us,
+// backward walk 1544 / 831 us, feature adjoint 1808 / 1680 us; the ordering itself
+// 12 us.  The line is one for all kernels and empirical: of the walks four
+// blocks share a CU (1024 tiles resident), of the feature adjoint and the dense
+// backward two, so below it some kernels gain from the order too (planes at
+// 640 x 400, 1000 tiles: backward 1684 / 1469 us) and others lose (room at
+// 480 x 368: 377 / 388); the caller or the autotuner chooses there.
 constexpr int64_t kOrderTiles = 1024;
 inline bool longest_first(const Layout& L, int sched) { return sched == kSchedPersistent || L.tiles > kOrderTiles; }
 
