@@ -3,7 +3,7 @@
 
 One step = forward + backward of the whole path (preprocess, depth sort,
 count scan, key emission, pair sort, tile ranges, forward walk with Top-K
-heap, Top-K feature blend, feature backward, backward walk, preprocess
+list, Top-K feature blend, feature backward, backward walk, preprocess
 backward) over one 1920x1080 frame of a 1M-surfel plane-structured scene with
 128-d FP32 features, K = 16, exact-ellipse tile lists.  Inputs are synthetic
 (seeded) and already resident in HBM; workspaces and outputs are allocated
@@ -37,7 +37,7 @@ FP32_VALU_PEAK_TFLOPS = 78.6   # 256 CU x 4 SIMD x 16 lanes x 2 flop x 2.4 GHz, 
 # Algorithmic work per unit of the walks (what the method must compute, not
 # what the kernels happen to issue)
 FLOP_PER_EVAL = 17.0       # one pixel x list entry: FP64 centred offset 2, u' 3, v' 3, w' 4, rho w'^2 3, 9 w'^2 test 2
-FLOP_PER_CONTRIB = 26.0    # contributor: 1/w', u, v, rho, exp, alpha, clamp, T', weight, 7 blend FMAs, depth, heap test
+FLOP_PER_CONTRIB = 26.0    # contributor: 1/w', u, v, rho, exp, alpha, clamp, T', weight, 7 blend FMAs, depth, list test
 BWD_FLOP_PER_EVAL = 17.0   # backward: the same test for each entry up to the pixel's last contributor
 BWD_FLOP_PER_CONTRIB = 70.0  # backward contributor: T recovery, e_i, d alpha, d rho, du, dv, dz, 17 terms, suffix
 
